@@ -57,8 +57,10 @@ extern "C" {
 #define LB_ESTATE (-4)  /* call out of order, e.g. stepping before init */
 
 /* Population storage. */
-#define LB_STORE_F64 0  /* raw FP64 populations, 2 x 19 x 8 B per site */
-#define LB_STORE_F32 1  /* raw FP32 populations, 2 x 19 x 4 B per site */
+#define LB_STORE_F64 0  /* raw FP64 populations, 2 x 19 x 8 B per site; between one-read steps
+                           the 23 values they follow from: 19 totals, phase, recolouring vector */
+#define LB_STORE_F32 1  /* raw FP32 populations, 2 x 19 x 4 B per site; between one-read steps
+                           as LB_STORE_F64, 92 B */
 #define LB_STORE_F16 2  /* 16-bit moment-split: per site FP32 density, momentum term of
                            the equilibrium, phase and recolouring vector (32 B) + per
                            direction the deviation of the total population from the
@@ -253,10 +255,10 @@ int64_t lb_footprint_bytes(const lb_params* params);
 
 /* Measurement aid for the roofline of the one-read step (not part of the
  * method): the memory access pattern of the FP32 one-read step on a periodic
- * lattice of params' sizes, with no arithmetic -- per site the 19 (t_i, d_i)
- * pair loads at the pull's upstream sites and the 19 pair stores, on that
- * step's tiles, z chunks, workgroup-to-XCD mapping, two barriers per plane and
- * LDS allocation (params->storage is ignored; tile settings apply as for an
+ * lattice of params' sizes, with no arithmetic -- per site the 19 total loads
+ * at the pull's upstream sites, the site's colour record (16 bytes) and their
+ * stores, on that step's tiles, z chunks, workgroup-to-XCD mapping, look-ahead
+ * loads, two barriers per plane and LDS allocation (params->storage is ignored; tile settings apply as for an
  * FP32 lattice).  Allocates two population buffers, runs 2 untimed and `reps`
  * timed launches on its own stream, frees them, and stores the average launch
  * duration in milliseconds in *ms.  The rate it gives bounds what the

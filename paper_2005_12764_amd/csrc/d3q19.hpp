@@ -83,6 +83,15 @@ __device__ __forceinline__ double rcp_of(double x) { return 1.0 / x; }
 __device__ __forceinline__ float rsq_of(float x) { return __builtin_amdgcn_rsqf(x); }
 __device__ __forceinline__ double rsq_of(double x) { return 1.0 / sqrt(x); }
 
+__device__ __forceinline__ float fma_of(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_of(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+template <typename R>
+__device__ __forceinline__ R dot3(R ax, R ay, R az, R bx, R by, R bz) {
+#pragma clang fp contract(off)
+    return fma_of(az, bz, fma_of(ay, by, ax * bx));
+}
+
 // Is |G| (G with squared length g2) above the threshold e (squared e2)?
 // FP32 compares squares; FP64 compares the root, as the definition reads.
 __device__ __forceinline__ bool above(float g2, float e, float e2) { (void)e; return g2 > e2; }
@@ -107,51 +116,69 @@ struct SiteTotals {
 // d_i = f^r_i - f^b_i (the colour difference).  Carrying the small t_i keeps
 // FP32 rounding relative to the deviations that hold the flow, not to the
 // O(w_i) populations (a per-step force increment is ~1e-7 of those).
-// t/d hold the pulled (post-streaming) values on entry and the post-collision,
-// recoloured values on exit.  (gx,gy,gz) is the colour gradient at the site,
-// (Fx,Fy,Fz) the total force.  PAIRED: evaluate each direction together with
-// its opposite (the same values up to rounding, fewer instructions: taken by
-// the arithmetic-bound 16-bit tile; the memory-bound raw tiles measured
-// faster with the per-direction form).
-template <typename R, bool PAIRED = false>
-__device__ __forceinline__ void collide(R (&t)[Q], R (&d)[Q], R gx, R gy, R gz, R Fx, R Fy, R Fz,
-                                        const Coeffs<R>& c, SiteTotals<R>* tot = nullptr) {
-    using L = Lattice;
+// t (and d) hold the pulled (post-streaming) values on entry and the
+// post-collision, recoloured values on exit.  (gx,gy,gz) is the colour gradient
+// at the site, (Fx,Fy,Fz) the total force.
+//
+// Equilibrium, source and perturbation are all w_i times a polynomial of second
+// degree in c_i, so they are summed once per site as
+//   w_i (a + c.b + c.M c),   b = 3 (w j + F),
+//   M = 4.5 rho (v v - (1 - w) u u) + (A/2)|G| n n,   v = u + F/rho,
+//   a = w drho - 1.5 rho (|v|^2 - (1 - w)|u|^2) -+ (A/2)|G|
+// (u u of the equilibrium and u du + du u + du du of the source together are
+// v v - (1 - w) u u; -B_i is -w_i for the moving directions and +w_0 at rest),
+// and each direction then costs (1 - w) t_i + w_i (even +- odd part).  The
+// linear term of the force enters through F itself, not through a difference
+// of equilibria.  Fused multiply-adds are written out and the compiler forms
+// none itself: a sum of two products can be fused either way, and every kernel
+// that collides a site (single tiles, batch tiles) has to round alike.
+//
+// Sums of a site's pulled values that the collision needs, each in ascending
+// direction.  rc = sum_i (w_i + t_i) is rounded term by term as dif = sum_i d_i
+// is: a pure component (d_i = +-(w_i + t_i)) then gives phi = dif/rc = +-1 and
+// x_r, x_b = 1, 0 exactly, and stays pure.
+template <typename R>
+struct SiteSums {
     R drho = R(0), dif = R(0), rc = R(0), jx = R(0), jy = R(0), jz = R(0);
-#pragma unroll
-    for (int i = 0; i < Q; ++i) {
-        drho += t[i];
-        dif += d[i];
-        rc += weight<R>(i) + t[i];
-        if (L::cx[i]) jx += L::cx[i] > 0 ? t[i] : -t[i];
-        if (L::cy[i]) jy += L::cy[i] > 0 ? t[i] : -t[i];
-        if (L::cz[i]) jz += L::cz[i] > 0 ? t[i] : -t[i];
+    // direction i: t_i, w_i + t_i, d_i
+    __device__ __forceinline__ void add(int i, R t, R wt, R d) {
+        using L = Lattice;
+        drho += t;
+        dif += d;
+        rc += wt;
+        if (L::cx[i]) jx += L::cx[i] > 0 ? t : -t;
+        if (L::cy[i]) jy += L::cy[i] > 0 ? t : -t;
+        if (L::cz[i]) jz += L::cz[i] > 0 ? t : -t;
     }
+};
+
+// t_i becomes the post-collision total of direction i; the recoloured colour
+// differences follow from it and the phase and recolouring vector left in tot
+// (recoloured()).
+template <typename R>
+__device__ __forceinline__ void collide_totals(R (&t)[Q], const SiteSums<R>& m, R gx, R gy, R gz, R Fx, R Fy, R Fz,
+                                               const Coeffs<R>& c, SiteTotals<R>& tot) {
+#pragma clang fp contract(off)
+    using L = Lattice;
+    const R drho = m.drho, rc = m.rc, jx = m.jx, jy = m.jy, jz = m.jz;
     const R rho = R(1) + drho;            // sum of the weights is 1
-    // The colour split uses rc = sum_i (w_i + t_i), rounded term by term as
-    // the colour difference is: a pure component (d_i = +-(w_i + t_i)) then
-    // gives phi = +-1 exactly (a divided, not multiplied, quotient) and
-    // x_r, x_b = 1, 0 exactly, and stays pure.
-    const R phi = dif / rc;               // x_r - x_b
-    const R xr = R(0.5) + R(0.5) * phi, xb = R(0.5) - R(0.5) * phi;
+    const R phi = m.dif / rc;             // x_r - x_b (a divided, not multiplied, quotient)
+    const R xr = fma_of(R(0.5), phi, R(0.5)), xb = fma_of(R(-0.5), phi, R(0.5));
     const R inv_rho = rcp_of(rho);
     const R ux = jx * inv_rho, uy = jy * inv_rho, uz = jz * inv_rho;
-    // exact-difference velocity shift du = F^k/rho_k with F^k = (rho_k/rho) F
-    const R dx = Fx * inv_rho, dy = Fy * inv_rho, dz = Fz * inv_rho;
-    const R vx = ux + dx, vy = uy + dy, vz = uz + dz;
-    // s = u + (u + du): f^eq(u + du) - f^eq(u) = rho_k w_i [3 c.du + 4.5 (c.du)(c.s)
-    // - 1.5 du.s], without subtracting two equilibria
-    const R sx = ux + vx, sy = uy + vy, sz = uz + vz;
-    const R ds = dx * sx + dy * sy + dz * sz;
+    // v = u + du, the exact-difference velocity shift du = F^k/rho_k with
+    // F^k = (rho_k/rho) F; rho v = j + F
+    const R px = jx + Fx, py = jy + Fy, pz = jz + Fz;
+    const R vx = px * inv_rho, vy = py * inv_rho, vz = pz * inv_rho;
     // mixture relaxation: 1/nu_bar = x_r/nu_r + x_b/nu_b, w = 2 cs2/(2 nu_bar + cs2)
     R omega = c.omega;
     if (!c.same_tau) {
-        const R nubar = rcp_of(xr * c.inv_nu_r + xb * c.inv_nu_b);
-        omega = R(2) * rcp_of(R(6) * nubar + R(1));
+        const R nubar = rcp_of(fma_of(xb, c.inv_nu_b, xr * c.inv_nu_r));
+        omega = R(2) * rcp_of(fma_of(R(6), nubar, R(1)));
     }
-    const R uu = ux * ux + uy * uy + uz * uz;
+    const R om1 = R(1) - omega;
 
-    const R g2 = gx * gx + gy * gy + gz * gz;
+    const R g2 = dot3(gx, gy, gz, gx, gy, gz);
     const bool has_n = above(g2, c.eps_g, c.eps_g2);
     const R inv_gm = has_n ? inv_norm(g2) : R(0);
     const R gm = g2 * inv_gm;
@@ -161,71 +188,83 @@ __device__ __forceinline__ void collide(R (&t)[Q], R (&d)[Q], R gx, R gy, R gz, 
     const R seg = has_n ? c.beta * xr * xb * rc : R(0);
     const R nx = gx * inv_gm, ny = gy * inv_gm, nz = gz * inv_gm;
 
-    if constexpr (PAIRED) {
-        // rest direction (c = 0), then each pair (i, opposite): the even
-        // terms once, the odd ones (c.u, c.du, c.n) with both signs
-        {
-            const R w0 = weight<R>(0);
-            const R teq = w0 * (drho + rho * (-R(1.5) * uu));
-            const R tp = t[0] - omega * (t[0] - teq) + rho * (w0 * (-R(1.5) * ds));
-            const R ts = tp - pa * bpert<R>(0);
-            t[0] = ts;
-            d[0] = phi * (w0 + ts);
-        }
+    // T = rho (v v - (1 - w) u u)
+    const R kx = om1 * jx, ky = om1 * jy, kz = om1 * jz;
+    const R Txx = fma_of(px, vx, -(kx * ux)), Tyy = fma_of(py, vy, -(ky * uy)), Tzz = fma_of(pz, vz, -(kz * uz));
+    const R Txy = fma_of(px, vy, -(kx * uy)), Txz = fma_of(px, vz, -(kx * uz)), Tyz = fma_of(py, vz, -(ky * uz));
+    constexpr R w0 = weight<R>(0), w1 = weight<R>(1), w2 = weight<R>(7);
+    const R a = fma_of(omega, drho, R(-1.5) * ((Txx + Tyy) + Tzz));
+    // times the weight of a diagonal direction (the axis weight is twice it)
+    const R pw = w2 * pa;
+    const R qx = pw * nx, qy = pw * ny, qz = pw * nz;
+    constexpr R k45 = R(4.5) * w2, k9 = R(9) * w2;
+    const R mxx = fma_of(qx, nx, k45 * Txx), myy = fma_of(qy, ny, k45 * Tyy), mzz = fma_of(qz, nz, k45 * Tzz);
+    const R hx = R(2) * qx, hy = R(2) * qy;
+    const R mxy = fma_of(hx, ny, k9 * Txy), mxz = fma_of(hx, nz, k9 * Txz), myz = fma_of(hy, nz, k9 * Tyz);
+    constexpr R k3 = R(3) * w2;
+    const R bx = k3 * fma_of(omega, jx, Fx), by = k3 * fma_of(omega, jy, Fy), bz = k3 * fma_of(omega, jz, Fz);
+    const R a2 = fma_of(w2, a, -pw);
+    t[0] = fma_of(om1, t[0], w0 * (a + pa));
+    auto pair = [&](int i, R even, R odd) {
+        const int o = L::opp[i];
+        t[i] = fma_of(om1, t[i], even + odd);
+        t[o] = fma_of(om1, t[o], even - odd);
+    };
+    pair(1, R(2) * (a2 + mxx), R(2) * bx);
+    pair(3, R(2) * (a2 + myy), R(2) * by);
+    pair(5, R(2) * (a2 + mzz), R(2) * bz);
+    const R exy = a2 + (mxx + myy), exz = a2 + (mxx + mzz), eyz = a2 + (myy + mzz);
+    pair(7, exy + mxy, bx + by);
+    pair(9, exy - mxy, bx - by);
+    pair(11, exz + mxz, bx + bz);
+    pair(13, exz - mxz, bx - bz);
+    pair(15, eyz + myz, by + bz);
+    pair(17, eyz - myz, by - bz);
+    tot.drho = drho;
+    tot.jx = R(3) * px;  // 3 rho v = 3 (j + F)
+    tot.jy = R(3) * py;
+    tot.jz = R(3) * pz;
+    tot.phi = phi;
+    tot.vx = seg * nx;
+    tot.vy = seg * ny;
+    tot.vz = seg * nz;
+}
+
+// Recolouring f^r = x_r f* + rec, f^b = x_b f* - rec, f* = w_i + t*_i, rec =
+// w_i (c_i . v)/|c_i|: the colour difference d_i = phi f* + 2 rec of a direction
+// from wt = w_i + t*_i and the site's phase and recolouring vector, which are
+// kept as s = 2 w_7 v/|c_7| so that the twelve diagonal directions need no
+// factor.
+template <typename R>
+struct Colour {
+    R phi, sx, sy, sz;
+};
+template <typename R>
+__device__ __forceinline__ Colour<R> colour_of(const SiteTotals<R>& tot) {
+#pragma clang fp contract(off)
+    constexpr R k = R(2) * weight<R>(7) * inv_clen<R>(7);
+    return Colour<R>{tot.phi, k * tot.vx, k * tot.vy, k * tot.vz};
+}
+template <typename R>
+__device__ __forceinline__ R recoloured(int i, R wt, const Colour<R>& q) {
+#pragma clang fp contract(off)
+    if (i == 0) return q.phi * wt;
+    const R cs = cdot3<R>(i, q.sx, q.sy, q.sz);
+    constexpr R k = weight<R>(1) / (weight<R>(7) * inv_clen<R>(7));
+    return fma_of(q.phi, wt, Lattice::len2(i) == 1 ? k * cs : cs);
+}
+
+// The collision with the colour differences held per direction.
+template <typename R>
+__device__ __forceinline__ void collide(R (&t)[Q], R (&d)[Q], R gx, R gy, R gz, R Fx, R Fy, R Fz,
+                                        const Coeffs<R>& c, SiteTotals<R>* tot) {
+    SiteSums<R> m;
 #pragma unroll
-        for (int i = 1; i < Q; ++i) {
-            const int o = L::opp[i];
-            if (o < i) continue;  // evaluated with the first of the pair
-            const R w = weight<R>(i);
-            const R cu = cdot3<R>(i, ux, uy, uz);
-            const R cd = cdot3<R>(i, dx, dy, dz);
-            const R cs = cdot3<R>(i, sx, sy, sz);
-            const R cn = cdot3<R>(i, nx, ny, nz);
-            const R te = w * (drho + rho * (R(4.5) * cu * cu - R(1.5) * uu));  // teq, even part
-            const R to = w * rho * (R(3) * cu);                               // teq, odd part
-            const R se = rho * (w * (R(4.5) * cd * cs - R(1.5) * ds));        // rho * source, even
-            const R so = rho * (w * (R(3) * cd));                             // rho * source, odd
-            const R pert = pa * (w * cn * cn - bpert<R>(i));                  // perturbation (even)
-            const R rec2 = R(2) * (seg * w * cn * inv_clen<R>(i));            // 2 rec (odd)
-            const R tpi = t[i] - omega * (t[i] - (te + to)) + (se + so) + pert;
-            const R tpo = t[o] - omega * (t[o] - (te - to)) + (se - so) + pert;
-            t[i] = tpi;
-            d[i] = phi * (w + tpi) + rec2;
-            t[o] = tpo;
-            d[o] = phi * (w + tpo) - rec2;
-        }
-    } else {
+    for (int i = 0; i < Q; ++i) m.add(i, t[i], weight<R>(i) + t[i], d[i]);
+    collide_totals<R>(t, m, gx, gy, gz, Fx, Fy, Fz, c, *tot);
+    const Colour<R> q = colour_of(*tot);
 #pragma unroll
-        for (int i = 0; i < Q; ++i) {
-            const R w = weight<R>(i);
-            const R cu = cdot3<R>(i, ux, uy, uz);
-            const R cd = cdot3<R>(i, dx, dy, dz);
-            const R cs = cdot3<R>(i, sx, sy, sz);
-            const R q = R(3) * cu + R(4.5) * cu * cu - R(1.5) * uu;                // f^eq/(w rho) - 1
-            const R de = w * (R(3) * cd + R(4.5) * cd * cs - R(1.5) * ds);        // source / rho_k
-            // total: BGK toward rho w (1 + q) (deviation w (drho + rho q)) plus rho de
-            const R teq = w * (drho + rho * q);
-            const R tp = t[i] - omega * (t[i] - teq) + rho * de;
-            // (the components' own relaxation only enters through this total:
-            // recolouring redistributes the colour from rho_r/rho and f*)
-            const R cn = cdot3<R>(i, nx, ny, nz);   // c_i . n
-            const R ts = tp + pa * (w * cn * cn - bpert<R>(i));                    // perturbation
-            // recolouring: f^r = x_r f* + rec, f^b = x_b f* - rec, f* = w + t*
-            const R rec = seg * w * cn * inv_clen<R>(i);
-            t[i] = ts;
-            d[i] = phi * (w + ts) + R(2) * rec;
-        }
-    }
-    if (tot) {
-        tot->drho = drho;
-        tot->jx = R(3) * rho * vx;  // v = (j + F)/rho
-        tot->jy = R(3) * rho * vy;
-        tot->jz = R(3) * rho * vz;
-        tot->phi = phi;
-        tot->vx = seg * nx;
-        tot->vy = seg * ny;
-        tot->vz = seg * nz;
-    }
+    for (int i = 0; i < Q; ++i) d[i] = recoloured<R>(i, weight<R>(i) + t[i], q);
 }
 
 // Local collision of one site in the Shan-Chen model (Sec. 2.1: the
@@ -311,6 +350,23 @@ __device__ __forceinline__ R feq_unit(int i, R ux, R uy, R uz) {
     const R cu = cdot3<R>(i, ux, uy, uz);
     const R uu = ux * ux + uy * uy + uz * uz;
     return weight<R>(i) * (R(1) + R(3) * cu + R(4.5) * cu * cu - R(1.5) * uu);
+}
+
+// G = 3 sum_i w_i phi_i c_i from the 18 neighbour values, phi(i) the value at
+// x + c_i: differences of opposite neighbours, the diagonal ones added before
+// their weight (a uniform field gives exactly zero).
+template <typename R, typename Phi>
+__device__ __forceinline__ void stencil_gradient(const Phi& phi, R& gx, R& gy, R& gz) {
+#pragma clang fp contract(off)
+    using L = Lattice;
+    R e[Q];
+#pragma unroll
+    for (int i = 1; i < Q; i += 2) e[i] = phi(i) - phi(L::opp[i]);
+    // (the axis weight is twice the diagonal one)
+    constexpr R k = R(3) * weight<R>(7);
+    gx = k * fma_of(R(2), e[1], (e[7] + e[9]) + (e[11] + e[13]));
+    gy = k * fma_of(R(2), e[3], (e[7] - e[9]) + (e[15] + e[17]));
+    gz = k * fma_of(R(2), e[5], (e[11] - e[13]) + (e[15] - e[17]));
 }
 
 // Near-contact amplitude A_h(h): full strength up to h_min, h^-3 beyond,

@@ -143,12 +143,15 @@ struct lb_t {
     int part_cur;      // part[part_cur] belongs to the current state ...
     bool part_valid;   // ... when this is set
     int part_ty = 0, part_tz = 0;  // tile boxes those sums follow
+    FusedShape own_shape{};  // the library's choice for this lattice (TY 0: not made yet)
     Neu* partial;      // reduction partials
     double* dtot;      // device totals [14]
     int cur;           // buffer holding the current state
     int64_t steps;
     bool initialised;
     bool fresh;        // the state was set (init/import), no collision since: no wall terms
+    bool packed;       // raw storage stepped with one read: steps write the packed form ...
+    bool pairs;        // ... and the current state, set or loaded, still is in pair arrays
     int kernel;        // LB_KERNEL_TWOPASS or LB_KERNEL_FUSED
     Coeffs<double> cd;
     Coeffs<float> cf;
@@ -164,19 +167,31 @@ lbm::LatticeView view_of(lb_t* h) {
     v.stream = h->stream;
     v.cur = h->buf[h->cur];
     v.nxt = h->buf[h->cur ^ 1];
-    v.pending = h->pending;
+    v.pending = h->packed && h->pairs ? h->buf[h->cur] : h->pending;
+    v.packed = h->packed;
     v.phi = h->phi;
     v.part_in = h->part[h->part_cur];
     v.part_out = h->part[h->part_cur ^ 1];
-    // sums gathered for other tile boxes than the next step's are summed again
-    if (h->part_valid) {
-        const lbm::FusedShape fs = lbm::tile_shape(h->p, lbm::TILE_SINGLE);
-        v.part_valid = fs.TY == h->part_ty && fs.TZ == h->part_tz;
-    } else {
-        v.part_valid = false;
+    if (h->kernel == LB_KERNEL_FUSED) {
+        if (lbm::tile_shape_asked(h->p, lbm::TILE_SINGLE)) {
+            v.shape = lbm::tile_shape(h->p, lbm::TILE_SINGLE);
+        } else {
+            if (h->own_shape.TY == 0) h->own_shape = lbm::tile_shape(h->p, lbm::TILE_SINGLE);
+            v.shape = h->own_shape;
+        }
     }
+    // sums gathered for other tile boxes than the next step's are summed again
+    v.part_valid = h->part_valid && v.shape.TY == h->part_ty && v.shape.TZ == h->part_tz;
     v.cd = h->cd;
     v.cf = h->cf;
+    return v;
+}
+
+// The view that setting the state writes through: pair arrays in the current
+// buffer (16-bit lattices: in the pending one).
+lbm::LatticeView set_view_of(lb_t* h) {
+    lbm::LatticeView v = view_of(h);
+    if (h->packed) v.pending = h->buf[h->cur];
     return v;
 }
 
@@ -257,6 +272,7 @@ int lb_create(const lb_params* params, void* hip_stream, lb_t** out) {
         delete h;
         return fail(LB_EINVAL, "the fused kernel cannot hold this near-contact halo in LDS; use LB_KERNEL_TWOPASS");
     }
+    h->packed = h->kernel == LB_KERNEL_FUSED && h->p.storage < LB_STORE_F16;
     const size_t N = (size_t)h->g.N;
     const size_t pb = pop_bytes(h->p.storage, N);
     int rc = LB_OK;
@@ -320,7 +336,7 @@ int lb_init_fields(lb_t* h, const void* rho_r, const void* rho_b, const void* u,
     if (!rc) rc = copy_in(rho_b, on_device, N * es, &d_rb, scratch ? (char*)scratch + N * es : nullptr, h->stream);
     if (!rc && u) rc = copy_in(u, on_device, 3 * N * es, &d_u, scratch ? (char*)scratch + 2 * N * es : nullptr, h->stream);
     if (!rc) {
-        LatticeView v = view_of(h);
+        LatticeView v = set_view_of(h);
         rc = launch_init(v, d_rr, d_rb, d_u, dtype);
     }
     if (scratch) {
@@ -330,6 +346,7 @@ int lb_init_fields(lb_t* h, const void* rho_r, const void* rho_b, const void* u,
     if (rc) return rc;
     h->initialised = true;
     h->fresh = true;
+    h->pairs = true;
     h->part_valid = false;
     h->steps = 0;
     return LB_OK;
@@ -362,7 +379,7 @@ int lb_init_droplets(lb_t* h, const double* centres, const double* radii, int32_
     if (!rc && n) rc = check_hip(hipMemcpyAsync(dr, radii, sizeof(double) * n, hipMemcpyHostToDevice, h->stream), "H2D");
     if (!rc) rc = launch_droplets(h->stream, h->g, dc, dr, n, width, background, rho0, rr, rb);
     if (!rc) {
-        LatticeView v = view_of(h);
+        LatticeView v = set_view_of(h);
         rc = launch_init(v, rr, rb, nullptr, LB_DTYPE_F64);
     }
     (void)hipStreamSynchronize(h->stream);
@@ -370,6 +387,7 @@ int lb_init_droplets(lb_t* h, const double* centres, const double* radii, int32_
     if (rc) return rc;
     h->initialised = true;
     h->fresh = true;
+    h->pairs = true;
     h->part_valid = false;
     h->steps = 0;
     return LB_OK;
@@ -379,10 +397,9 @@ int lb_init_droplets(lb_t* h, const double* centres, const double* radii, int32_
 // that ran.
 static int advance(lb_t* h, const StepEvents* t, int* used) {
     LatticeView v = view_of(h);
-    // the first step of a 16-bit lattice with moving walls (from its raw
-    // initial state) takes two passes: the one-read kernel of that step does
-    // not gather the wall terms the next step's pull adds
-    const bool first16 = h->g.moving && h->pending;
+    // the one-read step takes a 16-bit lattice's initial pair arrays through
+    // 32-bit offsets of its own; beyond them that one step takes two passes
+    const bool first16 = h->pending && (uint64_t)40 * raw_stride((size_t)h->g.N) >= ((uint64_t)1 << 32);
     const int kernel = (h->kernel == LB_KERNEL_FUSED && first16) ? LB_KERNEL_TWOPASS : h->kernel;
     int rc = launch_step(v, kernel, t);
     if (rc) return rc;
@@ -395,12 +412,12 @@ static int advance(lb_t* h, const StepEvents* t, int* used) {
     h->cur ^= 1;
     h->steps++;
     h->fresh = false;
+    h->pairs = false;
     if (kernel == LB_KERNEL_FUSED) {
-        const FusedShape fs = tile_shape(h->p, TILE_SINGLE);
         h->part_cur ^= 1;
         h->part_valid = true;
-        h->part_ty = fs.TY;
-        h->part_tz = fs.TZ;
+        h->part_ty = v.shape.TY;
+        h->part_tz = v.shape.TZ;
     } else {
         h->part_valid = false;
     }
@@ -577,7 +594,7 @@ int lb_set_state(lb_t* h, const void* f, int32_t dtype, int32_t on_device) {
         }
         in = staging;
     }
-    LatticeView v = view_of(h);
+    LatticeView v = set_view_of(h);
     int rc = launch_import(v, in, dtype);
     if (staging) {
         (void)hipStreamSynchronize(h->stream);
@@ -586,6 +603,7 @@ int lb_set_state(lb_t* h, const void* f, int32_t dtype, int32_t on_device) {
     if (rc) return rc;
     h->initialised = true;
     h->fresh = true;
+    h->pairs = true;
     h->part_valid = false;
     return LB_OK;
 }
@@ -600,7 +618,14 @@ int lb_save_raw(lb_t* h, void* dst, int32_t on_device) {
     if (!h->initialised) return fail(LB_ESTATE, "no state yet");
     if (h->pending) return fail(LB_ESTATE, "16-bit lattice holds a raw initial state until its first step; use lb_get_state");
     const size_t b = pop_bytes(h->p.storage, (size_t)h->g.N);
-    int rc = check_hip(hipMemcpyAsync(dst, h->buf[h->cur], b, on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, h->stream), "copy raw state");
+    const void* from = h->buf[h->cur];
+    int rc = LB_OK;
+    if (h->packed && !h->pairs) {
+        // saved states are pair arrays: unpacked into the buffer the next step overwrites
+        rc = launch_unpack(view_of(h), h->buf[h->cur ^ 1]);
+        from = h->buf[h->cur ^ 1];
+    }
+    if (!rc) rc = check_hip(hipMemcpyAsync(dst, from, b, on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, h->stream), "copy raw state");
     if (!rc && !on_device) rc = check_hip(hipStreamSynchronize(h->stream), "sync");
     return rc;
 }
@@ -618,6 +643,7 @@ int lb_load_raw(lb_t* h, const void* src, int32_t on_device) {
     }
     h->initialised = true;
     h->fresh = false;
+    h->pairs = true;
     h->part_valid = false;
     return LB_OK;
 }

@@ -28,7 +28,7 @@
 
 #include "lb.h"
 #include "lb_internal.hpp"
-#include "lb_lean.hpp"
+#include "lb_lean_launch.hpp"
 
 using namespace lbm;
 
@@ -58,47 +58,27 @@ struct WorkItem {
     int block;
 };
 
-// Storage views of a job's buffers: the assembly's source view, and the
-// lean tile's policy from the source and destination buffers.
-template <typename H>
-__device__ __forceinline__ SplitPop<H> split_storage_view(void* buf, size_t N, float scale) {
-    SplitPop<H> s;
-    s.rec = (float*)buf;
-    s.dev = (H*)((float*)buf + 8 * N);
-    s.N = N;
-    s.scale = scale;
-    s.inv_scale = 1.0f / scale;
-    return s;
-}
-
+// Storage views of a job's buffers: the assembly's source view, and the tile's
+// policy.
 template <typename S>
 struct BatchStorage;
 template <typename T>
-struct BatchStorage<LeanRaw<T>> {
-    using Src = RawPop<T>;
-    static __device__ __forceinline__ Src view(void* buf, size_t N, float) { return Src{(T*)buf, N}; }
-    static __device__ __forceinline__ LeanRaw<T> policy(void* in, void* out, size_t, float, f4*, int) {
-        return LeanRaw<T>{(const T*)in, (T*)out};
+struct BatchStorage<LeanPack<T>> {
+    using Src = PackPop<T>;
+    static __device__ __forceinline__ Src view(void* buf, size_t N, float) {
+        return Src{(const T*)buf, (const T*)buf + pack_t_offset<T>(N), N};
     }
+    static __device__ __forceinline__ LeanPack<T> policy(void* buf, size_t N, float) { return lean_pack<T>(buf, N); }
 };
 template <typename H>
 struct BatchStorage<LeanSplit<H>> {
     using Src = SplitPop<H>;
     static __device__ __forceinline__ Src view(void* buf, size_t N, float scale) {
-        return split_storage_view<H>(buf, N, scale);
+        return Src{(float*)buf, (H*)((float*)buf + 8 * N), N, scale, 1.0f / scale};
     }
-    static __device__ __forceinline__ LeanSplit<H> policy(void* in, void* out, size_t N, float scale, f4* ring,
-                                                          int TY) {
-        const SplitPop<H> a = split_storage_view<H>(in, N, scale), b = split_storage_view<H>(out, N, scale);
-        LeanSplit<H> st;
-        st.rin = a.rec;
-        st.din = a.dev;
-        st.rout = b.rec;
-        st.dout = b.dev;
-        st.codec = a;
-        st.ring = ring;
-        st.TY = TY;
-        return st;
+    static __device__ __forceinline__ LeanSplit<H> policy(void* buf, size_t N, float scale) {
+        const Src s = view(buf, N, scale);
+        return LeanSplit<H>{s.rec, s.dev, s};
     }
 };
 
@@ -142,7 +122,7 @@ __global__ __launch_bounds__(kAsmThreads) void batch_assemble_kernel(const Batch
 // LDS of the batch tile kernel: that of a lean tile with the batch halo.
 template <typename S, int TY>
 __host__ __device__ constexpr size_t batch_lds_bytes() {
-    return lean_lds_bytes<S, TY, kBatchH>();
+    return LeanLds<S, TY, kBatchH>::bytes;
 }
 
 // Tiles: collide, stream and gather the next state's phase sums of every
@@ -156,12 +136,6 @@ __global__ __launch_bounds__(kTX * TY) void batch_tile_kernel(const BatchJob<typ
     using R = typename S::R;
     using B = BatchStorage<S>;
     extern __shared__ unsigned char lds_raw[];
-    R* ringb = reinterpret_cast<R*>(lds_raw);
-    size_t off = (phi_ring_bytes<R, kTX, kBatchH>(TY) + 15) & ~size_t(15);
-    f4* rec_ring = reinterpret_cast<f4*>(lds_raw + off);
-    off += S::ring_bytes(TY);
-    R* xch = reinterpret_cast<R*>(lds_raw + off);
-    Part2<R>* vs = reinterpret_cast<Part2<R>*>(lds_raw + off + lean_xch_bytes<R, TY>());
     const int first = W ? n_items[0] : 0, n = n_items[W ? 1 : 0];
     const long long gs = *gstep;
     for (int w = persistent_start(); w < n; w += gridDim.x) {
@@ -170,14 +144,15 @@ __global__ __launch_bounds__(kTX * TY) void batch_tile_kernel(const BatchJob<typ
         if (!job_live(J, gs)) continue;  // uniform over the workgroup
         const int par = (int)((gs - J.first) & 1);
         const Geom g = J.g;
-        const S st = B::policy(J.buf[par], J.buf[par ^ 1], (size_t)g.N, J.scale, rec_ring, TY);
+        const S src = B::policy(J.buf[par], (size_t)g.N, J.scale), dst = B::policy(J.buf[par ^ 1], (size_t)g.N, J.scale);
         const int tile = it.block % J.tiles, chunk = it.block / J.tiles;
         const int x0 = (tile % J.fs.tiles_x) * kTX, y0 = (tile / J.fs.tiles_x) * TY;
         const int za = chunk * J.fs.TZ, zb = min(za + J.fs.TZ, g.nz);
         Part2<R>* const pin = (Part2<R>*)J.part[par];
         Part2<R>* const pout = (Part2<R>*)J.part[par ^ 1];
-        lean_tile<S, TY, kBatchH, W>(g, st, J.c, ringb, xch, vs, x0, y0, za, zb, phi_of<kTX>(pin, g), pout,
-                                     phi_of<kTX>(pout, g), 0);  // (batched jobs have no moving walls)
+        // (batched jobs have no moving walls)
+        lean_tile<S, S, TY, kBatchH, W, false>(g, src, dst, J.c, lds_raw, x0, y0, za, zb, phi_of<kTX>(pin, g), pout,
+                                               phi_of<kTX>(pout, g), 0);
         __syncthreads();  // the next item restages every LDS ring
     }
 }
@@ -192,8 +167,8 @@ int batch_rows(int want) { return want > 0 && want < 8 ? 4 : 8; }
 
 size_t batch_tile_lds(int storage, int TY) {
     switch (storage) {
-        case LB_STORE_F64: return TY == 4 ? batch_lds_bytes<LeanRaw<double>, 4>() : batch_lds_bytes<LeanRaw<double>, 8>();
-        case LB_STORE_F32: return TY == 4 ? batch_lds_bytes<LeanRaw<float>, 4>() : batch_lds_bytes<LeanRaw<float>, 8>();
+        case LB_STORE_F64: return TY == 4 ? batch_lds_bytes<LeanPack<double>, 4>() : batch_lds_bytes<LeanPack<double>, 8>();
+        case LB_STORE_F32: return TY == 4 ? batch_lds_bytes<LeanPack<float>, 4>() : batch_lds_bytes<LeanPack<float>, 8>();
         default:
             return TY == 4 ? batch_lds_bytes<LeanSplit<__half>, 4>() : batch_lds_bytes<LeanSplit<__half>, 8>();
     }
@@ -268,6 +243,7 @@ struct HostJob {
     Coeffs<double> cd;
     Coeffs<float> cf;
     FusedShape fs;
+    bool pairs = false;     // raw storage: no step taken, the state is in pair arrays
 };
 
 }  // namespace
@@ -440,8 +416,8 @@ int launch_batch_step(lb_batch_t* b) {
 
 int batch_step_once(lb_batch_t* b) {
     switch (b->storage) {
-        case LB_STORE_F64: return launch_batch_step<LeanRaw<double>>(b);
-        case LB_STORE_F32: return launch_batch_step<LeanRaw<float>>(b);
+        case LB_STORE_F64: return launch_batch_step<LeanPack<double>>(b);
+        case LB_STORE_F32: return launch_batch_step<LeanPack<float>>(b);
         case LB_STORE_F16: return launch_batch_step<LeanSplit<__half>>(b);
         case LB_STORE_BF16: return launch_batch_step<LeanSplit<__hip_bfloat16>>(b);
     }
@@ -453,9 +429,9 @@ template <bool W>
 const void* batch_tile_kernel_of(int storage, int TY) {
     switch (storage) {
         case LB_STORE_F64:
-            return TY == 4 ? tile_kernel_of<LeanRaw<double>, 4, W>() : tile_kernel_of<LeanRaw<double>, 8, W>();
+            return TY == 4 ? tile_kernel_of<LeanPack<double>, 4, W>() : tile_kernel_of<LeanPack<double>, 8, W>();
         case LB_STORE_F32:
-            return TY == 4 ? tile_kernel_of<LeanRaw<float>, 4, W>() : tile_kernel_of<LeanRaw<float>, 8, W>();
+            return TY == 4 ? tile_kernel_of<LeanPack<float>, 4, W>() : tile_kernel_of<LeanPack<float>, 8, W>();
         case LB_STORE_F16:
             return TY == 4 ? tile_kernel_of<LeanSplit<__half>, 4, W>() : tile_kernel_of<LeanSplit<__half>, 8, W>();
         default:
@@ -506,10 +482,10 @@ LatticeView job_view(lb_batch_t* b, int slot, void* cur, void* nxt, void* pendin
     v.cur = cur;
     v.nxt = nxt;
     v.pending = pending;
+    v.packed = b->storage < LB_STORE_F16;
     v.phi = nullptr;
     v.cd = h.cd;
     v.cf = h.cf;
-    v.shape_set = true;
     v.shape = h.fs;
     return v;
 }
@@ -525,7 +501,10 @@ void* job_current(lb_batch_t* b, int slot) {
     return b->arena_base + h.off + ((done & 1) ? half : 0);
 }
 
-LatticeView current_view(lb_batch_t* b, int slot) { return job_view(b, slot, job_current(b, slot), nullptr, nullptr); }
+LatticeView current_view(lb_batch_t* b, int slot) {
+    void* cur = job_current(b, slot);
+    return job_view(b, slot, cur, nullptr, b->jobs[slot].pairs ? cur : nullptr);
+}
 
 }  // namespace
 
@@ -678,7 +657,8 @@ static int batch_admit(lb_batch_t* b, const lb_params* params, int64_t steps, in
     int rc = ensure_staging(b, (split ? lbm::pop_bytes(LB_STORE_F32, N) : 0) + 5 * N * sizeof(double) + 64);
     long long done = 0;
     if (!rc) {
-        LatticeView v = job_view(b, s, b0, b1, split ? b->staging : nullptr);
+        // the initial state: pair arrays, of a 16-bit job in the staging area
+        LatticeView v = job_view(b, s, b0, b1, split ? b->staging : b0);
         v.part_in = p0;
         v.part_out = p0 + job_part(h.p);
         v.part_valid = false;
@@ -695,6 +675,7 @@ static int batch_admit(lb_batch_t* b, const lb_params* params, int64_t steps, in
         return rc;
     }
     h.used = true;
+    h.pairs = !split && done == 0;
     h.first = b->gstep - done;
     h.last = h.first + steps;
     rc = upload_desc(b, s);

@@ -93,18 +93,12 @@ __device__ __forceinline__ void lds_gradient(const PhiRing<R, TX, H>& ring, int 
     const R* pm = ring.plane(sm);
     const R* p0 = ring.plane(s0);
     const R* pp = ring.plane(sp);
-    R ax = R(0), ay = R(0), az = R(0);
-#pragma unroll
-    for (int i = 1; i < Q; ++i) {
-        const R* pl = L::cz[i] < 0 ? pm : (L::cz[i] > 0 ? pp : p0);
-        const R v = weight<R>(i) * pl[(ly + L::cy[i]) * LX + lx + L::cx[i]];
-        if (L::cx[i]) ax += L::cx[i] > 0 ? v : -v;
-        if (L::cy[i]) ay += L::cy[i] > 0 ? v : -v;
-        if (L::cz[i]) az += L::cz[i] > 0 ? v : -v;
-    }
-    gx = R(3) * ax;
-    gy = R(3) * ay;
-    gz = R(3) * az;
+    stencil_gradient<R>(
+        [&](int i) {
+            const R* pl = L::cz[i] < 0 ? pm : (L::cz[i] > 0 ? pp : p0);
+            return pl[(ly + L::cy[i]) * LX + lx + L::cx[i]];
+        },
+        gx, gy, gz);
 }
 
 // Near-contact force from the phi ring (probe samples within K < H sites).
@@ -112,8 +106,9 @@ template <typename R, int TX, int H>
 __device__ __forceinline__ void ring_near_contact(const Geom& g, const PhiRing<R, TX, H>& ring, int s0, int x,
                                                   int y, int z, int ly, int lx, R gx, R gy, R gz,
                                                   const Coeffs<R>& c, R& Fx, R& Fy, R& Fz) {
+#pragma clang fp contract(off)
     constexpr int NP = 2 * H + 1;
-    const R g2 = gx * gx + gy * gy + gz * gz;
+    const R g2 = dot3(gx, gy, gz, gx, gy, gz);
     if (!at_least(g2, c.g_iface, c.g_iface2)) return;
     const R inv_gm = inv_norm(g2);
     const R nx = -gx * inv_gm, ny = -gy * inv_gm, nz = -gz * inv_gm;
@@ -126,20 +121,22 @@ __device__ __forceinline__ void ring_near_contact(const Geom& g, const PhiRing<R
         if (g.wx && (x + ox < 0 || x + ox >= g.nx)) break;
         if (g.wy && (y + oy < 0 || y + oy >= g.ny)) break;
         if (g.wz && (z + oz < 0 || z + oz >= g.nz)) break;
-        const int t0 = (s0 + oz + NP) % NP;
+        int t0 = s0 + oz;
+        t0 = t0 < 0 ? t0 + NP : (t0 >= NP ? t0 - NP : t0);
         R qx, qy, qz;
-        lds_gradient<R, TX, H>(ring, (t0 + NP - 1) % NP, t0, (t0 + 1) % NP, ly + oy, lx + ox, qx, qy, qz);
-        const R q2 = qx * qx + qy * qy + qz * qz;
-        const R dot = qx * gx + qy * gy + qz * gz;
+        lds_gradient<R, TX, H>(ring, t0 == 0 ? NP - 1 : t0 - 1, t0, t0 == NP - 1 ? 0 : t0 + 1, ly + oy, lx + ox, qx, qy,
+                               qz);
+        const R q2 = dot3(qx, qy, qz, qx, qy, qz);
+        const R dot = dot3(qx, qy, qz, gx, gy, gz);
         if (dot < R(0) && at_least(q2, c.g_iface, c.g_iface2)) {
             h = k;
             break;
         }
     }
     const R ah = nc_amplitude<R>(h, c);
-    Fx += ah * gx;
-    Fy += ah * gy;
-    Fz += ah * gz;
+    Fx = fma_of(ah, gx, Fx);
+    Fy = fma_of(ah, gy, Fy);
+    Fz = fma_of(ah, gz, Fz);
 }
 
 // One tile of the collide pass: columns [x0, x0+TX) x [y0, y0+TY), planes

@@ -2,9 +2,12 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <string>
+#include <type_traits>
 
 #include "lb.h"
+#include "lb_pack.hpp"
 #include "lb_single.hpp"
 
 namespace lbm {
@@ -20,13 +23,14 @@ struct LatticeView {
     hipStream_t stream = nullptr;
     void* cur = nullptr;       // post-collision buffer holding the current state
     void* nxt = nullptr;       // buffer the next step writes
-    void* pending = nullptr;   // raw FP32 current state of a 16-bit lattice (else null)
+    void* pending = nullptr;   // pair arrays of a state no collision made, of a lattice whose steps
+                               // write another form (else null)
+    bool packed = false;       // raw storage: steps write (and, unless pending, cur holds) the packed form
     void* phi = nullptr;       // phase-field scratch of the two-pass step
     void* part_in = nullptr;   // phase sums and phase field of the current state (one-read step)
     void* part_out = nullptr;  // the same, written by the one-read step for the next state
     bool part_valid = false;   // part_in holds the current state's sums
-    bool shape_set = false;    // the one-read step uses `shape` (not the lattice's own tile shape)
-    FusedShape shape{};
+    FusedShape shape{};        // tile shape of the one-read step
     Coeffs<double> cd;
     Coeffs<float> cf;
 };
@@ -38,8 +42,25 @@ Coeffs<R> make_coeffs(const lb_params& p);
 Geom make_geom(const lb_params& p);
 size_t pop_bytes(int storage, size_t N);
 
+// Views of a population buffer.
+template <typename T, bool MW = false>
+PackPop<T, MW> pack_view(void* buf, size_t N) {
+    return PackPop<T, MW>{(const T*)buf, (const T*)buf + pack_t_offset<T>(N), N};
+}
+template <typename H, bool MW = false>
+SplitPop<H, MW> split_view(void* buf, size_t N, int scale_log2) {
+    SplitPop<H, MW> s;
+    s.rec = (float*)buf;
+    s.dev = (H*)((float*)buf + 8 * N);
+    s.N = N;
+    const float sc = std::is_same<H, __half>::value ? std::ldexp(1.0f, scale_log2) : 1.0f;
+    s.scale = sc;
+    s.inv_scale = 1.0f / sc;
+    return s;
+}
+
 // Tile kernels: 64-wide tiles of TY rows marching z-chunks of TZ planes.
-constexpr int kTX = 64;
+constexpr int kTX = kTileX;
 enum TileKind { TILE_COLLIDE = 0, TILE_SINGLE = 1, TILE_PHASE = 2, TILE_BATCH = 3 };
 // Tile shape set through lb_set_tiles for (kind, storage): 0 = unset.
 struct TileSetting {
@@ -51,7 +72,9 @@ int env_int(const char* name, int dflt);
 int tile_halo(const lb_params& p);
 size_t tile_lds(const lb_params& p, int kind, int TY);
 int tile_rows(const lb_params& p, int kind);
-FusedShape tile_shape(const lb_params& p, int kind, int target_blocks = 1024);
+FusedShape tile_shape(const lb_params& p, int kind);
+// A shape of this kind was asked for (lb_set_tiles or the environment).
+bool tile_shape_asked(const lb_params& p, int kind);
 
 int choose_kernel(const lb_params& p);
 // Events recorded around the passes of one step (null = no timing):
@@ -61,14 +84,19 @@ struct StepEvents {
     hipEvent_t ev[3];
 };
 int launch_step(const LatticeView& v, int kernel, const StepEvents* t = nullptr);
-// Tile kernel of the one-read step for raw storage (lb_lean.hip): collide and
-// stream fin into fout, gathering the next state's own phase sums.
+// Tile kernel of the one-read step (lb_lean*.hip): collide and stream the
+// current state into v.nxt, gathering the next state's own phase sums.  raw:
+// packed storage; split: 16-bit moment-split storage; first: from pair arrays
+// (v.pending) into either.
 template <typename T>
-int launch_lean(const LatticeView& v, const T* fin, T* fout, const Coeffs<T>& c, const FusedShape& fs);
-// The same for 16-bit moment-split storage (lb_lean16.hip).
+int launch_lean_raw(const LatticeView& v, const Coeffs<T>& c, const FusedShape& fs);
 template <typename H>
-int launch_lean_split(const LatticeView& v, const SplitPop<H>& src, const SplitPop<H>& dst, const Coeffs<float>& c,
-                      const FusedShape& fs);
+int launch_lean_split(const LatticeView& v, const Coeffs<float>& c, const FusedShape& fs);
+template <typename T>
+int launch_lean_first(const LatticeView& v, const Coeffs<T>& c, const FusedShape& fs);
+size_t lean_tile_lds(const lb_params& p, int TY);
+// Pair arrays of the current packed state (a checkpoint's form) into f.
+int launch_unpack(const LatticeView& v, void* f);
 int launch_init(const LatticeView& v, const void* rr, const void* rb, const void* u, int dtype);
 int launch_import(const LatticeView& v, const void* f, int dtype);
 int launch_export(const LatticeView& v, void* out, int dtype);

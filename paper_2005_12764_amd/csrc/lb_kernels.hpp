@@ -113,9 +113,11 @@ __device__ __forceinline__ int nbr_source(const Geom& g, const Nbr& n, int i, in
 
 // Moving-wall term of direction i arriving at (x,y,z) by reflection, in the
 // compute type: 2 w_i (c_i . U)/c_s^2 summed over the wall faces the upstream
-// site x - c_i lies beyond (reference density 1).
+// site x - c_i lies beyond (reference density 1).  Not fused into the sum it
+// enters, so that every reading of a reflected value rounds alike.
 template <typename R>
 __device__ __forceinline__ R wall_term(const Geom& g, int i, int x, int y, int z) {
+#pragma clang fp contract(off)
     using L = Lattice;
     R cu = R(0);
     const int v[3] = {x - L::cx[i], y - L::cy[i], z - L::cz[i]};
@@ -161,6 +163,27 @@ __device__ __forceinline__ void raw_put(T* f, size_t N, int i, int s, T t, T d) 
     *reinterpret_cast<typename RawPair<T>::type*>(f + 2 * ((size_t)i * raw_stride(N) + s)) = v;
 }
 
+// Moving-wall terms of the reflected directions of a site, shared between the
+// components by its own post-collision rho_k/rho (src.own_phase).
+template <typename R, typename Src>
+__device__ void raw_wall_terms(const Src& src, const Geom& g, int s, int x, int y, int z, R (&t)[Q], R (&d)[Q]) {
+    R ph = R(0);
+    bool have = false;
+#pragma unroll
+    for (int i = 1; i < Q; ++i) {
+        int dir;
+        (void)pull_source(g, i, x, y, z, s, dir);
+        if (dir == i) continue;
+        if (!have) {
+            ph = src.template own_phase<R>(s);
+            have = true;
+        }
+        const R add = wall_term<R>(g, i, x, y, z);
+        t[i] += add;
+        d[i] = fma_of(add, ph, d[i]);   // add x_r - add x_b
+    }
+}
+
 // Raw storage policy.  MW: the lattice has moving walls (a separate
 // instantiation, so resting-wall kernels carry none of that code).
 template <typename T, bool MW = false>
@@ -180,7 +203,7 @@ struct RawPop {
             d[i] = R(v.y);
         }
         if constexpr (MW) {
-            if (g.moving) add_wall_terms<R>(g, s, x, y, z, t, d);
+            if (g.moving) raw_wall_terms<R>(*this, g, s, x, y, z, t, d);
         }
     }
 
@@ -205,26 +228,6 @@ struct RawPop {
         }
         return sd / st;
     }
-    // Moving-wall terms of the reflected directions, shared between the
-    // components by the site's own post-collision rho_k/rho.
-    template <typename R>
-    __device__ void add_wall_terms(const Geom& g, int s, int x, int y, int z, R (&t)[Q], R (&d)[Q]) const {
-        R ph = R(0);
-        bool have = false;
-#pragma unroll
-        for (int i = 1; i < Q; ++i) {
-            int dir;
-            (void)pull_source(g, i, x, y, z, s, dir);
-            if (dir == i) continue;
-            if (!have) {
-                ph = own_phase<R>(s);
-                have = true;
-            }
-            const R add = wall_term<R>(g, i, x, y, z);
-            t[i] += add;
-            d[i] += add * ph;   // add x_r - add x_b
-        }
-    }
     template <typename R>
     __device__ __forceinline__ void store(int s, const R (&t)[Q], const R (&d)[Q],
                                           const SiteTotals<R>&) const {
@@ -236,17 +239,6 @@ struct RawPop {
             __builtin_nontemporal_store(v, reinterpret_cast<typename RawPair<T>::type*>(f + 2 * ((size_t)i * raw_stride(N) + s)));
         }
     }
-    // Store, and replace t, d by the values a later pull reads.
-    template <typename R>
-    __device__ __forceinline__ void store_as_read(int s, R (&t)[Q], R (&d)[Q], const SiteTotals<R>& tot) const {
-        store(s, t, d, tot);
-#pragma unroll
-        for (int i = 0; i < Q; ++i) {
-            t[i] = R(T(t[i]));
-            d[i] = R(T(d[i]));
-        }
-    }
-    static constexpr bool needs_totals = false;
     static constexpr bool ring = false;
     static constexpr bool moving = MW;
 };
@@ -314,8 +306,12 @@ struct SplitPop {
                                            float& dd) const {
         const float w = weight<float>(i);
         tt = __builtin_fmaf(Half<H>::to_f(dv16), inv_scale, w * X);
+        dd = colour_diff(i, sg, w + tt, rb);
+    }
+    // colour difference of direction i from wt = w_i + t_i
+    static __device__ __forceinline__ float colour_diff(int i, float sg, float wt, const f4& rb) {
         const float cv = cdot(i, sg, rb.y, rb.z, rb.w);
-        dd = __builtin_fmaf(rb.x, w + tt, (2.0f * w * inv_clen<float>(i)) * cv);
+        return __builtin_fmaf(rb.x, wt, (2.0f * weight<float>(i) * inv_clen<float>(i)) * cv);
     }
     template <typename R>
     __device__ __forceinline__ void decode(int i, int d, const f4& ra, const f4& rb, H dv16, R& t_i,
@@ -369,7 +365,7 @@ struct SplitPop {
             if (dir == i) continue;
             const R add = wall_term<R>(g, i, x, y, z);
             t[i] += add;
-            d[i] += add * R(phi);
+            d[i] = fma_of(add, R(phi), d[i]);
         }
     }
 
@@ -399,19 +395,8 @@ struct SplitPop {
     }
 
     template <typename R>
-    __device__ __forceinline__ void store(int s, const R (&t)[Q], const R (&d)[Q],
+    __device__ __forceinline__ void store(int s, const R (&t)[Q], const R (&)[Q],
                                           const SiteTotals<R>& tot) const {
-        R tc[Q], dc[Q];
-#pragma unroll
-        for (int i = 0; i < Q; ++i) {
-            tc[i] = t[i];
-            dc[i] = d[i];
-        }
-        store_as_read(s, tc, dc, tot);
-    }
-    // Store, and replace t, d by the values a later pull decodes (exactly).
-    template <typename R>
-    __device__ __forceinline__ void store_as_read(int s, R (&t)[Q], R (&d)[Q], const SiteTotals<R>& tot) const {
         const f4 ra = {float(tot.drho), float(tot.jx), float(tot.jy), float(tot.jz)};
         const f4 rb = {float(tot.phi), float(tot.vx), float(tot.vy), float(tot.vz)};
         __builtin_nontemporal_store(ra, reinterpret_cast<f4*>(rec + 8 * (size_t)s));
@@ -420,15 +405,9 @@ struct SplitPop {
         for (int i = 0; i < Q; ++i) {
             const float X = excess(i, 1.0f, ra);
             // deviation of f*_i - w_i = t_i from w_i X
-            const H h = Half<H>::from_f((float(t[i]) - weight<float>(i) * X) * scale);
-            dev[(size_t)i * dev_stride(N) + s] = h;
-            float tt, dd;
-            finish(i, 1.0f, X, rb, h, tt, dd);
-            t[i] = R(tt);
-            d[i] = R(dd);
+            dev[(size_t)i * dev_stride(N) + s] = Half<H>::from_f((float(t[i]) - weight<float>(i) * X) * scale);
         }
     }
-    static constexpr bool needs_totals = true;
     static constexpr bool ring = true;
     static constexpr bool moving = MW;
 };
@@ -462,20 +441,14 @@ template <typename R>
 __device__ __forceinline__ void gradient(const Geom& g, const R* __restrict__ phi, int x, int y,
                                          int z, R& gx, R& gy, R& gz) {
     using L = Lattice;
-    R ax = R(0), ay = R(0), az = R(0);
-#pragma unroll
-    for (int i = 1; i < Q; ++i) {
-        const int xn = L::cx[i] ? stencil_coord(x + L::cx[i], g.nx, g.wx) : x;
-        const int yn = L::cy[i] ? stencil_coord(y + L::cy[i], g.ny, g.wy) : y;
-        const int zn = L::cz[i] ? stencil_coord(z + L::cz[i], g.nz, g.wz) : z;
-        const R p = weight<R>(i) * phi[site_of(g, xn, yn, zn)];
-        if (L::cx[i]) ax += L::cx[i] > 0 ? p : -p;
-        if (L::cy[i]) ay += L::cy[i] > 0 ? p : -p;
-        if (L::cz[i]) az += L::cz[i] > 0 ? p : -p;
-    }
-    gx = R(3) * ax;
-    gy = R(3) * ay;
-    gz = R(3) * az;
+    stencil_gradient<R>(
+        [&](int i) {
+            const int xn = L::cx[i] ? stencil_coord(x + L::cx[i], g.nx, g.wx) : x;
+            const int yn = L::cy[i] ? stencil_coord(y + L::cy[i], g.ny, g.wy) : y;
+            const int zn = L::cz[i] ? stencil_coord(z + L::cz[i], g.nz, g.wz) : z;
+            return phi[site_of(g, xn, yn, zn)];
+        },
+        gx, gy, gz);
 }
 
 __device__ __forceinline__ int wrap_any(int v, int n) {
@@ -490,7 +463,8 @@ template <typename R>
 __device__ __forceinline__ void near_contact(const Geom& g, const R* __restrict__ phi, int x, int y,
                                              int z, R gx, R gy, R gz, const Coeffs<R>& c, R& Fx,
                                              R& Fy, R& Fz) {
-    const R g2 = gx * gx + gy * gy + gz * gz;
+#pragma clang fp contract(off)
+    const R g2 = dot3(gx, gy, gz, gx, gy, gz);
     if (!at_least(g2, c.g_iface, c.g_iface2)) return;
     const R inv_gm = inv_norm(g2);
     const R nx = -gx * inv_gm, ny = -gy * inv_gm, nz = -gz * inv_gm;
@@ -504,17 +478,17 @@ __device__ __forceinline__ void near_contact(const Geom& g, const R* __restrict_
         if (g.wz) { if (pz < 0 || pz >= g.nz) break; } else pz = wrap_any(pz, g.nz);
         R qx, qy, qz;
         gradient<R>(g, phi, px, py, pz, qx, qy, qz);
-        const R q2 = qx * qx + qy * qy + qz * qz;
-        const R dot = qx * gx + qy * gy + qz * gz;
+        const R q2 = dot3(qx, qy, qz, qx, qy, qz);
+        const R dot = dot3(qx, qy, qz, gx, gy, gz);
         if (dot < R(0) && at_least(q2, c.g_iface, c.g_iface2)) {
             h = k;
             break;
         }
     }
     const R ah = nc_amplitude<R>(h, c);
-    Fx += ah * gx;
-    Fy += ah * gy;
-    Fz += ah * gz;
+    Fx = fma_of(ah, gx, Fx);
+    Fy = fma_of(ah, gy, Fy);
+    Fz = fma_of(ah, gz, Fz);
 }
 
 // ---------------------------------------------------------------------------

@@ -32,27 +32,20 @@ int launch_status(const char* what) {
 
 unsigned grid_for(int N) { return (unsigned)((N + kBlock - 1) / kBlock); }
 
-template <typename H, bool MW = false>
-SplitPop<H, MW> split_view(void* buf, size_t N, int scale_log2) {
-    SplitPop<H, MW> s;
-    s.rec = (float*)buf;
-    s.dev = (H*)((float*)buf + 8 * N);
-    s.N = N;
-    const float sc = std::is_same<H, __half>::value ? std::ldexp(1.0f, scale_log2) : 1.0f;
-    s.scale = sc;
-    s.inv_scale = 1.0f / sc;
-    return s;
-}
-
 // Calls fn(R{}, src, coeffs) with the compute type and a view of the current
 // state in its storage; lattices with moving walls get the storage types that
-// add the moving-wall terms (a raw initial state is never pulled with them).
+// add the moving-wall terms (the first state of a 16-bit lattice is never pulled
+// with them).
 template <bool MW, typename Fn>
 int with_state_mw(const LatticeView& v, Fn&& fn) {
     const size_t N = (size_t)v.g.N;
     switch (v.p->storage) {
-        case LB_STORE_F64: return fn(double(0), RawPop<double, MW>{(double*)v.cur, N}, v.cd);
-        case LB_STORE_F32: return fn(float(0), RawPop<float, MW>{(float*)v.cur, N}, v.cf);
+        case LB_STORE_F64:
+            if (v.packed && !v.pending) return fn(double(0), pack_view<double, MW>(v.cur, N), v.cd);
+            return fn(double(0), RawPop<double, MW>{(double*)(v.pending ? v.pending : v.cur), N}, v.cd);
+        case LB_STORE_F32:
+            if (v.packed && !v.pending) return fn(float(0), pack_view<float, MW>(v.cur, N), v.cf);
+            return fn(float(0), RawPop<float, MW>{(float*)(v.pending ? v.pending : v.cur), N}, v.cf);
         case LB_STORE_F16:
             if (v.pending) return fn(float(0), RawPop<float>{(float*)v.pending, N}, v.cf);
             return fn(float(0), split_view<__half, MW>(v.cur, N, v.p->scale_log2), v.cf);
@@ -118,28 +111,15 @@ int zmarch(const LatticeView& v, const Src& src, const Dst& dst, const Coeffs<R>
 // part_kernel when no such step made them; assemble_kernel adds the
 // cross-tile terms into phi of the face sites; the tile kernel collides,
 // streams and gathers the next state's sums and interior phi.
-template <typename R, typename Src, typename Dst, int TY, int H>
-int single_h(const LatticeView& v, const Src& src, const Dst& dst, const Coeffs<R>& c, const FusedShape& fs) {
-    if constexpr (!Src::ring && !Dst::ring) {
-        // raw storage: the lean tile kernel
-        return launch_lean<R>(v, src.f, dst.f, c, fs);
-    } else if constexpr (Src::ring && Dst::ring) {
-        // 16-bit moment-split storage: the lean tile kernel with the record ring
-        return launch_lean_split(v, src, dst, c, fs);
-    } else {
-        // the first step of a 16-bit lattice, from its raw FP32 initial state
-        const size_t lds = tile_lds(*v.p, TILE_SINGLE, TY);
-        auto kern = single_kernel<R, Src, Dst, kTX, TY, H>;
-        if (lds > 65536) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            if (e != hipSuccess)
-                return set_error(LB_EDEVICE, (std::string("single_kernel LDS: ") + hipGetErrorString(e)).c_str());
-        }
-        hipLaunchKernelGGL(kern, dim3(fs.nblocks), dim3(kTX * TY), lds, v.stream, v.g, src, dst, c, fs,
-                           (const Part2<R>*)v.part_in, (Part2<R>*)v.part_out);
-        return launch_status("single_kernel");
+int lean_step(const LatticeView& v, const FusedShape& fs) {
+    switch (v.p->storage) {
+        case LB_STORE_F64: return v.pending ? launch_lean_first<double>(v, v.cd, fs) : launch_lean_raw<double>(v, v.cd, fs);
+        case LB_STORE_F32: return v.pending ? launch_lean_first<float>(v, v.cf, fs) : launch_lean_raw<float>(v, v.cf, fs);
+        case LB_STORE_F16: return v.pending ? launch_lean_first<float>(v, v.cf, fs) : launch_lean_split<__half>(v, v.cf, fs);
+        case LB_STORE_BF16:
+            return v.pending ? launch_lean_first<float>(v, v.cf, fs) : launch_lean_split<__hip_bfloat16>(v, v.cf, fs);
     }
+    return set_error(LB_EINVAL, "unknown storage");
 }
 
 // phi of the face sites of a one-read state (its interior phi is already in
@@ -152,9 +132,8 @@ int assemble_phase(const LatticeView& v, const Src& src, const FusedShape& fs) {
     return launch_status("assemble_kernel");
 }
 
-template <typename R, typename Src, typename Dst, int TY>
-int single_ty(const LatticeView& v, const Src& src, const Dst& dst, const Coeffs<R>& c, const FusedShape& fs,
-              const StepEvents* t) {
+template <typename R, typename Src, int TY>
+int single_ty(const LatticeView& v, const Src& src, const FusedShape& fs, const StepEvents* t) {
     if (!v.part_valid) {
         hipLaunchKernelGGL((part_kernel<R, Src, kTX, TY>), dim3(grid_for(v.g.N)), dim3(kBlock), 0, v.stream, v.g,
                            src, fs.TZ, (Part2<R>*)v.part_in);
@@ -164,25 +143,18 @@ int single_ty(const LatticeView& v, const Src& src, const Dst& dst, const Coeffs
     int rc = assemble_phase<R, Src, TY>(v, src, fs);
     if (rc) return rc;
     if (t) (void)hipEventRecord(t->ev[1], v.stream);
-    switch (tile_halo(*v.p)) {
-        case 1: return single_h<R, Src, Dst, TY, 1>(v, src, dst, c, fs);
-        case 2: return single_h<R, Src, Dst, TY, 2>(v, src, dst, c, fs);
-        case 3: return single_h<R, Src, Dst, TY, 3>(v, src, dst, c, fs);
-        case 4: return single_h<R, Src, Dst, TY, 4>(v, src, dst, c, fs);
-        case 5: return single_h<R, Src, Dst, TY, 5>(v, src, dst, c, fs);
-    }
-    return set_error(LB_EINVAL, "near-contact range outside the tile kernels' halo");
+    return lean_step(v, fs);
 }
 
-template <typename R, typename Src, typename Dst>
-int single_pass(const LatticeView& v, const Src& src, const Dst& dst, const Coeffs<R>& c, const StepEvents* t) {
+template <typename R, typename Src>
+int single_pass(const LatticeView& v, const Src& src, const StepEvents* t) {
     if (!v.part_in || !v.part_out) return set_error(LB_EINVAL, "one-read step without its phase buffers");
-    const FusedShape fs = v.shape_set ? v.shape : tile_shape(*v.p, TILE_SINGLE);
+    const FusedShape fs = v.shape;
     if (t) (void)hipEventRecord(t->ev[0], v.stream);
     int rc;
-    if (fs.TY == kSingleTY) rc = single_ty<R, Src, Dst, kSingleTY>(v, src, dst, c, fs, t);
-    else if (fs.TY == kSingleTYSmall) rc = single_ty<R, Src, Dst, kSingleTYSmall>(v, src, dst, c, fs, t);
-    else if (fs.TY == kSingleTYLarge) rc = single_ty<R, Src, Dst, kSingleTYLarge>(v, src, dst, c, fs, t);
+    if (fs.TY == kSingleTY) rc = single_ty<R, Src, kSingleTY>(v, src, fs, t);
+    else if (fs.TY == kSingleTYSmall) rc = single_ty<R, Src, kSingleTYSmall>(v, src, fs, t);
+    else if (fs.TY == kSingleTYLarge) rc = single_ty<R, Src, kSingleTYLarge>(v, src, fs, t);
     else return set_error(LB_EINVAL, "one-read tile does not fit in LDS");
     if (rc) return rc;
     if (t) (void)hipEventRecord(t->ev[2], v.stream);
@@ -251,15 +223,6 @@ int two_pass(const LatticeView& v, const Src& src, const Dst& dst, const Coeffs<
     return rc;
 }
 
-template <typename R, typename Src, typename Dst>
-int step_with(const LatticeView& v, int kernel, const Src& src, const Dst& dst, const Coeffs<R>& c,
-              const StepEvents* t) {
-    if constexpr (!Src::moving) {
-        if (kernel == LB_KERNEL_FUSED) return single_pass<R>(v, src, dst, c, t);
-    }
-    return two_pass<R>(v, src, dst, c, t);
-}
-
 }  // namespace
 
 int env_int(const char* name, int dflt) {
@@ -289,44 +252,89 @@ size_t tile_lds(const lb_params& p, int kind, int TY) {
     switch (kind) {
         case TILE_PHASE: return rec;
         case TILE_COLLIDE: return ((phi + 15) & ~size_t(15)) + (split ? rec : 0);
-        default:  // TILE_SINGLE: phi ring, record ring, exchange of the c_y != 0 directions
-                  // (raw storage: rows padded by a zero at both ends), running x-face sums
-                  // of the edge lanes
-            return ((phi + 15) & ~size_t(15)) + (split ? rec : 0) +
-                   (size_t)2 * kXchDirs * (kTX + 2) * TY * real_size(p) + (size_t)2 * 3 * TY * 2 * real_size(p);
+        default: return lean_tile_lds(p, TY);
     }
 }
 
-// Tile rows: preferred per kind and storage (measured on MI355X), else the
-// largest that keeps the LDS rings within the per-workgroup budget.
-int tile_rows(const lb_params& p, int kind) {
-    if (kind == TILE_SINGLE) {
-        // FP32 lattices of 2^23 sites or more take 16 rows (1024-thread
-        // workgroups, one per CU: the autotuner's choice at 256^3) when they
-        // split into whole rounds of 256 such workgroups, so that no CU idles
-        // (measured: 384^3 with 144 of them ran 24 % slower than with 8 rows);
-        // other lattices take 8 (16-bit storage too: with its record ring that
-        // is one workgroup of 8 waves per CU, measured faster than two
-        // workgroups of 4 rows)
-        const int set = tile_setting(TILE_SINGLE, p.storage).ty;
-        int dflt = kSingleTY;
-        if (p.storage == LB_STORE_F32 && set <= 0 && (size_t)p.nx * p.ny * p.nz >= ((size_t)1 << 23)) {
-            const int tiles = ((p.nx + kTX - 1) / kTX) * ((p.ny + kSingleTYLarge - 1) / kSingleTYLarge);
-            const int want_chunks = std::max(1, 256 / tiles);
-            const int tz = std::max(4 * tile_halo(p), (p.nz + want_chunks - 1) / want_chunks);
-            const int blocks = tiles * ((p.nz + tz - 1) / tz);
-            if (blocks % 256 == 0) dflt = kSingleTYLarge;
+// Rows asked for by lb_set_tiles or the environment (0 = none).
+static int wanted_rows(const lb_params& p, int kind) {
+    const int set = tile_setting(kind, p.storage).ty;
+    if (set > 0) return set;
+    return env_int(kind == TILE_SINGLE ? "LB_SINGLE_TY" : (kind == TILE_PHASE ? "LB_PHASE_TY" : "LB_COLLIDE_TY"), 0);
+}
+static int wanted_planes(const lb_params& p, int kind) {
+    const int set = tile_setting(kind, p.storage).tz;
+    if (set > 0) return set;
+    return env_int(kind == TILE_PHASE ? "LB_PHASE_TZ" : "LB_TZ", 0);
+}
+
+static bool single_rows_fit(const lb_params& p, int ty) {
+    return (ty == kSingleTY || ty == kSingleTYSmall || ty == kSingleTYLarge) &&
+           tile_lds(p, TILE_SINGLE, ty) <= (size_t)device_lds_bytes();
+}
+
+// Estimated microseconds of a one-read step with TY rows and chunks of TZ
+// planes: workgroups run in rounds of as many as the 256 CUs hold at once (LDS
+// and registers); a workgroup starts its rings (8 us with the launch) and then
+// takes a plane in a + b w with w wavefronts per SIMD (a: the latency of a plane
+// that nothing overlaps, b: the issue of one more row); the assembly takes 8 us
+// or 16 ns per thousand face sites.  Fitted to the times of 64^3 to 384^3 in
+// each storage (64^3 FP32, tile only: 41 us with 4 rows and 8 planes, 26 with 4
+// planes, 21 with 2; 256^3 FP32: 693 us with 8 rows and 128 planes, 740 with 64,
+// 701 with 4 rows and 32 planes; 384^3 bf16: 2.05 ms with 48 planes, 9 whole
+// rounds, 3.90 ms with 384, 1.1 rounds).
+static double single_cost(const lb_params& p, int TY, int TZ) {
+    const int H = tile_halo(p);
+    const double a = p.storage == LB_STORE_F64 ? 1.0 : (split_storage(p) ? 2.6 : 2.2);
+    const double b = p.storage == LB_STORE_F64 ? 5.6 : (split_storage(p) ? 1.7 : 1.5);
+    const int waves = p.storage == LB_STORE_F32 ? 3 : (split_storage(p) || H == 1 ? 2 : 1);  // per SIMD, by registers
+    const int per_simd = std::max(1, TY / 4);
+    const int hold = std::max(1, std::min((int)(kLdsBytes / tile_lds(p, TILE_SINGLE, TY)), waves / per_simd));
+    const double tiles = double((p.nx + kTX - 1) / kTX) * ((p.ny + TY - 1) / TY);
+    const int chunks = (p.nz + TZ - 1) / TZ;
+    const double per_cu = std::ceil(tiles * chunks / 256.0);
+    const double resident = std::min<double>(hold, per_cu);
+    // (rounds beyond the second start as CUs become free)
+    const double rounds = per_cu <= 2 * hold ? std::ceil(per_cu / resident) : per_cu / resident;
+    const double tile = rounds * (8.0 + TZ * (a + b * per_simd * resident));
+    auto faces = [](double n, int T) { return std::min(n, 2.0 * std::ceil(n / T)); };
+    const double fx = faces(p.nx, kTX) / p.nx, fy = faces(p.ny, TY) / p.ny, fz = faces(p.nz, TZ) / p.nz;
+    const double sites = double(p.nx) * p.ny * p.nz * (1.0 - (1.0 - fx) * (1.0 - fy) * (1.0 - fz));
+    return tile + std::max(8.0, sites * 1.6e-5);
+}
+
+// Rows and planes of the one-read step nothing else was asked for: the least
+// estimated step over 8 and 4 rows and the plane counts that divide the lattice
+// into equal chunks.  (16 rows of FP32 need more registers than four wavefronts
+// per SIMD have and spill: 256^3 995 us against 693 with 8.)
+static void single_auto(const lb_params& p, int ty_wanted, int tz_wanted, int& ty, int& tz) {
+    double best = -1.0;
+    for (int r : {kSingleTY, kSingleTYSmall, kSingleTYLarge}) {
+        if (!single_rows_fit(p, r)) continue;
+        if (ty_wanted > 0 ? r != ty_wanted : r == kSingleTYLarge) continue;
+        for (int chunks = 1; chunks <= p.nz; chunks += chunks < 16 ? 1 : chunks / 8) {
+            const int planes = tz_wanted > 0 ? std::min(tz_wanted, p.nz) : (p.nz + chunks - 1) / chunks;
+            const double cost = single_cost(p, r, planes);
+            if (best < 0.0 || cost < best) {
+                best = cost;
+                ty = r;
+                tz = planes;
+            }
+            if (tz_wanted > 0) break;
         }
-        const int want = set > 0 ? set : env_int("LB_SINGLE_TY", dflt);
+    }
+}
+
+// Tile rows: what was asked for or is preferred per kind and storage (measured
+// on MI355X), else the largest that keeps the LDS rings within the budget; 0
+// when none fits.
+int tile_rows(const lb_params& p, int kind) {
+    int want = wanted_rows(p, kind);
+    if (kind == TILE_SINGLE) {
         for (int ty : {want, kSingleTY, kSingleTYSmall})
-            if ((ty == kSingleTY || ty == kSingleTYSmall || ty == kSingleTYLarge) &&
-                tile_lds(p, kind, ty) <= (size_t)device_lds_bytes())
-                return ty;
+            if (single_rows_fit(p, ty)) return ty;
         return 0;
     }
-    const char* env = kind == TILE_PHASE ? "LB_PHASE_TY" : "LB_COLLIDE_TY";
-    int want = tile_setting(kind, p.storage).ty;
-    if (want <= 0) want = env_int(env, 0);
     if (want <= 0) {
         // the autotuner's choices for the 256^3 emulsion on MI355X
         if (kind == TILE_PHASE) want = 4;
@@ -338,34 +346,32 @@ int tile_rows(const lb_params& p, int kind) {
     return 0;
 }
 
-FusedShape tile_shape(const lb_params& p, int kind, int target_blocks) {
+FusedShape tile_shape(const lb_params& p, int kind) {
     FusedShape fs;
+    int tz = wanted_planes(p, kind);
     fs.TY = tile_rows(p, kind);
+    if (kind == TILE_SINGLE && fs.TY > 0) {
+        const int want = wanted_rows(p, kind);
+        single_auto(p, single_rows_fit(p, want) ? want : 0, tz, fs.TY, tz);
+    }
     fs.tiles_x = (p.nx + kTX - 1) / kTX;
     fs.tiles_y = (p.ny + fs.TY - 1) / fs.TY;
     const int tiles = fs.tiles_x * fs.tiles_y;
-    int tz = tile_setting(kind, p.storage).tz;
-    if (tz <= 0) tz = env_int(kind == TILE_PHASE ? "LB_PHASE_TZ" : "LB_TZ", 0);
     // the autotuner's choices for the 256^3 emulsion on MI355X: 16-plane chunks
     // for the 16-bit phase pass and the raw-storage two-pass collide
     if (tz <= 0 && (kind == TILE_PHASE || (kind == TILE_COLLIDE && !split_storage(p)))) tz = 16;
-    // one-read tiles that fill a CU alone -- 16-row tiles (1024 threads) and
-    // 16-bit storage's 8-row tiles (their LDS rings) -- aim for one round of
-    // 256 workgroups (deep chunks: fewer halo planes and face sites; measured
-    // at 256^3: fp16 1.31 ms/step with 32-plane chunks, 1.23 ms with 128)
-    if (kind == TILE_SINGLE && (fs.TY == kSingleTYLarge || (split_storage(p) && fs.TY == kSingleTY)))
-        target_blocks = 256;
     if (tz <= 0) {
-        // aim for target_blocks workgroups, keeping chunks a few halos deep
-        const int H = kind == TILE_PHASE ? 1 : tile_halo(p);
-        const int want_chunks = std::max(1, target_blocks / std::max(1, tiles));
-        tz = std::max(4 * H, (p.nz + want_chunks - 1) / want_chunks);
+        // aim for 1024 workgroups, keeping chunks a few halos deep
+        const int want_chunks = std::max(1, 1024 / std::max(1, tiles));
+        tz = std::max(4 * tile_halo(p), (p.nz + want_chunks - 1) / want_chunks);
     }
     fs.TZ = std::min(std::max(tz, 1), p.nz);
     fs.chunks = (p.nz + fs.TZ - 1) / fs.TZ;
     fs.nblocks = tiles * fs.chunks;
     return fs;
 }
+
+bool tile_shape_asked(const lb_params& p, int kind) { return wanted_rows(p, kind) > 0 || wanted_planes(p, kind) > 0; }
 
 int choose_kernel(const lb_params& p) {
     const bool fits = tile_rows(p, TILE_SINGLE) > 0;
@@ -381,36 +387,51 @@ int choose_kernel(const lb_params& p) {
     return LB_KERNEL_FUSED;
 }
 
-// Source/destination storage pairs a step may combine: same storage, or the
-// raw FP32 initial state of a 16-bit lattice into its moment-split storage.
+// Source/destination storage pairs a two-pass step may combine: same storage,
+// or the raw FP32 initial state of a 16-bit lattice into its moment-split
+// storage.
 template <typename Src, typename Dst>
 struct StepPair : std::false_type {};
 template <typename T, bool MW>
 struct StepPair<RawPop<T, MW>, RawPop<T>> : std::true_type {};
-template <typename H>
-struct StepPair<RawPop<float>, SplitPop<H>> : std::true_type {};
+template <typename H, bool MW>
+struct StepPair<RawPop<float, MW>, SplitPop<H>> : std::true_type {};
 template <typename H, bool MW>
 struct StepPair<SplitPop<H, MW>, SplitPop<H>> : std::true_type {};
 
 template <typename Dst>
-int step_into(const LatticeView& v, int kernel, const Dst& dst, const StepEvents* t) {
+int two_pass_into(const LatticeView& v, const Dst& dst, const StepEvents* t) {
     return with_state(v, [&](auto rt, auto src, const auto& c) {
         using R = decltype(rt);
         using S = decltype(src);
-        if constexpr (StepPair<S, Dst>::value) return step_with<R>(v, kernel, src, dst, c, t);
+        if constexpr (StepPair<S, Dst>::value) return two_pass<R>(v, src, dst, c, t);
         return set_error(LB_EINVAL, "storage/compute mismatch");
     });
 }
 
 int launch_step(const LatticeView& v, int kernel, const StepEvents* t) {
     const size_t N = (size_t)v.g.N;
+    if (kernel == LB_KERNEL_FUSED)
+        return with_state(v, [&](auto rt, auto src, const auto&) { return single_pass<decltype(rt)>(v, src, t); });
     switch (v.p->storage) {
-        case LB_STORE_F64: return step_into(v, kernel, RawPop<double>{(double*)v.nxt, N}, t);
-        case LB_STORE_F32: return step_into(v, kernel, RawPop<float>{(float*)v.nxt, N}, t);
-        case LB_STORE_F16: return step_into(v, kernel, split_view<__half>(v.nxt, N, v.p->scale_log2), t);
-        case LB_STORE_BF16: return step_into(v, kernel, split_view<__hip_bfloat16>(v.nxt, N, v.p->scale_log2), t);
+        case LB_STORE_F64: return two_pass_into(v, RawPop<double>{(double*)v.nxt, N}, t);
+        case LB_STORE_F32: return two_pass_into(v, RawPop<float>{(float*)v.nxt, N}, t);
+        case LB_STORE_F16: return two_pass_into(v, split_view<__half>(v.nxt, N, v.p->scale_log2), t);
+        case LB_STORE_BF16: return two_pass_into(v, split_view<__hip_bfloat16>(v.nxt, N, v.p->scale_log2), t);
     }
     return set_error(LB_EINVAL, "unknown storage");
+}
+
+int launch_unpack(const LatticeView& v, void* f) {
+    const unsigned grid = grid_for(v.g.N);
+    const size_t N = (size_t)v.g.N;
+    if (v.p->storage == LB_STORE_F64)
+        hipLaunchKernelGGL(unpack_kernel<double>, dim3(grid), dim3(kBlock), 0, v.stream, v.g.N,
+                           pack_view<double>(v.cur, N), (double*)f);
+    else
+        hipLaunchKernelGGL(unpack_kernel<float>, dim3(grid), dim3(kBlock), 0, v.stream, v.g.N,
+                           pack_view<float>(v.cur, N), (float*)f);
+    return launch_status("unpack_kernel");
 }
 
 // Initial state goes to raw storage: the current buffer for F64/F32, the
@@ -420,9 +441,9 @@ static int init_typed(const LatticeView& v, const In* rr, const In* rb, const In
     const unsigned grid = grid_for(v.g.N);
     if (v.p->storage == LB_STORE_F64) {
         hipLaunchKernelGGL((init_raw_kernel<double, In>), dim3(grid), dim3(kBlock), 0, v.stream, v.g,
-                           (double*)v.cur, rr, rb, u);
+                           (double*)(v.pending ? v.pending : v.cur), rr, rb, u);
     } else {
-        float* dst = (float*)(v.p->storage == LB_STORE_F32 ? v.cur : v.pending);
+        float* dst = (float*)(v.pending ? v.pending : v.cur);
         hipLaunchKernelGGL((init_raw_kernel<float, In>), dim3(grid), dim3(kBlock), 0, v.stream, v.g, dst, rr, rb, u);
     }
     return launch_status("init_raw_kernel");
@@ -438,9 +459,9 @@ static int import_typed(const LatticeView& v, const In* f) {
     const unsigned grid = grid_for(v.g.N);
     if (v.p->storage == LB_STORE_F64) {
         hipLaunchKernelGGL((import_raw_kernel<double, In>), dim3(grid), dim3(kBlock), 0, v.stream, v.g,
-                           (double*)v.cur, f);
+                           (double*)(v.pending ? v.pending : v.cur), f);
     } else {
-        float* dst = (float*)(v.p->storage == LB_STORE_F32 ? v.cur : v.pending);
+        float* dst = (float*)(v.pending ? v.pending : v.cur);
         hipLaunchKernelGGL((import_raw_kernel<float, In>), dim3(grid), dim3(kBlock), 0, v.stream, v.g, dst, f);
     }
     return launch_status("import_raw_kernel");
@@ -490,7 +511,7 @@ int launch_korteweg(const LatticeView& v, double lam, int b, void* kout, void* p
         const R* field = (const R*)v.phi;
         int rc;
         if (v.part_valid && v.part_in) {
-            const FusedShape fs = tile_shape(*v.p, TILE_SINGLE);
+            const FusedShape fs = v.shape;
             if (fs.TY == kSingleTY) rc = assemble_phase<R, S, kSingleTY>(v, src, fs);
             else if (fs.TY == kSingleTYLarge) rc = assemble_phase<R, S, kSingleTYLarge>(v, src, fs);
             else rc = assemble_phase<R, S, kSingleTYSmall>(v, src, fs);

@@ -1,28 +1,39 @@
-// lb_lean.hip -- instantiation and launch of the lean one-read tile kernel for
-// raw (FP64/FP32) storage.
+// lb_lean.hip -- one-read tile kernel for packed FP32 storage, and the LDS of
+// the tiles.
 #include "lb_lean_launch.hpp"
 
 namespace lbm {
 
-template <typename T>
-int launch_lean(const LatticeView& v, const T* fin, T* fout, const Coeffs<T>& c, const FusedShape& fs) {
-    // byte offsets within a buffer resource of five pair arrays are 32-bit
-    if ((uint64_t)kResArrays * sizeof(T) * (uint64_t)raw_stride((size_t)v.g.N) >= ((uint64_t)1 << 32))
-        return set_error(LB_EINVAL, "lattice too large for the one-read step (10 x sites x value size >= 2^32)");
-    const LeanRaw<T> st{fin, fout};
-    switch (fs.TY) {
-        case kSingleTYSmall: return lean_launch::launch_ty<LeanRaw<T>, kSingleTYSmall>(v, st, c, fs);
-        case kSingleTY: return lean_launch::launch_ty<LeanRaw<T>, kSingleTY>(v, st, c, fs);
-        case kSingleTYLarge:
-            // (FP64 rings of 16 rows do not fit the LDS: tile_rows never picks them)
-            if constexpr (sizeof(T) == 4) return lean_launch::launch_ty<LeanRaw<T>, kSingleTYLarge>(v, st, c, fs);
-            break;
-    }
-    return set_error(LB_EINVAL, "one-read tile rows must be 4, 8 or 16 (4 or 8 in FP64)");
+template <>
+int launch_lean_raw<float>(const LatticeView& v, const Coeffs<float>& c, const FusedShape& fs) {
+    const size_t N = (size_t)v.g.N;
+    if (!lean_launch::raw_fits<float>(N)) return lean_launch::too_large();
+    return lean_launch::launch(v, lean_pack<float>(v.cur, N), lean_pack<float>(v.nxt, N), c, fs);
 }
 
-template int launch_lean<float>(const LatticeView&, const float*, float*, const Coeffs<float>&, const FusedShape&);
-template int launch_lean<double>(const LatticeView&, const double*, double*, const Coeffs<double>&,
-                                 const FusedShape&);
+namespace {
+template <typename S, int TY>
+size_t lds_of(int H) {
+    switch (H) {
+        case 1: return LeanLds<S, TY, 1>::bytes;
+        case 2: return LeanLds<S, TY, 2>::bytes;
+        case 3: return LeanLds<S, TY, 3>::bytes;
+        case 4: return LeanLds<S, TY, 4>::bytes;
+        default: return LeanLds<S, TY, 5>::bytes;
+    }
+}
+template <typename S>
+size_t lds_of(int TY, int H) {
+    return TY == kSingleTYSmall ? lds_of<S, kSingleTYSmall>(H)
+                                : (TY == kSingleTY ? lds_of<S, kSingleTY>(H) : lds_of<S, kSingleTYLarge>(H));
+}
+}  // namespace
+
+size_t lean_tile_lds(const lb_params& p, int TY) {
+    const int H = tile_halo(p);
+    if (p.storage == LB_STORE_F64) return lds_of<LeanPack<double>>(TY, H);
+    if (p.storage == LB_STORE_F32) return lds_of<LeanPack<float>>(TY, H);
+    return lds_of<LeanSplit<__half>>(TY, H);
+}
 
 }  // namespace lbm

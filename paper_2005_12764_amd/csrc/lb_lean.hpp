@@ -1,61 +1,47 @@
-// lb_lean.hpp -- the one-read step for raw (FP64/FP32) storage, written for
-// the CDNA4 instruction mix.
+// lb_lean.hpp -- the tile of the one-read step.
 //
-// Same step and same phase-sum bookkeeping as single_tile (lb_single.hpp):
-// the tile collides and streams its sites and gathers, in the same fixed
-// order, the own phase sums of the next state.  What differs is how the work
-// maps onto a wavefront:
-//   - a tile row is one wavefront, so the row's y and the plane's z are
-//     wave-uniform: every upstream row offset (periodic wrap, wall tests) is
-//     scalar arithmetic, and each of the 38 pulls and 38 stores is a global
-//     access with a scalar row base plus one of three loop-invariant per-lane
-//     column offsets (x, x-1, x+1 with the periodic wrap);
-//   - the phase-field ring is staged row by row with scalar row addresses;
-//   - neighbours in the same row are read with DPP wavefront shifts that fill
-//     the lane beyond the row's end with zero, so a source outside the tile
-//     (or beyond an x wall) contributes nothing without a per-lane test, and
-//     the shift folds into the add that consumes it;
-//   - values for other rows go through LDS rows padded with a zero at both
-//     ends, for the same reason;
-//   - every lane runs the collision (lanes beyond the lattice on clamped
-//     coordinates); only stores are masked.
-// The kernel the step launched before (single_kernel) computes the same
-// quantities; the two agree to rounding (the collision is shared).
+// A workgroup owns 64 x TY columns of a z-chunk and marches it plane by plane,
+// one tile row per wavefront (64-wide wavefronts, so the row's y and the plane's
+// z are wave-uniform and every row offset is scalar).  Per plane a wavefront
+//   - stores the phase field of plane z + H and the colour records of plane
+//     z + 1, loaded a plane ahead, into their LDS rings;
+//   - pulls its sites: the totals t_i come from memory (loaded a plane ahead),
+//     the colour differences are decoded from the source sites' records in LDS
+//     (packed and 16-bit storage; the first step of a state reads pair arrays);
+//   - takes the colour gradient and the near-contact probe from the ring,
+//     collides and stores;
+//   - gathers the phase sums of the next state: each row adds what it sends to
+//     the rows above, beside and below it (neighbouring columns by DPP shifts
+//     that read zero beyond the wavefront's end), and hands the six sums for
+//     other rows over through LDS.
+// A site whose sources all lie in the tile gets its phase field here; face sites
+// keep their own sums for the assembly.
+//
+// What bounds it: FP32 moves 92 B per site each way and runs about 1000 VALU
+// instructions per site, 0.59 ms of memory (at the rate its access pattern
+// reaches without arithmetic, lb_pattern_ms) against 0.43 ms of issue at 256^3,
+// so both have to overlap: everything a plane needs from memory is loaded while
+// the plane before it is collided.
 #pragma once
+#include "lb_pack.hpp"
 #include "lb_single.hpp"
 
 namespace lbm {
 
 __device__ __forceinline__ int wave_uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
-// Keep a wave-uniform value in a vector register.
-__device__ __forceinline__ void in_vgpr(float& v) { asm volatile("" : "+v"(v)); }
-__device__ __forceinline__ void in_vgpr(double& v) { asm volatile("" : "+v"(v)); }
 
-// The 19 (t_i, d_i) pair arrays of a raw buffer as four buffer resources of
-// up to five arrays (ten values per site) each: a pull or store is then one
-// buffer access of a pair with the row in a scalar offset and the column in a
-// per-lane offset, with no 64-bit address arithmetic per access.  Each range
-// is exact, so an access outside it reads zero or is dropped.  Needs
-// 10 raw_stride(N) sizeof(T) < 2^32 (checked on the host).
+// Values per buffer resource of the raw forms: the 19 arrays t_i as two
+// resources of 9 and 10 (a direction and its opposite in one), the 19 pair
+// arrays as four of up to five, so that a load or store is one buffer access
+// with a scalar row offset and a per-lane column offset and needs no 64-bit
+// address arithmetic.  Needs 10 raw_stride(N) sizeof(T) < 2^32 (checked on the
+// host).
 constexpr int kResArrays = 10;
 constexpr int kResPairs = kResArrays / 2;
 constexpr unsigned kRsrcWord3 = 0x00020000;  // raw 32-bit buffer on gfx9-family targets
-template <typename T>
-struct PopRes {
-    __amdgpu_buffer_rsrc_t r[4];
-    // S: pairs from one array to the next (raw_stride(N))
-    __device__ __forceinline__ PopRes(const T* f, unsigned S) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const unsigned np = (unsigned)min(kResPairs, Q - k * kResPairs);
-            r[k] = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(f) + (size_t)k * kResArrays * S, 0,
-                                                     (int)(np * S * 2u * (unsigned)sizeof(T)), (int)kRsrcWord3);
-        }
-    }
-};
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-// (t, d) pair loads and non-temporal pair stores
+// (t, d) pair loads
 __device__ __forceinline__ void res_load_pair(float& t, float& d, __amdgpu_buffer_rsrc_t r, unsigned voff,
                                               unsigned soff) {
     const auto v = __builtin_bit_cast(RawPair<float>::type, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0));
@@ -67,20 +53,6 @@ __device__ __forceinline__ void res_load_pair(double& t, double& d, __amdgpu_buf
     const auto v = __builtin_bit_cast(RawPair<double>::type, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
     t = v.x;
     d = v.y;
-}
-__device__ __forceinline__ void res_store_pair(float t, float d, __amdgpu_buffer_rsrc_t r, unsigned voff,
-                                               unsigned soff) {
-    RawPair<float>::type v;
-    v.x = t;
-    v.y = d;
-    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, voff, soff, 2);
-}
-__device__ __forceinline__ void res_store_pair(double t, double d, __amdgpu_buffer_rsrc_t r, unsigned voff,
-                                               unsigned soff) {
-    RawPair<double>::type v;
-    v.x = t;
-    v.y = d;
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, voff, soff, 2);
 }
 __device__ __forceinline__ float res_load(float, __amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff) {
     return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0));
@@ -97,13 +69,15 @@ __device__ __forceinline__ void res_store(double v, __amdgpu_buffer_rsrc_t r, un
     __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(V, v), r, voff, soff, 2);
 }
 
-// Resource over n values of an array whose pointer is made opaque first (the
-// resource is then rebuilt where it is used instead of held in scalar
-// registers across the loop).
+// Resource of an array, its range all 32-bit offsets (every access is in range
+// by its clamped coordinates or masked).  The pointer is made opaque first: the
+// resource is then rebuilt where it is used, from two scalar registers and two
+// constants, instead of holding four registers across the loop, whose resources
+// together would spill.
 template <typename T>
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t array_res(const T* p, unsigned n) {
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t array_res(const T* p) {
     asm volatile("" : "+s"(p));
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(p), 0, (int)(n * (unsigned)sizeof(T)), (int)kRsrcWord3);
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(p), 0, -1, (int)kRsrcWord3);
 }
 // phase-sum pair (own sums of a face site), 8 or 16 bytes
 __device__ __forceinline__ void res_store(const Part2<float>& v, __amdgpu_buffer_rsrc_t r, unsigned voff,
@@ -111,10 +85,15 @@ __device__ __forceinline__ void res_store(const Part2<float>& v, __amdgpu_buffer
     using V = decltype(__builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0));
     __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(V, v), r, voff, soff, 0);
 }
+// (16-byte stores take the whole offset per lane and none in a scalar register:
+// the compiler keeps the instruction after such a store from overwriting its
+// data only in that form, and with a scalar offset a record's first value was
+// seen replaced by the next instruction's result in the last quarter of every
+// 16 lanes)
 __device__ __forceinline__ void res_store(const Part2<double>& v, __amdgpu_buffer_rsrc_t r, unsigned voff,
                                           unsigned soff) {
     using V = decltype(__builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(V, v), r, voff, soff, 0);
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(V, v), r, voff + soff, 0, 0);
 }
 __device__ __forceinline__ void res_store_cached(float v, __amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff) {
     __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, voff, soff, 0);
@@ -145,757 +124,888 @@ __device__ __forceinline__ double from_right(double v) {
     return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
-// Upstream row (scalar): element offset (z*ny + y)*nx of the row a population
-// with velocity (., cy, cz) arriving in row (y, z) comes from, with the
-// periodic wrap.  W: the lattice may have walls; `bb` is then set when that
-// row lies beyond one (the population is a bounce-back).
-template <bool W>
-__device__ __forceinline__ unsigned upstream_row(const Geom& g, int y, int z, int cy, int cz, bool& bb) {
-    int ys = y - cy, zs = z - cz;
-    const bool out_y = ys < 0 || ys >= g.ny, out_z = zs < 0 || zs >= g.nz;
-    ys = ys < 0 ? ys + g.ny : (ys >= g.ny ? ys - g.ny : ys);
-    zs = zs < 0 ? zs + g.nz : (zs >= g.nz ? zs - g.nz : zs);
-    bb = W && ((g.wy && out_y) || (g.wz && out_z));
-    return (unsigned)((zs * g.ny + ys) * g.nx);
-}
-
-// Plane and lane context of the pulls and stores of a lean tile.
-struct LeanPlane {
-    unsigned Np;       // sites N, re-read each plane (keeps array offsets out of loop-invariant registers)
-    unsigned own_row;  // (cz ny + yc) nx, the site's row
-    int yc, cz;        // the site's (clamped) row and its plane
-    int rs[3];         // record-ring slots of planes cz - 1, cz, cz + 1 (16-bit storage)
-};
-struct LeanLane {
-    unsigned cx0, cxm, cxp;   // columns x, x - 1, x + 1 (periodic wrap; beyond an x wall x itself)
-    bool wall_xlo, wall_xhi;  // an x wall lies beyond this lane's site
-    int lane, ty;
-};
-
-// Raw storage: (t_i, d_i) pairs in Q arrays.  Pulls read each array at the
-// upstream row (scalar offset) and column (per lane); stores write in place.
-// The pulls load their values where they need them: loading them one plane
-// ahead takes 2 Q more vector registers, and the occupancy that costs (FP32:
-// 4 -> 2 waves per SIMD) measured slower (256^3: 1.30 against 1.12 ms).
+// 16-byte pieces of a record
+typedef double d2 __attribute__((ext_vector_type(2)));
 template <typename T>
-struct LeanRaw {
+struct Chunk;
+template <>
+struct Chunk<float> {
+    typedef f4 type;
+};
+template <>
+struct Chunk<double> {
+    typedef d2 type;
+};
+template <typename C>
+__device__ __forceinline__ C res_load_chunk(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff) {
+    return __builtin_bit_cast(C, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
+}
+template <typename C>
+__device__ __forceinline__ void res_store_chunk(C v, __amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff) {
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, voff + soff, 0, 2);
+}
+
+// Rows a site's pulls read: r[1 + dz][1 + dy] = first site of the row
+// (y + dy, z + dz) with the periodic wrap, and the walls its row lies next to.
+// All of it is scalar.
+struct LeanRows {
+    unsigned r[3][3];
+    bool ylo, yhi, zlo, zhi;
+    __device__ __forceinline__ unsigned own() const { return r[1][1]; }
+    // the source of direction i lies beyond a y or z wall
+    __device__ __forceinline__ bool beyond(int i) const {
+        using L = Lattice;
+        return (L::cy[i] > 0 && ylo) || (L::cy[i] < 0 && yhi) || (L::cz[i] > 0 && zlo) || (L::cz[i] < 0 && zhi);
+    }
+    __device__ __forceinline__ unsigned from(int i) const { return r[1 - Lattice::cz[i]][1 - Lattice::cy[i]]; }
+};
+// Per-lane context: columns x, x - 1, x + 1 (periodic wrap; beyond an x wall x
+// itself) and the x walls next to the lane's site.
+struct LeanLane {
+    unsigned c0, cm, cp;
+    bool wx, xlo, xhi;
+    int lane, ty, x;
+    __device__ __forceinline__ unsigned col(int i) const {
+        return Lattice::cx[i] > 0 ? cm : (Lattice::cx[i] < 0 ? cp : c0);
+    }
+    __device__ __forceinline__ bool beyond(int i) const {
+        return (Lattice::cx[i] > 0 && xlo) || (Lattice::cx[i] < 0 && xhi);
+    }
+};
+// Offsets of direction i's source value: site = row (scalar) + column (lane),
+// in array a.  Off a y or z wall the wavefront reads the opposite direction of
+// its own row; with x walls the lanes next to one do (W only).
+//   load(a, row, col): the value at that row and column of array a
+//   load_at(site_and_array offset per lane)
+template <bool W, typename Load, typename LoadLane>
+__device__ __forceinline__ void source_of(int i, const LeanRows& rw, const LeanLane& ln, const Load& load,
+                                          const LoadLane& load_lane) {
+    using L = Lattice;
+    if constexpr (W) {
+        const bool bb = rw.beyond(i);
+        const int a = bb ? L::opp[i] : i;
+        const unsigned row = bb ? rw.own() : rw.from(i);
+        const unsigned col = bb ? ln.c0 : ln.col(i);
+        if (L::cx[i] != 0 && ln.wx) load_lane(a, row, col, L::opp[i], rw.own(), ln.c0, ln.beyond(i));
+        else load(a, row, col);
+    } else {
+        load(i, rw.from(i), ln.col(i));
+    }
+}
+
+// halo_coord along z for a plane at most a few halos beyond the lattice, without
+// a division (the scalar unit has none).
+__device__ __forceinline__ int halo_plane(int z, int n, int wall) {
+    if (wall) {
+        const int m = z < 0 ? -1 - z : (z >= n ? 2 * n - 1 - z : z);
+        return m < 0 ? 0 : (m >= n ? n - 1 : m);
+    }
+    while (z < 0) z += n;
+    while (z >= n) z -= n;
+    return z;
+}
+
+// LDS ring of the source records of planes z - 1, z, z + 1 (tile plus one site
+// around it): per plane NC runs of 16-byte pieces, so consecutive lanes read
+// consecutive pieces, free of bank conflicts.
+constexpr int kRecRow = kTileX + 2;
+template <typename C, int NC, int TY>
+struct RecPlanes {
+    C* base;
+    static constexpr int half = (TY + 2) * kRecRow;
+    static constexpr int plane = NC * half;
+    static constexpr size_t bytes = (size_t)3 * plane * sizeof(C);
+    // piece k of ring entry e of slot s
+    __device__ __forceinline__ C& at(int s, int k, int e) const { return base[s * plane + k * half + e]; }
+};
+
+// ------------------------------------------------------------- pair arrays
+// Source of a state's first step: pairs (t_i, d_i), read where they are needed.
+template <typename T>
+struct LeanPairs {
     using R = T;
-    static constexpr bool split = false;
-    const T* fin;
-    T* fout;
-    __host__ __device__ static constexpr size_t ring_bytes(int) { return 0; }
+    using C = typename Chunk<T>::type;
+    static constexpr int NC = 0;
+    const T* f;
     struct Pre {};
-    __device__ __forceinline__ void stage_load(const Geom&, int, int, int, int, int, Pre&) const {}
-    __device__ __forceinline__ void stage_store(int, int, int, const Pre&) const {}
-
-    // t_i, d_i of site (x, yc, cz): direction i at the upstream site, or (a
-    // bounce-back off a y or z wall) the opposite direction at the site itself
-    template <bool W>
-    __device__ __forceinline__ void load(const Geom& g, int yc, int cz, const LeanLane& ln, T (&t)[Q],
-                                         T (&d)[Q]) const {
-        using L = Lattice;
-        unsigned Sp = (unsigned)raw_stride((size_t)g.N);
-        asm volatile("" : "+s"(Sp));
-        const T* fin_p = fin;
-        asm volatile("" : "+s"(fin_p));  // resources rebuilt each plane (short-lived scalar registers)
-        const PopRes<T> fi(fin_p, Sp);
-        constexpr unsigned SZ = 2 * (unsigned)sizeof(T);  // bytes of a (t, d) pair
-        const unsigned bx0 = ln.cx0 * SZ, bxm = ln.cxm * SZ, bxp = ln.cxp * SZ;
-        const unsigned own_row = (unsigned)((cz * g.ny + yc) * g.nx);
-        // byte offset of direction i's pair at site e within its resource
-        auto soff = [&](int i, unsigned e) { return ((unsigned)(i % kResPairs) * Sp + e) * SZ; };
+    // four resources of up to five arrays
+    struct Res {
+        __amdgpu_buffer_rsrc_t r[4];
+    };
+    __device__ __forceinline__ Res res(unsigned N) const {
+        const unsigned S = N + kRawPad;
+        Res o;
 #pragma unroll
-        for (int i = 0; i < Q; ++i) {
-            bool bb;
-            const unsigned row = upstream_row<W>(g, yc, cz, L::cy[i], L::cz[i], bb);
-            const unsigned col = L::cx[i] > 0 ? bxm : (L::cx[i] < 0 ? bxp : bx0);
-            if (W && bb) {
-                const int o = L::opp[i];
-                res_load_pair(t[i], d[i], fi.r[o / kResPairs], bx0, soff(o, own_row));
-            } else {
-                res_load_pair(t[i], d[i], fi.r[i / kResPairs], col, soff(i, row));
-            }
-        }
+        for (int k = 0; k < 4; ++k) o.r[k] = array_res(f + (size_t)k * kResArrays * S);
+        return o;
     }
     template <bool W>
-    __device__ __forceinline__ void dev_load(const Geom&, int, int, const LeanLane&, Pre&) const {}
+    __device__ __forceinline__ void fetch(const Geom&, const LeanRows&, const LeanLane&, Pre&) const {}
 
-    // MV: the lattice may have moving walls (resting-wall kernels carry none
-    // of that code)
-    template <bool W, bool MV>
-    __device__ __forceinline__ void pull(const Geom& g, const LeanPlane& P, const LeanLane& ln, const Pre&,
-                                         R (&t)[Q], R (&d)[Q]) const {
-        using L = Lattice;
-        load<W>(g, P.yc, P.cz, ln, t, d);
-        if constexpr (W) {
-            // lanes next to an x wall: their bounce-backs, from the site itself
-            constexpr unsigned SZ = 2 * (unsigned)sizeof(T);
-            const unsigned bx0 = ln.cx0 * SZ;
-            const unsigned Sp = P.Np + kRawPad;
-            auto soff = [&](int i, unsigned e) { return ((unsigned)(i % kResPairs) * Sp + e) * SZ; };
-            const T* fin_p = fin;
-            asm volatile("" : "+s"(fin_p));
-            const PopRes<T> fi(fin_p, Sp);
-            if (ln.wall_xlo || ln.wall_xhi) {
+    // The own post-collision phase from the pairs of the site itself.
+    template <int TY>
+    __device__ __forceinline__ T own_phase(const Geom& g, unsigned own, const LeanLane& ln,
+                                           const RecPlanes<C, 1, TY>&, int) const {
+        const Res rs = res((unsigned)g.N);
+        constexpr unsigned SZ = 2 * (unsigned)sizeof(T);
+        const unsigned S = (unsigned)g.N + kRawPad;
+        T st = T(0), sd = T(0);
 #pragma unroll
-                for (int i = 1; i < Q; ++i) {
-                    if (!((L::cx[i] > 0 && ln.wall_xlo) || (L::cx[i] < 0 && ln.wall_xhi))) continue;
-                    const int o = L::opp[i];
-                    res_load_pair(t[i], d[i], fi.r[o / kResPairs], bx0, soff(o, P.own_row));
-                }
-            }
-            // moving walls: each reflected direction gains the wall term,
-            // shared between the components by the site's own post-collision
-            // phase (as RawPop::add_wall_terms)
-            const bool wyz = (g.wy && (P.yc == 0 || P.yc == g.ny - 1)) || (g.wz && (P.cz == 0 || P.cz == g.nz - 1));
-            if (MV && g.moving && (wyz || ln.wall_xlo || ln.wall_xhi)) {
-                R st = R(0), sd = R(0);
-                for (int j = 0; j < Q; ++j) {
-                    R tj, dj;
-                    res_load_pair(tj, dj, fi.r[j / kResPairs], bx0, soff(j, P.own_row));
-                    st += weight<R>(j) + tj;
-                    sd += dj;
-                }
-                const R ph = sd / st;
-#pragma unroll
-                for (int i = 1; i < Q; ++i) {
-                    bool bb;
-                    (void)upstream_row<W>(g, P.yc, P.cz, L::cy[i], L::cz[i], bb);
-                    const bool rx = (L::cx[i] > 0 && ln.wall_xlo) || (L::cx[i] < 0 && ln.wall_xhi);
-                    if (!(bb || rx)) continue;
-                    const R add = wall_term<R>(g, i, (int)ln.cx0, P.yc, P.cz);
-                    t[i] += add;
-                    d[i] += add * ph;
-                }
-            }
+        for (int j = 0; j < Q; ++j) {
+            T tj, dj;
+            res_load_pair(tj, dj, rs.r[j / kResPairs], ln.c0 * SZ, ((unsigned)(j % kResPairs) * S + own) * SZ);
+            st += weight<T>(j) + tj;
+            sd += dj;
         }
+        return sd / st;
     }
-
-    // Store, and keep in t, d the values a later pull reads.
-    __device__ __forceinline__ void store(const Geom&, const LeanPlane& P, const LeanLane& ln, R (&t)[Q],
-                                          R (&d)[Q], const SiteTotals<R>&, bool site_in) const {
-        if (site_in) {
-            T* fout_p = fout;
-            asm volatile("" : "+s"(fout_p));
-            const unsigned Sp = P.Np + kRawPad;
-            const PopRes<T> fo(fout_p, Sp);
-            constexpr unsigned SZ = 2 * (unsigned)sizeof(T);
-            auto soff = [&](int i, unsigned e) { return ((unsigned)(i % kResPairs) * Sp + e) * SZ; };
-#pragma unroll
-            for (int i = 0; i < Q; ++i) res_store_pair(T(t[i]), T(d[i]), fo.r[i / kResPairs], ln.cx0 * SZ, soff(i, P.own_row));
-        }
+    template <bool W, int TY>
+    __device__ __forceinline__ void values(const Geom& g, const LeanRows& rw, const LeanLane& ln,
+                                           const RecPlanes<C, 1, TY>&, int, int, int, const Pre&, T (&t)[Q],
+                                           T (&d)[Q]) const {
+        const Res rs = res((unsigned)g.N);
+        constexpr unsigned SZ = 2 * (unsigned)sizeof(T);
+        const unsigned S = (unsigned)g.N + kRawPad;
 #pragma unroll
         for (int i = 0; i < Q; ++i) {
-            t[i] = R(T(t[i]));
-            d[i] = R(T(d[i]));
+            // (a direction and its opposite may lie in different resources)
+            auto off = [&](int a, unsigned row) { return ((unsigned)(a % kResPairs) * S + row) * SZ; };
+            const int o = Lattice::opp[i];
+            bool bb = false;
+            if constexpr (W) bb = rw.beyond(i);
+            if (bb) res_load_pair(t[i], d[i], rs.r[o / kResPairs], ln.c0 * SZ, off(o, rw.own()));
+            else res_load_pair(t[i], d[i], rs.r[i / kResPairs], ln.col(i) * SZ, off(i, rw.from(i)));
+            if constexpr (W) {
+                if (Lattice::cx[i] != 0 && ln.beyond(i))
+                    res_load_pair(t[i], d[i], rs.r[o / kResPairs], ln.c0 * SZ, off(o, rw.own()));
+            }
         }
     }
 };
 
-// 16-bit moment-split storage (the codec of SplitPop): per site an FP32
-// record of 8 values, per direction a 16-bit deviation.  The records of
-// planes cz - 1, cz, cz + 1 (tile plus one site) sit in an LDS ring, staged a
-// plane ahead, so a pull reads its source record from LDS and only the 16-bit
-// deviation from memory (scalar row offset, per-lane column).
-__device__ __forceinline__ f4 res_load4(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff) {
-    return __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
-}
-__device__ __forceinline__ void res_store4(f4 v, __amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff) {
-    using V = decltype(__builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(V, v), r, voff, soff, 2);
-}
+// ------------------------------------------------------------------ packed
+template <typename T>
+struct LeanPack {
+    using R = T;
+    using C = typename Chunk<T>::type;
+    static constexpr int NC = (int)(sizeof(T) / 4);  // pieces of a record
+    T* rec;
+    T* tot;
+    struct Pre {
+        T v[Q];
+    };
+    static constexpr int kFirst = 9;  // arrays of the first resource
+    static __device__ __forceinline__ int part(int i) { return i < kFirst ? 0 : 1; }
+    static __device__ __forceinline__ unsigned off(int i, unsigned S, unsigned site) {
+        return ((unsigned)(i < kFirst ? i : i - kFirst) * S + site) * (unsigned)sizeof(T);
+    }
+    struct Res {
+        __amdgpu_buffer_rsrc_t t[2];
+    };
+    __device__ __forceinline__ Res res(unsigned N) const {
+        return Res{{array_res(tot), array_res(tot + (size_t)kFirst * (N + kRawPad))}};
+    }
+    __device__ __forceinline__ __amdgpu_buffer_rsrc_t rec_res() const { return array_res(rec); }
+    template <bool W>
+    __device__ __forceinline__ void fetch(const Geom& g, const LeanRows& rw, const LeanLane& ln, Pre& p) const {
+        const Res rs = res((unsigned)g.N);
+        const unsigned S = (unsigned)g.N + kRawPad;
+        unsigned step = S * (unsigned)sizeof(T), at = 0;  // array offset, accumulated (re-read each plane:
+        asm volatile("" : "+s"(step));                    // 19 loop-invariant offsets would spill)
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+            if (i == kFirst) at = 0;
+            source_of<W>(
+                i, rw, ln,
+                [&](int a, unsigned row, unsigned col) {
+                    if constexpr (W)
+                        p.v[i] = res_load(T(0), rs.t[part(i)], col * (unsigned)sizeof(T), off(a, S, row));
+                    else
+                        p.v[i] = res_load(T(0), rs.t[part(i)], col * (unsigned)sizeof(T),
+                                          at + row * (unsigned)sizeof(T));
+                },
+                [&](int a, unsigned row, unsigned col, int o, unsigned own, unsigned c0, bool refl) {
+                    const unsigned v = refl ? off(o, S, own) + c0 * (unsigned)sizeof(T)
+                                            : off(a, S, row) + col * (unsigned)sizeof(T);
+                    p.v[i] = res_load(T(0), rs.t[part(i)], v, 0);
+                });
+            at += step;
+        }
+    }
+    template <int TY>
+    static __device__ __forceinline__ Colour<T> colour(const RecPlanes<C, NC, TY>& rp, int s, int e) {
+        if constexpr (NC == 1) {
+            const C a = rp.at(s, 0, e);
+            return Colour<T>{a.x, a.y, a.z, a.w};
+        } else {
+            const C a = rp.at(s, 0, e), b = rp.at(s, 1, e);
+            return Colour<T>{a.x, a.y, b.x, b.y};
+        }
+    }
+    // The own post-collision phase, summed as RawPop sums its pairs; s0: slot of
+    // the site's plane.
+    template <int TY>
+    __device__ __forceinline__ T own_phase(const Geom& g, unsigned own, const LeanLane& ln,
+                                           const RecPlanes<C, NC, TY>& rp, int s0) const {
+        const Res rs = res((unsigned)g.N);
+        const Colour<T> q = colour<TY>(rp, s0, (ln.ty + 1) * kRecRow + ln.lane + 1);
+        const unsigned S = (unsigned)g.N + kRawPad;
+        T st = T(0), sd = T(0);
+#pragma unroll
+        for (int j = 0; j < Q; ++j) {
+            const T v = res_load(T(0), rs.t[part(j)], ln.c0 * (unsigned)sizeof(T), off(j, S, own));
+            st += weight<T>(j) + v;
+            sd += recoloured<T>(j, weight<T>(j) + v, q);
+        }
+        return sd / st;
+    }
+    // Colour difference of a value arriving in direction i, read from the
+    // opposite direction where refl.
+    static __device__ __forceinline__ T diff(int i, T wt, const Colour<T>& q, bool refl) {
+#pragma clang fp contract(off)
+        if (i == 0) return q.phi * wt;
+        const T cs = cdot3<T>(i, q.sx, q.sy, q.sz);
+        constexpr T k = weight<T>(1) / (weight<T>(7) * inv_clen<T>(7));
+        const T v = Lattice::len2(i) == 1 ? k * cs : cs;
+        return fma_of(q.phi, wt, refl ? -v : v);
+    }
+    // t_i, d_i of the site at ring entry e; sm, s0, sp: slots of planes z - 1,
+    // z, z + 1
+    template <bool W, int TY>
+    __device__ __forceinline__ void values(const Geom&, const LeanRows& rw, const LeanLane& ln,
+                                           const RecPlanes<C, NC, TY>& rp, int sm, int s0, int sp, const Pre& p,
+                                           T (&t)[Q], T (&d)[Q]) const {
+        using L = Lattice;
+        const int own = (ln.ty + 1) * kRecRow + ln.lane + 1;
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+            int s = L::cz[i] > 0 ? sm : (L::cz[i] < 0 ? sp : s0), e = own - L::cy[i] * kRecRow - L::cx[i];
+            bool refl = false;
+            if constexpr (W) {
+                refl = rw.beyond(i) || (L::cx[i] != 0 && ln.beyond(i));
+                s = refl ? s0 : s;
+                e = refl ? own : e;
+            }
+            t[i] = p.v[i];
+            d[i] = diff(i, weight<T>(i) + t[i], colour<TY>(rp, s, e), refl);
+        }
+    }
+    // Destination: store the site and keep what a later pull reads of it.
+    struct Kept {
+        Colour<T> q;
+        T phase;
+    };
+    __device__ __forceinline__ void store(const Geom& g, unsigned own, const LeanLane& ln, T (&t)[Q],
+                                          const SiteTotals<T>& tot_, bool site_in, Kept& k) const {
+        k.q = colour_of(tot_);
+        if (site_in) {
+            const Res rs = res((unsigned)g.N);
+            const __amdgpu_buffer_rsrc_t rr = rec_res();
+            const unsigned S = (unsigned)g.N + kRawPad;
+            constexpr unsigned RB = 4 * (unsigned)sizeof(T);
+            if constexpr (NC == 1) {
+                res_store_chunk(C{k.q.phi, k.q.sx, k.q.sy, k.q.sz}, rr, ln.c0 * RB, own * RB);
+            } else {
+                res_store_chunk(C{k.q.phi, k.q.sx}, rr, ln.c0 * RB, own * RB);
+                res_store_chunk(C{k.q.sy, k.q.sz}, rr, ln.c0 * RB + 16u, own * RB);
+            }
+            unsigned step = S * (unsigned)sizeof(T), at = own * (unsigned)sizeof(T);
+            asm volatile("" : "+s"(step));
+#pragma unroll
+            for (int i = 0; i < Q; ++i) {
+                if (i == kFirst) at = own * (unsigned)sizeof(T);
+                res_store(t[i], rs.t[part(i)], ln.c0 * (unsigned)sizeof(T), at);
+                at += step;
+            }
+        }
+    }
+    __device__ __forceinline__ T kept_diff(int i, T wt, const Kept& k) const { return recoloured<T>(i, wt, k.q); }
+    static __device__ __forceinline__ void clear(Kept& k) { k.q = Colour<T>{T(0), T(0), T(0), T(0)}; }
+    // phase a moving wall's term is shared by: from the stored values
+    __device__ __forceinline__ T kept_phase(const T (&t)[Q], const Kept& k) const {
+        T st = T(0), sd = T(0);
+#pragma unroll
+        for (int j = 0; j < Q; ++j) {
+            st += weight<T>(j) + t[j];
+            sd += recoloured<T>(j, weight<T>(j) + t[j], k.q);
+        }
+        return sd / st;
+    }
+};
+
+// ------------------------------------------------- 16-bit moment-split form
+// (the codec of SplitPop): per site an FP32 record of 8 values, per direction a
+// 16-bit deviation.
 template <typename H>
 struct LeanSplit {
     using R = float;
-    static constexpr bool split = true;
-    static constexpr int LXR = kTX + 2;  // ring row: the tile's 64 columns and one on each side
-    const float* rin;                   // records [N][8] of the current state
-    const H* din;                       // deviations [Q][N] of the current state
-    float* rout;                        // the same of the next state
-    H* dout;
-    SplitPop<H> codec;                  // scale and the record arithmetic
-    f4* ring;                           // LDS: 3 planes x 2 halves x (TY + 2) rows x LXR sites, f4
-    int TY;
-    __host__ __device__ static constexpr size_t ring_bytes(int ty) {
-        return (size_t)3 * (ty + 2) * LXR * 2 * sizeof(f4);
-    }
-    // a plane holds the first f4 of every site, then (half() later) the second:
-    // consecutive lanes read consecutive 16-byte words, free of bank conflicts
-    __device__ __forceinline__ f4* plane(int slot) const { return ring + (size_t)slot * (TY + 2) * LXR * 2; }
-    __device__ __forceinline__ int half() const { return (TY + 2) * LXR; }
-    __device__ __forceinline__ __amdgpu_buffer_rsrc_t rec_res(const float* p, unsigned N) const {
-        asm volatile("" : "+s"(p));
-        return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, (int)(N * 32u), (int)kRsrcWord3);
-    }
-    __device__ __forceinline__ __amdgpu_buffer_rsrc_t dev_res(const H* p, unsigned N) const {
-        asm volatile("" : "+s"(p));
-        return __builtin_amdgcn_make_buffer_rsrc(const_cast<H*>(p), 0, (int)(Q * (N + kDevPad) * 2u), (int)kRsrcWord3);
-    }
-
-    // Loaded one plane ahead, so that their latency overlaps a collision:
-    // records of two ring rows (and of the two columns past the tile) for the
-    // next staging, and the 16-bit deviations of the next site's pulls.
+    using C = f4;
+    static constexpr int NC = 2;
+    float* rec;
+    H* dev;
+    SplitPop<H> codec;  // scale and the record arithmetic
     struct Pre {
-        f4 a0[2], a1[2], b0[2], b1[2];
-        unsigned dv[Q];  // the 16-bit deviations, one per register (two per register would make
-                         // every load wait at once for the packing)
+        unsigned dv[Q];  // one per register (two per register would make every load wait
+                         // at once for the packing)
     };
     static __device__ __forceinline__ H dev_of(unsigned v) { return __builtin_bit_cast(H, (unsigned short)v); }
-
-    // Records of plane q, rows y0 - 1 .. y0 + TY and columns x0 - 1 .. x0 + 64
-    // (periodic wrap or mirror images beyond walls): loaded into registers,
-    // then (stage_store) written to a ring slot.  Thread row ty takes ring
-    // rows ty and ty + TY (TY >= 2: at most two rows).
-    __device__ __forceinline__ void stage_load(const Geom& g, int q, int x0, int y0, int ty, int lane,
-                                               Pre& pr) const {
-        const int zz = halo_coord(q, g.nz, g.wz);
-        const unsigned ca = (unsigned)halo_coord(x0 - 1 + lane, g.nx, g.wx) * 32u;
-        const unsigned cb = (unsigned)halo_coord(x0 - 1 + kTX + lane, g.nx, g.wx) * 32u;
-        const __amdgpu_buffer_rsrc_t rr = rec_res(rin, (unsigned)g.N);
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const int r = ty + k * TY;
-            if (r < TY + 2) {
-                const int yy = halo_coord(y0 - 1 + r, g.ny, g.wy);
-                const unsigned so = (unsigned)((zz * g.ny + yy) * g.nx) * 32u;
-                pr.a0[k] = res_load4(rr, ca, so);
-                pr.a1[k] = res_load4(rr, ca + 16u, so);
-                if (lane < 2) {
-                    pr.b0[k] = res_load4(rr, cb, so);
-                    pr.b1[k] = res_load4(rr, cb + 16u, so);
-                }
-            }
-        }
+    static __device__ __forceinline__ unsigned off(int i, unsigned S, unsigned site) {
+        return ((unsigned)i * S + site) * 2u;
     }
-    __device__ __forceinline__ void stage_store(int slot, int ty, int lane, const Pre& pr) const {
-        f4* pl = plane(slot);
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const int r = ty + k * TY;
-            if (r < TY + 2) {
-                pl[r * LXR + lane] = pr.a0[k];
-                pl[half() + r * LXR + lane] = pr.a1[k];
-                if (lane < 2) {
-                    pl[r * LXR + kTX + lane] = pr.b0[k];
-                    pl[half() + r * LXR + kTX + lane] = pr.b1[k];
-                }
-            }
-        }
-    }
-
-    // Deviations the pulls of site (x, yc, cz) read: direction i at the
-    // upstream site, or (a bounce-back off a y or z wall) the opposite
-    // direction at the site itself; the lanes next to an x wall re-read
-    // theirs in pull.
+    __device__ __forceinline__ __amdgpu_buffer_rsrc_t rec_res() const { return array_res(rec); }
     template <bool W>
-    __device__ __forceinline__ void dev_load(const Geom& g, int yc, int cz, const LeanLane& ln, Pre& pr) const {
-        using L = Lattice;
-        unsigned Np = (unsigned)g.N;
-        asm volatile("" : "+s"(Np));
-        const unsigned own_row = (unsigned)((cz * g.ny + yc) * g.nx);
-        const __amdgpu_buffer_rsrc_t dr = dev_res(din, Np);
+    __device__ __forceinline__ void fetch(const Geom& g, const LeanRows& rw, const LeanLane& ln, Pre& p) const {
+        const __amdgpu_buffer_rsrc_t rd = array_res(dev);
+        const unsigned S = (unsigned)g.N + kDevPad;
+        unsigned step = 2u * S, at = 0;
+        asm volatile("" : "+s"(step));
 #pragma unroll
         for (int i = 0; i < Q; ++i) {
-            bool bb;
-            const unsigned row = upstream_row<W>(g, yc, cz, L::cy[i], L::cz[i], bb);
-            const int a = (W && bb) ? L::opp[i] : i;
-            const unsigned col = (W && bb) ? ln.cx0 : (L::cx[i] > 0 ? ln.cxm : (L::cx[i] < 0 ? ln.cxp : ln.cx0));
-            const unsigned rw = (W && bb) ? own_row : row;
-            pr.dv[i] = __builtin_amdgcn_raw_buffer_load_b16(dr, col * 2u, ((unsigned)a * (Np + kDevPad) + rw) * 2u, 0);
+            source_of<W>(
+                i, rw, ln,
+                [&](int a, unsigned row, unsigned col) {
+                    p.dv[i] = __builtin_amdgcn_raw_buffer_load_b16(rd, col * 2u, W ? off(a, S, row) : at + 2u * row, 0);
+                },
+                [&](int a, unsigned row, unsigned col, int o, unsigned own, unsigned c0, bool refl) {
+                    const unsigned v = refl ? off(o, S, own) + c0 * 2u : off(a, S, row) + col * 2u;
+                    p.dv[i] = __builtin_amdgcn_raw_buffer_load_b16(rd, v, 0, 0);
+                });
+            at += step;
         }
     }
-
-    template <bool W, bool MV>
-    __device__ __forceinline__ void pull(const Geom& g, const LeanPlane& P, const LeanLane& ln, const Pre& pr,
-                                         R (&t)[Q], R (&d)[Q]) const {
+    template <bool W, int TY>
+    __device__ __forceinline__ void values(const Geom&, const LeanRows& rw, const LeanLane& ln,
+                                           const RecPlanes<C, NC, TY>& rp, int sm, int s0, int sp, const Pre& p,
+                                           float (&t)[Q], float (&d)[Q]) const {
         using L = Lattice;
-        const f4* pm = plane(P.rs[0]);
-        const f4* p0 = plane(P.rs[1]);
-        const f4* pp = plane(P.rs[2]);
-        const int own = (ln.ty + 1) * LXR + ln.lane + 1;
+        const int own = (ln.ty + 1) * kRecRow + ln.lane + 1;
 #pragma unroll
         for (int i = 0; i < Q; ++i) {
-            bool bb;
-            (void)upstream_row<W>(g, P.yc, P.cz, L::cy[i], L::cz[i], bb);
-            if (W && bb) {
-                codec.decode(i, L::opp[i], p0[own], p0[half() + own], dev_of(pr.dv[i]), t[i], d[i]);
-            } else {
-                // the source (x - c_i) in plane cz - c_z: cz - 1 is pm, cz + 1 is pp
-                const f4* pl = L::cz[i] > 0 ? pm : (L::cz[i] < 0 ? pp : p0);
-                const int pos = own - L::cy[i] * LXR - L::cx[i];
-                codec.decode(i, i, pl[pos], pl[half() + pos], dev_of(pr.dv[i]), t[i], d[i]);
+            int s = L::cz[i] > 0 ? sm : (L::cz[i] < 0 ? sp : s0), e = own - L::cy[i] * kRecRow - L::cx[i];
+            float sg = 1.0f;
+            if constexpr (W) {
+                const bool refl = rw.beyond(i) || (L::cx[i] != 0 && ln.beyond(i));
+                s = refl ? s0 : s;
+                e = refl ? own : e;
+                sg = refl ? -1.0f : 1.0f;
             }
-        }
-        if constexpr (W) {
-            if (ln.wall_xlo || ln.wall_xhi) {
-                const __amdgpu_buffer_rsrc_t dr = dev_res(din, P.Np);
-#pragma unroll
-                for (int i = 1; i < Q; ++i) {
-                    if (!((L::cx[i] > 0 && ln.wall_xlo) || (L::cx[i] < 0 && ln.wall_xhi))) continue;
-                    const int o = L::opp[i];
-                    const H dv = __builtin_bit_cast(H, __builtin_amdgcn_raw_buffer_load_b16(
-                                                           dr, ln.cx0 * 2u, ((unsigned)o * (P.Np + kDevPad) + P.own_row) * 2u, 0));
-                    codec.decode(i, o, p0[own], p0[half() + own], dv, t[i], d[i]);
-                }
-            }
-            // moving walls: each reflected direction gains the wall term,
-            // shared by the phase of the site's own record (as
-            // SplitPop::add_wall_terms)
-            const bool wyz = (g.wy && (P.yc == 0 || P.yc == g.ny - 1)) || (g.wz && (P.cz == 0 || P.cz == g.nz - 1));
-            if (MV && g.moving && (wyz || ln.wall_xlo || ln.wall_xhi)) {
-                const float ph = p0[half() + own].x;
-#pragma unroll
-                for (int i = 1; i < Q; ++i) {
-                    bool bb;
-                    (void)upstream_row<W>(g, P.yc, P.cz, L::cy[i], L::cz[i], bb);
-                    const bool rx = (L::cx[i] > 0 && ln.wall_xlo) || (L::cx[i] < 0 && ln.wall_xhi);
-                    if (!(bb || rx)) continue;
-                    const R add = wall_term<R>(g, i, (int)ln.cx0, P.yc, P.cz);
-                    t[i] += add;
-                    d[i] += add * R(ph);
-                }
-            }
+            const f4 ra = rp.at(s, 0, e), rb = rp.at(s, 1, e);
+            codec.finish(i, sg, SplitPop<H>::excess(i, sg, ra), rb, dev_of(p.dv[i]), t[i], d[i]);
         }
     }
-
-    // Encode and store the record and the deviations, and keep in t, d the
-    // values a later pull decodes (exactly: the same codec arithmetic).
-    __device__ __forceinline__ void store(const Geom& g, const LeanPlane& P, const LeanLane& ln, R (&t)[Q],
-                                          R (&d)[Q], const SiteTotals<R>& tot, bool site_in) const {
+    // The phase of the site's own record.
+    template <int TY>
+    __device__ __forceinline__ float own_phase(const Geom&, unsigned, const LeanLane& ln,
+                                               const RecPlanes<C, NC, TY>& rp, int s0) const {
+        return rp.at(s0, 1, (ln.ty + 1) * kRecRow + ln.lane + 1).x;
+    }
+    // Destination: encode and store the record and the deviations, and keep in
+    // t the totals a later pull decodes (exactly: the same codec arithmetic).
+    struct Kept {
+        f4 rb;
+    };
+    __device__ __forceinline__ void store(const Geom& g, unsigned own, const LeanLane& ln, float (&t)[Q],
+                                          const SiteTotals<float>& tot, bool site_in, Kept& k) const {
+#pragma clang fp contract(off)
         const f4 ra = {tot.drho, tot.jx, tot.jy, tot.jz};
-        const f4 rb = {tot.phi, tot.vx, tot.vy, tot.vz};
+        k.rb = f4{tot.phi, tot.vx, tot.vy, tot.vz};
         H h[Q];
-        float X[Q];
 #pragma unroll
         for (int i = 0; i < Q; ++i) {
-            X[i] = SplitPop<H>::excess(i, 1.0f, ra);
-            h[i] = Half<H>::from_f((t[i] - weight<float>(i) * X[i]) * codec.scale);
+            const float wX = weight<float>(i) * SplitPop<H>::excess(i, 1.0f, ra);
+            h[i] = Half<H>::from_f((t[i] - wX) * codec.scale);
+            t[i] = fma_of(Half<H>::to_f(h[i]), codec.inv_scale, wX);
         }
         if (site_in) {
-            const __amdgpu_buffer_rsrc_t rr = rec_res(rout, P.Np);
-            const __amdgpu_buffer_rsrc_t dr = dev_res(dout, P.Np);
-            res_store4(ra, rr, ln.cx0 * 32u, P.own_row * 32u);
-            res_store4(rb, rr, ln.cx0 * 32u + 16u, P.own_row * 32u);
+            const unsigned S = (unsigned)g.N + kDevPad;
+            const __amdgpu_buffer_rsrc_t rr = rec_res(), rd = array_res(dev);
+            res_store_chunk(ra, rr, ln.c0 * 32u, own * 32u);
+            res_store_chunk(k.rb, rr, ln.c0 * 32u + 16u, own * 32u);
+            unsigned step = 2u * S, at = 2u * own;
+            asm volatile("" : "+s"(step));
 #pragma unroll
-            for (int i = 0; i < Q; ++i)
-                __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, h[i]), dr, ln.cx0 * 2u,
-                                                      ((unsigned)i * (P.Np + kDevPad) + P.own_row) * 2u, 2);
-        }
-        (void)g;
-#pragma unroll
-        for (int i = 0; i < Q; ++i) {
-            float tt, dd;
-            codec.finish(i, 1.0f, X[i], rb, h[i], tt, dd);
-            t[i] = tt;
-            d[i] = dd;
+            for (int i = 0; i < Q; ++i) {
+                __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, h[i]), rd, ln.c0 * 2u, at, 2);
+                at += step;
+            }
         }
     }
+    __device__ __forceinline__ float kept_diff(int i, float wt, const Kept& k) const {
+        return SplitPop<H>::colour_diff(i, 1.0f, wt, k.rb);
+    }
+    static __device__ __forceinline__ void clear(Kept& k) { k.rb = f4{0.0f, 0.0f, 0.0f, 0.0f}; }
+    __device__ __forceinline__ float kept_phase(const float (&)[Q], const Kept& k) const { return k.rb.x; }
 };
 
-// Exchange rows in LDS: per tile row, kXchDirs x 2 values (w_i + t_i, d_i)
-// of the directions with c_y != 0, each a row of 64 lanes with a zero pad
-// before and after it.
-constexpr int kLeanRowPad = kTX + 2;
-template <typename R, int TY>
-__host__ __device__ constexpr size_t lean_xch_bytes() {
-    return (size_t)TY * 2 * kXchDirs * kLeanRowPad * sizeof(R);
-}
+// ------------------------------------------------------------ phase sums
+// What a row sends to the rows above and below it, summed over the columns it
+// comes from: slot (e, f) for direction velocities c_y = e, c_z = f.
+__host__ __device__ constexpr int xch_slot(int e, int f) { return (e > 0 ? 0 : 3) + (f == 0 ? 0 : (f > 0 ? 1 : 2)); }
+constexpr int kXchSlots = 6;
+constexpr int kXchRow = kTileX + 2;  // a row's 64 columns and one beyond each end (x-face terms)
 
-// As xedge_rows, reading the exchange rows of the lean tile: the in-plane
-// terms from the rows above and below that the edge lanes of those rows send
-// across this x face (ascending direction); the chunk's last plane is then
-// complete.
-template <typename R, int TY, int SX>
-__device__ __forceinline__ void lean_xedge_rows(const Geom& g, const R* __restrict__ xch, Part2<R>* __restrict__ vs,
-                                                int ty, int tx, int nrows, int y, int cz, int za, int zb, int bd,
-                                                Part2<R>* __restrict__ xf) {
-    using L = Lattice;
-    constexpr int XROW = 2 * kXchDirs * kLeanRowPad;
+// LDS of a tile with source S: phase ring, record ring, exchange rows (D and R
+// sums at once, or one after the other where both do not fit), x-face sums.
+template <typename S, int TY, int H>
+struct LeanLds {
+    using R = typename S::R;
+    static constexpr size_t phi = (phi_ring_bytes<R, kTileX, H>(TY) + 15) & ~size_t(15);
+    static constexpr size_t rec = RecPlanes<typename S::C, S::NC, TY>::bytes;
+    static constexpr size_t half = (size_t)TY * kXchSlots * kXchRow * sizeof(R);
+    static constexpr size_t vs = (size_t)2 * 3 * TY * sizeof(Part2<R>);
+    static constexpr int rounds = phi + rec + 2 * half + vs <= kLdsBytes ? 1 : 2;
+    static constexpr size_t xch = rounds == 1 ? 2 * half : half;
+    static constexpr size_t bytes = phi + rec + xch + vs;
+};
+
+// x-face sums an edge lane of a tile column accumulates for the face sites of
+// the neighbouring column: the lo edge lane (SX = -1) feeds the hi face of the
+// column on its left, the hi edge lane (SX = +1) the lo face of the one on its
+// right (periodic wrap; none beyond an x wall).  The running sums of the
+// destination planes z-1, z, z+1 of its row live in LDS, vs[side][plane mod
+// 3][row].  Before the exchange: the lane's own terms of plane cz close the sum
+// of destination plane cz - 1 (stored), add the first in-plane term of plane cz
+// and open the sum of plane cz + 1.  a, d: w_i + t_i and d_i of direction i.
+template <int SX, typename R, int TY, typename V>
+__device__ __forceinline__ void xedge_own(const Geom& g, const V& val, Part2<R>* __restrict__ vs, int ty, int y, int cz,
+                                          int k0, int za, int zb, int bd, __amdgpu_buffer_rsrc_t xf) {
+    constexpr int im = dir_of(SX, 0, -1), i0 = dir_of(SX, 0, 0), ip = dir_of(SX, 0, 1);
+    constexpr int side = SX < 0 ? 0 : 1;
+    const int km = k0 == 0 ? 2 : k0 - 1, kp = k0 == 2 ? 0 : k0 + 1;
+    Part2<R>* v = vs + side * 3 * TY + ty;
+    if (cz - 1 >= za) {
+        Part2<R> P = v[km * TY];
+        const Part2<R> e = val(im);
+        P.rc += e.rc;
+        P.dn += e.dn;
+        res_store(P, xf, 0, xface_at(g, bd, 1 - side, y, cz - 1) * (unsigned)sizeof(P));
+    }
+    Part2<R> P = cz == za ? Part2<R>{R(0), R(0)} : v[k0 * TY];
+    const Part2<R> e = val(i0);
+    P.rc += e.rc;
+    P.dn += e.dn;
+    v[k0 * TY] = P;
+    if (cz + 1 < zb) v[kp * TY] = val(ip);
+}
+// After the exchange: the in-plane terms the edge lanes of the rows below and
+// above send across the face (ascending direction); the chunk's last plane is
+// then complete.  up, dn: those terms of the two rows.
+template <int SX, typename R, int TY>
+__device__ __forceinline__ void xedge_rows(const Geom& g, const Part2<R>& up, const Part2<R>& dn,
+                                           Part2<R>* __restrict__ vs, int ty, int y, int cz, int k0, int zb, int bd,
+                                           __amdgpu_buffer_rsrc_t xf) {
     constexpr int side = SX < 0 ? 0 : 1;
     Part2<R>* v = vs + side * 3 * TY + ty;
-    Part2<R> P = v[((cz - za) % 3) * TY];
-#pragma unroll
-    for (int i = 1; i < Q; ++i) {
-        if (L::cx[i] != SX || L::cz[i] != 0 || L::cy[i] == 0) continue;
-        const int ys = ty - L::cy[i];
-        if (ys < 0 || ys >= nrows) continue;
-        const R* src = xch + ys * XROW + 1 + tx;
-        P.rc += src[(2 * xch_slot(i)) * kLeanRowPad];
-        P.dn += src[(2 * xch_slot(i) + 1) * kLeanRowPad];
-    }
-    if (cz == zb - 1) xf[xface_at(g, bd, 1 - side, y, cz)] = P;
-    else v[((cz - za) % 3) * TY] = P;
+    Part2<R> P = v[k0 * TY];
+    // c_x = +1: directions 7 (from the row below) then 9 (from the row above);
+    // c_x = -1: 8 (above) then 10 (below)
+    P.rc += SX > 0 ? up.rc : dn.rc;
+    P.dn += SX > 0 ? up.dn : dn.dn;
+    P.rc += SX > 0 ? dn.rc : up.rc;
+    P.dn += SX > 0 ? dn.dn : up.dn;
+    if (cz == zb - 1) res_store(P, xf, 0, xface_at(g, bd, 1 - side, y, cz) * (unsigned)sizeof(P));
+    else v[k0 * TY] = P;
 }
 
-// One tile of the lean one-read step: columns [x0, x0+64) x [y0, y0+TY),
-// planes [za, zb); blockDim.x == 64 * TY.  W: the lattice has walls (an
-// all-periodic lattice carries none of their tests; the lanes next to an x
-// wall take their bounce-backs from a second, masked pull).
-template <typename S, int TY, int H, bool W, bool MV = false>
-__device__ __forceinline__ void lean_tile(const Geom& g, const S& st, const Coeffs<typename S::R>& cs,
-                                          typename S::R* __restrict__ ringb, typename S::R* __restrict__ xch,
-                                          Part2<typename S::R>* __restrict__ vs, int x0, int y0, int za, int zb,
+// One tile of the one-read step: columns [x0, x0+64) x [y0, y0+TY), planes
+// [za, zb); blockDim.x == 64 TY; source S, destination D (the same form, or
+// pair arrays into either).  W: the lattice has walls (an all-periodic lattice
+// carries none of their tests), MV: some may move.
+template <typename S, typename D, int TY, int H, bool W, bool MV>
+__device__ __forceinline__ void lean_tile(const Geom& g, const S& src, const D& dst, const Coeffs<typename S::R>& c,
+                                          unsigned char* __restrict__ lds, int x0, int y0, int za, int zb,
                                           const typename S::R* __restrict__ phi_in,
                                           Part2<typename S::R>* __restrict__ part_out,
                                           typename S::R* __restrict__ phi_out, int moving_next) {
+#pragma clang fp contract(off)
     using L = Lattice;
     using R = typename S::R;
-    constexpr int TX = kTX;
-    constexpr int LX = TX + 2 * H;
-    constexpr int NP = 2 * H + 1;
-    constexpr int LY = TY + 2 * H;
-    constexpr int PLANE = LY * LX;
-    constexpr int XROW = 2 * kXchDirs * kLeanRowPad;  // exchange reals per tile row
-    const unsigned N = (unsigned)g.N;  // byte offsets within a resource < 2^32 (checked on the host)
-    // the collision's real coefficients in vector registers: the loop holds
-    // more wave-uniform values than the scalar register file, and a VALU
-    // operation reads a vector register at no cost (the flags that steer
-    // control flow stay scalar)
-    Coeffs<R> c = cs;
-    in_vgpr(c.inv_nu_r);
-    in_vgpr(c.inv_nu_b);
-    in_vgpr(c.omega);
-    in_vgpr(c.half_A);
-    in_vgpr(c.beta);
-    in_vgpr(c.eps_g);
-    in_vgpr(c.eps_g2);
-    in_vgpr(c.g_iface);
-    in_vgpr(c.g_iface2);
-    in_vgpr(c.nc_strength);
-    in_vgpr(c.nc_hmin);
-    in_vgpr(c.fx);
-    in_vgpr(c.fy);
-    in_vgpr(c.fz);
+    using C = typename S::C;
+    using Lds = LeanLds<S, TY, H>;
+    constexpr int TX = kTileX, NT = TX * TY;
+    constexpr int LX = TX + 2 * H, LY = TY + 2 * H, NP = 2 * H + 1, PLANE = LY * LX;
+    constexpr int NC = S::NC, NCA = NC > 0 ? NC : 1;
+    R* const ring = reinterpret_cast<R*>(lds);
+    const RecPlanes<C, NCA, TY> rp{reinterpret_cast<C*>(lds + Lds::phi)};
+    R* const xch = reinterpret_cast<R*>(lds + Lds::phi + Lds::rec);
+    Part2<R>* const vs = reinterpret_cast<Part2<R>*>(lds + Lds::phi + Lds::rec + Lds::xch);
+
     const int lane = threadIdx.x & 63;
     const int ty = wave_uniform(threadIdx.x >> 6);
-    const int x = x0 + lane;
-    const int y = y0 + ty;
+    const int x = x0 + lane, y = y0 + ty;
     const int x1 = min(x0 + TX, g.nx), y1 = min(y0 + TY, g.ny);
     const int nrows = y1 - y0;
-    const bool xin = x < g.nx;
-    const bool row_in = y < g.ny;
+    const bool xin = x < g.nx, row_in = y < g.ny, site_in = xin && row_in;
     const bool ragged = x1 - x0 < TX;
-    // clamped coordinates: lanes and rows beyond the lattice compute on a
-    // valid site and store nothing
-    const int xc = xin ? x : g.nx - 1;
-    const int yc = row_in ? y : g.ny - 1;
-    // per-lane column offsets of the pulls: x, x - 1 and x + 1 with the wrap
-    // (beyond an x wall the lane's own column; its bounce-back is re-pulled)
-    const unsigned cx0 = (unsigned)xc;
+    // clamped coordinates: lanes and rows beyond the lattice compute on a valid
+    // site and store nothing
+    const int xc = xin ? x : g.nx - 1, yc = row_in ? y : g.ny - 1;
     const bool WX = W && g.wx;
-    const unsigned cxm = (unsigned)(xc == 0 ? (WX ? 0 : g.nx - 1) : xc - 1);
-    const unsigned cxp = (unsigned)(xc == g.nx - 1 ? (WX ? xc : 0) : xc + 1);
-    const bool wall_xlo = WX && xc == 0, wall_xhi = WX && xc == g.nx - 1;
-    const LeanLane ln{cx0, cxm, cxp, wall_xlo, wall_xhi, lane, ty};
-    // phase-ring columns of this lane: x0 - H + lane and x0 - H + 64 + lane
-    const int ra = halo_coord(x0 - H + lane, g.nx, g.wx);
-    const int rb = halo_coord(x0 - H + TX + lane, g.nx, g.wx);
-    // edge lanes of the row and the columns their x-face sums go to
-    Part2<R>* const xf = part_out + g.N;
-    int bd_lo = 0, bd_hi = 0;
-    const bool edge_lo = row_in && lane == 0 && xface_dest<TX>(g, x0, x1, -1, bd_lo);
-    const bool edge_hi = row_in && x == x1 - 1 && xface_dest<TX>(g, x0, x1, 1, bd_hi);
-    // zero pads of this row's exchange slots
-    R* const xrow = xch + ty * XROW;
-    if (lane < 2 * kXchDirs) {
-        xrow[lane * kLeanRowPad] = R(0);
-        xrow[lane * kLeanRowPad + kLeanRowPad - 1] = R(0);
-    }
-    R prev_dn = R(0), prev_rc = R(0), cur_dn = R(0), cur_rc = R(0);
-
-    // phase field of plane q on the tile and its halo, rows ty, ty + TY, ...:
-    // loaded into registers one plane ahead, so that the loads of plane p + 1
-    // are in flight while plane p is collided
-    constexpr int NR = (LY + TY - 1) / TY;
-    R pfa[NR], pfb[NR];
-    auto fetch = [&](int q) {
-        const int zz = halo_coord(q, g.nz, g.wz);
-        const __amdgpu_buffer_rsrc_t pr = array_res(phi_in, N);
+    LeanLane ln;
+    ln.c0 = (unsigned)xc;
+    ln.cm = (unsigned)(xc == 0 ? (WX ? 0 : g.nx - 1) : xc - 1);
+    ln.cp = (unsigned)(xc == g.nx - 1 ? (WX ? xc : 0) : xc + 1);
+    ln.wx = WX;
+    ln.xlo = WX && xc == 0;
+    ln.xhi = WX && xc == g.nx - 1;
+    ln.lane = lane;
+    ln.ty = ty;
+    ln.x = xc;
+    const unsigned nxy = (unsigned)g.nxy;
+    const unsigned yr[3] = {(unsigned)(yc == 0 ? g.ny - 1 : yc - 1) * (unsigned)g.nx, (unsigned)(yc * g.nx),
+                            (unsigned)(yc == g.ny - 1 ? 0 : yc + 1) * (unsigned)g.nx};
+    const bool ylo = W && g.wy && yc == 0, yhi = W && g.wy && yc == g.ny - 1;
+    auto rows_of = [&](int z) {  // z in [0, nz)
+        LeanRows o;
+        const unsigned zr[3] = {(unsigned)(z == 0 ? g.nz - 1 : z - 1) * nxy, (unsigned)z * nxy,
+                                (unsigned)(z == g.nz - 1 ? 0 : z + 1) * nxy};
 #pragma unroll
-        for (int k = 0; k < NR; ++k) {
-            const int r = ty + k * TY;
-            if (r < LY) {
-                const int yy = halo_coord(y0 - H + r, g.ny, g.wy);
-                const unsigned so = (unsigned)((zz * g.ny + yy) * g.nx) * (unsigned)sizeof(R);
-                pfa[k] = res_load(R(0), pr, (unsigned)ra * (unsigned)sizeof(R), so);
-                pfb[k] = lane < 2 * H ? res_load(R(0), pr, (unsigned)rb * (unsigned)sizeof(R), so) : R(0);
+        for (int a = 0; a < 3; ++a)
+#pragma unroll
+            for (int b = 0; b < 3; ++b) o.r[a][b] = zr[a] + yr[b];
+        o.ylo = ylo;
+        o.yhi = yhi;
+        o.zlo = W && g.wz && z == 0;
+        o.zhi = W && g.wz && z == g.nz - 1;
+        return o;
+    };
+
+    // ---- staging of the rings: every thread loads its own site's entry and its
+    // share of the halo entries around the tile
+    constexpr int PE = LY * LX - TX * TY, NE = (PE + NT - 1) / NT;  // phase halo
+    constexpr int RE = 2 * kRecRow + 2 * TY;                        // record halo, at most one per thread
+    static_assert(RE <= NT, "a tile's record halo exceeds its threads");
+    const unsigned main_at = (unsigned)(halo_coord(y0 + ty, g.ny, g.wy) * g.nx + halo_coord(x, g.nx, g.wx));
+    const int main_lds = (ty + H) * LX + lane + H;
+    unsigned pe_at[NE];
+    int pe_lds[NE];
+#pragma unroll
+    for (int k = 0; k < NE; ++k) {
+        const int e = min((int)threadIdx.x + k * NT, PE - 1);  // (surplus threads repeat the last entry)
+        int r, q;
+        if (e < 2 * H * LX) {
+            r = e / LX;
+            q = e - r * LX;
+            r = r < H ? r : TY + r;
+        } else {
+            const int e2 = e - 2 * H * LX;
+            r = H + e2 / (2 * H);
+            q = e2 % (2 * H);
+            q = q < H ? q : TX + q;
+        }
+        pe_at[k] = (unsigned)(halo_coord(y0 - H + r, g.ny, g.wy) * g.nx + halo_coord(x0 - H + q, g.nx, g.wx));
+        pe_lds[k] = r * LX + q;
+    }
+    unsigned re_at = 0;
+    int re_lds = 0;
+    const bool re_on = NC > 0 && (int)threadIdx.x < RE;
+    if (NC > 0) {
+        const int e = min((int)threadIdx.x, RE - 1);
+        int r, q;
+        if (e < 2 * kRecRow) {
+            r = e < kRecRow ? 0 : TY + 1;
+            q = e < kRecRow ? e : e - kRecRow;
+        } else {
+            const int e2 = e - 2 * kRecRow;
+            r = 1 + (e2 >> 1);
+            q = (e2 & 1) ? TX + 1 : 0;
+        }
+        re_at = (unsigned)(halo_coord(y0 - 1 + r, g.ny, g.wy) * g.nx + halo_coord(x0 - 1 + q, g.nx, g.wx));
+        re_lds = r * kRecRow + q;
+    }
+    const int rmain_lds = (ty + 1) * kRecRow + lane + 1;
+    struct Stage {
+        R m, e[NE];
+        C rm[NCA], re[NCA];
+    };
+    auto load_phi = [&](int q, Stage& s) {
+        const unsigned so = (unsigned)halo_plane(q, g.nz, g.wz) * nxy * (unsigned)sizeof(R);
+        const __amdgpu_buffer_rsrc_t rphi = array_res(phi_in);
+        s.m = res_load(R(0), rphi, main_at * (unsigned)sizeof(R), so);
+#pragma unroll
+        for (int k = 0; k < NE; ++k) s.e[k] = res_load(R(0), rphi, pe_at[k] * (unsigned)sizeof(R), so);
+    };
+    auto put_phi = [&](int slot, const Stage& s) {
+        R* p = ring + slot * PLANE;
+        p[main_lds] = s.m;
+#pragma unroll
+        for (int k = 0; k < NE; ++k) p[pe_lds[k]] = s.e[k];
+    };
+    auto load_rec = [&](int q, Stage& s) {
+        if constexpr (NC > 0) {
+            constexpr unsigned RB = 16u * NC;
+            const __amdgpu_buffer_rsrc_t rr = src.rec_res();
+            const unsigned so = (unsigned)halo_plane(q, g.nz, g.wz) * nxy * RB;
+#pragma unroll
+            for (int k = 0; k < NC; ++k) s.rm[k] = res_load_chunk<C>(rr, main_at * RB + 16u * k, so);
+            if (re_on) {
+#pragma unroll
+                for (int k = 0; k < NC; ++k) s.re[k] = res_load_chunk<C>(rr, re_at * RB + 16u * k, so);
             }
         }
     };
-    fetch(za - H);
-    // Values loaded one plane ahead (records to stage, deviations to pull)
-    // are loaded in every iteration, at the same point, for a plane clamped
-    // into the lattice: a value the loop carries then has a single source,
-    // and no register copy at the loop head has to wait for its load.  The
-    // loads of planes nothing uses are in bounds and few.
-    typename S::Pre pre;
-    st.stage_load(g, za - 2 * H + 1, x0, y0, ty, lane, pre);
-
-    for (int p = za - H; p < zb + H; ++p) {
-        const int slot = (p - (za - H)) % NP;
-        // ---- phase field of plane p into its ring slot
-        {
-            R* dstp = ringb + slot * PLANE;
+    auto put_rec = [&](int slot, const Stage& s) {
+        if constexpr (NC > 0) {
 #pragma unroll
-            for (int k = 0; k < NR; ++k) {
-                const int r = ty + k * TY;
-                if (r < LY) {
-                    dstp[r * LX + lane] = pfa[k];
-                    if (lane < 2 * H) dstp[r * LX + TX + lane] = pfb[k];
+            for (int k = 0; k < NC; ++k) rp.at(slot, k, rmain_lds) = s.rm[k];
+            if (re_on) {
+#pragma unroll
+                for (int k = 0; k < NC; ++k) rp.at(slot, k, re_lds) = s.re[k];
+            }
+        }
+    };
+
+    // edge lanes of the row and the columns their x-face sums go to
+    int bd_lo = 0, bd_hi = 0;
+    const bool edge_lo = row_in && lane == 0 && xface_dest<TX>(g, x0, x1, -1, bd_lo);
+    const bool edge_hi = row_in && x == x1 - 1 && xface_dest<TX>(g, x0, x1, 1, bd_hi);
+    // a site on an x or y face of the box keeps its own sums for the assembly
+    const bool face_xy = lane == 0 || lane == TX - 1 || x == g.nx - 1 || ty == 0 || ty == TY - 1 || y == g.ny - 1;
+
+    // ---- prologue: the planes below the first one, all in flight together
+    Stage st;
+    typename S::Pre pre;
+    {
+        Stage s[2 * H];
+#pragma unroll
+        for (int k = 0; k < 2 * H; ++k) load_phi(za - H + k, s[k]);
+        load_rec(za - 1, s[0]);
+        load_rec(za, s[1]);
+        load_phi(za + H, st);
+        load_rec(za + 1, st);
+        LeanRows rw = rows_of(za);
+        src.template fetch<W>(g, rw, ln, pre);
+#pragma unroll
+        for (int k = 0; k < 2 * H; ++k) put_phi(k, s[k]);
+        put_rec(0, s[0]);
+        put_rec(1, s[1]);
+    }
+    R prev_dn = R(0), prev_rc = R(0), cur_dn = R(0), cur_rc = R(0);
+    int s0 = H;  // ring slot of plane cz
+    int k0 = 0;  // (cz - za) mod 3: x-face sums; record slots of cz - 1, cz, cz + 1 are k0, k0 + 1, k0 + 2
+
+    for (int cz = za; cz < zb; ++cz) {
+        const int r1 = k0 == 2 ? 0 : k0 + 1, r2 = k0 == 0 ? 2 : k0 - 1;
+        {
+            int sh = s0 + H;
+            sh = sh >= NP ? sh - NP : sh;
+            put_phi(sh, st);
+            put_rec(r2, st);
+        }
+        __syncthreads();
+        // ---- pull (x, y, cz), then load what the next plane needs: always, at
+        // the same point and for a plane clamped into the lattice, so that a
+        // value the loop carries has one source and nothing at the loop head
+        // waits for its load
+        const LeanRows rw = rows_of(cz);
+        const unsigned own = rw.own();
+        R t[Q], d[Q];
+        src.template values<W, TY>(g, rw, ln, rp, k0, r1, r2, pre, t, d);
+        if constexpr (W && MV) {
+            // off a moving wall each reflected direction gains the wall term,
+            // shared between the components by the site's own phase
+            const bool wyz = rw.ylo || rw.yhi || rw.zlo || rw.zhi;
+            if (g.moving && (wyz || ln.xlo || ln.xhi)) {
+                const R ph = src.template own_phase<TY>(g, own, ln, rp, r1);
+#pragma unroll
+                for (int i = 1; i < Q; ++i) {
+                    if (!(rw.beyond(i) || ln.beyond(i))) continue;
+                    const R add = wall_term<R>(g, i, ln.x, yc, cz);
+                    t[i] += add;
+                    d[i] = fma_of(add, ph, d[i]);
                 }
             }
         }
-        if constexpr (S::split) {
-            // records of plane p - H + 1, the cz + 1 of the plane collided below
-            const int qr = p - H + 1;
-            if (qr >= za - 1 && qr <= zb) st.stage_store((qr - (za - 1)) % 3, ty, lane, pre);
+        SiteSums<R> m;
+#pragma unroll
+        for (int i = 0; i < Q; ++i) m.add(i, t[i], weight<R>(i) + t[i], d[i]);
+        {
+            const int zn = min(cz + 1, g.nz - 1);
+            load_phi(cz + 1 + H, st);
+            load_rec(cz + 2, st);
+            const LeanRows rn = rows_of(zn);
+            src.template fetch<W>(g, rn, ln, pre);
         }
-        __syncthreads();
-        fetch(p + 1);
-        st.stage_load(g, p - H + 2, x0, y0, ty, lane, pre);
-        const int cz = p - H;
-        if (cz < za) {
-            // deviations of plane cz + 1 (the first collided plane's in the
-            // last such iteration)
-            st.template dev_load<W>(g, yc, max(cz + 1, 0), ln, pre);
-            continue;  // uniform over the workgroup
-        }
-        const int s0 = (cz - (za - H)) % NP;
-        const int sm = (s0 + NP - 1) % NP, sp = (s0 + 1) % NP;
-        // N re-read each plane: the array offsets a N then stay scalar
-        // arithmetic inside the loop instead of loop-invariant scalar
-        // registers (which spill)
-        unsigned Np = N;
-        asm volatile("" : "+s"(Np));
-        LeanPlane P;
-        P.Np = Np;
-        P.own_row = (unsigned)((cz * g.ny + yc) * g.nx);
-        P.yc = yc;
-        P.cz = cz;
-        P.rs[0] = (cz - 1 - (za - 1)) % 3;
-        P.rs[1] = (cz - (za - 1)) % 3;
-        P.rs[2] = (cz + 1 - (za - 1)) % 3;
-        // ---- pull (x, y, cz)
-        R t[Q], d[Q];
-        st.template pull<W, MV>(g, P, ln, pre, t, d);
-        st.template dev_load<W>(g, yc, min(cz + 1, g.nz - 1), ln, pre);
-        // ---- colour gradient from the ring: base at (ty + H - 1, lane + H - 1)
+        // ---- colour gradient and near contact from the ring
+        const int sm = s0 == 0 ? NP - 1 : s0 - 1, sp = s0 == NP - 1 ? 0 : s0 + 1;
         R gx, gy, gz;
         {
             const int b = (ty + H - 1) * LX + lane + H - 1;
-            const R* pm = ringb + sm * PLANE + b;
-            const R* p0 = ringb + s0 * PLANE + b;
-            const R* pp = ringb + sp * PLANE + b;
-            R ax = R(0), ay = R(0), az = R(0);
-#pragma unroll
-            for (int i = 1; i < Q; ++i) {
-                const R* pl = L::cz[i] < 0 ? pm : (L::cz[i] > 0 ? pp : p0);
-                const R v = weight<R>(i) * pl[(1 + L::cy[i]) * LX + 1 + L::cx[i]];
-                if (L::cx[i]) ax += L::cx[i] > 0 ? v : -v;
-                if (L::cy[i]) ay += L::cy[i] > 0 ? v : -v;
-                if (L::cz[i]) az += L::cz[i] > 0 ? v : -v;
-            }
-            gx = R(3) * ax;
-            gy = R(3) * ay;
-            gz = R(3) * az;
+            const R* pm = ring + sm * PLANE + b;
+            const R* p0 = ring + s0 * PLANE + b;
+            const R* pp = ring + sp * PLANE + b;
+            stencil_gradient<R>(
+                [&](int i) {
+                    const R* pl = L::cz[i] < 0 ? pm : (L::cz[i] > 0 ? pp : p0);
+                    return pl[(1 + L::cy[i]) * LX + 1 + L::cx[i]];
+                },
+                gx, gy, gz);
         }
         R Fx = c.fx, Fy = c.fy, Fz = c.fz;
         if (H > 1 && c.nc_range > 0) {
-            PhiRing<R, TX, H> ring{ringb, LY};
-            ring_near_contact<R, TX, H>(g, ring, s0, xc, yc, cz, ty + H, lane + H, gx, gy, gz, c, Fx, Fy, Fz);
+            const PhiRing<R, TX, H> pr{ring, LY};
+            ring_near_contact<R, TX, H>(g, pr, s0, xc, yc, cz, ty + H, lane + H, gx, gy, gz, c, Fx, Fy, Fz);
         }
         SiteTotals<R> tot;
-        collide<R, S::split>(t, d, gx, gy, gz, Fx, Fy, Fz, c, &tot);
-        // ---- store (x, y, cz) and keep the values a later pull reads
-        st.store(g, P, ln, t, d, tot, row_in && xin);
+        collide_totals<R>(t, m, gx, gy, gz, Fx, Fy, Fz, c, tot);
+        typename D::Kept kept;
+        dst.store(g, own, ln, t, tot, site_in, kept);
         if (ragged) {
             // lanes beyond the lattice hand nothing to their neighbours
             if (!xin) {
 #pragma unroll
-                for (int i = 0; i < Q; ++i) {
-                    t[i] = -weight<R>(i);
-                    d[i] = R(0);
-                }
+                for (int i = 0; i < Q; ++i) t[i] = -weight<R>(i);
+                D::clear(kept);
             }
         }
-        // bounce-backs into this site: its own values, before the in-plane
-        // group (off a moving wall, as the next pull reads them: plus the wall
-        // term, shared by the site's own post-collision phase)
-        {
-            const bool ylo = W && g.wy && yc == 0, yhi = W && g.wy && yc == g.ny - 1;
-            const bool zlo = W && g.wz && cz == 0, zhi = W && g.wz && cz == g.nz - 1;
+        // ---- phase sums of the next state.  val(i): what direction i carries
+        auto val = [&](int i) {
+            const R a = weight<R>(i) + t[i];
+            return Part2<R>{dst.kept_diff(i, a, kept), a};
+        };
+        auto add = [](Part2<R>& p, const Part2<R>& q) {
+            p.dn += q.dn;
+            p.rc += q.rc;
+        };
+        // sum over the columns of what this row sends in (c_y, c_z) = (e, f):
+        // c_x = 0, then from the left, then from the right
+        auto row_sum = [&](int e, int f) {
+            Part2<R> p = val(dir_of(0, e, f));
+            if (e == 0 || f == 0) {
+                const Part2<R> l = val(dir_of(1, e, f)), r = val(dir_of(-1, e, f));
+                add(p, Part2<R>{from_left(l.dn), from_left(l.rc)});
+                add(p, Part2<R>{from_right(r.dn), from_right(r.rc)});
+            }
+            return p;
+        };
+        // bounce-backs into this site: its own values, before the in-plane group
+        // (off a moving wall, as the next pull reads them)
+        if constexpr (W) {
             R ph = R(0);
             bool mv = false;
-            if constexpr (W && MV) {
-                mv = moving_next && (ylo || yhi || zlo || zhi || wall_xlo || wall_xhi);
-                if (mv) {
-                    if constexpr (S::split) {
-                        ph = tot.phi;  // the phase the site's record holds
-                    } else {
-                        R st = R(0), sd = R(0);
-                        for (int j = 0; j < Q; ++j) {
-                            st += weight<R>(j) + t[j];
-                            sd += d[j];
-                        }
-                        ph = sd / st;
-                    }
-                }
+            if constexpr (MV) {
+                mv = moving_next && (rw.ylo || rw.yhi || rw.zlo || rw.zhi || ln.xlo || ln.xhi);
+                if (mv) ph = dst.kept_phase(t, kept);
             }
 #pragma unroll
             for (int i = 1; i < Q; ++i) {
-                const bool ryz = (L::cy[i] > 0 && ylo) || (L::cy[i] < 0 && yhi) || (L::cz[i] > 0 && zlo) ||
-                                 (L::cz[i] < 0 && zhi);
-                if constexpr (W) {
-                    const bool rx = (L::cx[i] > 0 && wall_xlo) || (L::cx[i] < 0 && wall_xhi);
-                    if (ryz || rx) {
-                        R tv = t[L::opp[i]], dv = d[L::opp[i]];
-                        if (mv) {
-                            const R add = wall_term<R>(g, i, xc, yc, cz);
-                            tv += add;
-                            dv += add * ph;
+                if (!(rw.beyond(i) || ln.beyond(i))) continue;
+                const R tv = t[L::opp[i]];
+                R dv = dst.kept_diff(L::opp[i], weight<R>(i) + tv, kept);
+                R wa = weight<R>(i) + tv;
+                if (mv) {
+                    const R ad = wall_term<R>(g, i, xc, yc, cz);
+                    wa = weight<R>(i) + (tv + ad);
+                    dv = fma_of(ad, ph, dv);
+                }
+                cur_rc += wa;
+                cur_dn += dv;
+            }
+        }
+        if (edge_lo) xedge_own<-1, R, TY>(g, val, vs, ty, y, cz, k0, za, zb, bd_lo, array_res(part_out + g.N));
+        if (edge_hi) xedge_own<1, R, TY>(g, val, vs, ty, y, cz, k0, za, zb, bd_hi, array_res(part_out + g.N));
+        // by destination plane cz - 1, cz, cz + 1 (c_z + 1): the running sum, then
+        // this row's terms, those of the row below (c_y = 1) and of the row above
+        Part2<R> sum[3] = {{prev_dn, prev_rc}, {cur_dn, cur_rc}, {R(0), R(0)}};
+#pragma unroll
+        for (int f = -1; f <= 1; ++f) add(sum[f + 1], row_sum(0, f));
+        Part2<R> up_lo{}, dn_lo{}, up_hi{}, dn_hi{};
+        const int xe = x1 - x0;  // column just beyond the tile
+#pragma unroll
+        for (int round = 0; round < Lds::rounds; ++round) {
+            if (round) __syncthreads();
+            constexpr int STEP = Lds::rounds == 1 ? 2 : 1;
+            R* const mine = xch + ty * (STEP * kXchSlots * kXchRow);
+#pragma unroll
+            for (int e = 1; e >= -1; e -= 2)
+#pragma unroll
+                for (int f = -1; f <= 1; ++f) {
+                    const Part2<R> p = row_sum(e, f);
+                    R* o = mine + xch_slot(e, f) * kXchRow + 1 + lane;
+                    if (STEP == 2 || round == 0) o[0] = p.rc;
+                    if (STEP == 2) o[kXchSlots * kXchRow] = p.dn;
+                    else if (round == 1) o[0] = p.dn;
+                    if (f == 0) {
+                        // terms that leave a full row through its ends
+                        if (lane == 0 || lane == TX - 1) {
+                            const Part2<R> l = val(dir_of(-1, e, 0)), r = val(dir_of(1, e, 0));
+                            R* q = mine + xch_slot(e, 0) * kXchRow + (lane == 0 ? 0 : TX + 1);
+                            const R vr = lane == 0 ? l.rc : r.rc, vd = lane == 0 ? l.dn : r.dn;
+                            if (STEP == 2 || round == 0) q[0] = vr;
+                            if (STEP == 2) q[kXchSlots * kXchRow] = vd;
+                            else if (round == 1) q[0] = vd;
                         }
-                        cur_rc += weight<R>(i) + tv;
-                        cur_dn += dv;
-                    }
-                } else {
-                    if (ryz) {
-                        cur_rc += weight<R>(i) + t[L::opp[i]];
-                        cur_dn += d[L::opp[i]];
                     }
                 }
-            }
-        }
-        // ---- hand the stored values of the directions with c_y != 0 to the
-        // rows they stream to (LDS), w_i + t_i and d_i
+            __syncthreads();
 #pragma unroll
-        for (int i = 0; i < Q; ++i) {
-            if (L::cy[i] == 0) continue;
-            xrow[(2 * xch_slot(i)) * kLeanRowPad + 1 + lane] = weight<R>(i) + t[i];
-            xrow[(2 * xch_slot(i) + 1) * kLeanRowPad + 1 + lane] = d[i];
-        }
-        if (edge_lo) xedge_own<R, TY, -1>(g, t, d, vs, ty, y, cz, za, zb, bd_lo, xf);
-        if (edge_hi) xedge_own<R, TY, 1>(g, t, d, vs, ty, y, cz, za, zb, bd_hi, xf);
-        __syncthreads();
-        if (edge_lo) lean_xedge_rows<R, TY, -1>(g, xch, vs, ty, lane, nrows, y, cz, za, zb, bd_lo, xf);
-        if (edge_hi) lean_xedge_rows<R, TY, 1>(g, xch, vs, ty, lane, nrows, y, cz, za, zb, bd_hi, xf);
-        // value of direction i from the source (x - cx, y - cy) in plane cz:
-        // 0 when the source is outside the tile or beyond a wall
-        auto from = [&](int i, R& va, R& vd) {
-            if (L::cy[i] != 0) {
-                // (a source row beyond a y wall is also outside the tile's rows)
-                const int ys = ty - L::cy[i];
-                if (ys < 0 || ys >= nrows) {
-                    va = R(0);
-                    vd = R(0);
-                    return;
+            for (int s = 0; s < 2; ++s) {
+                const int e = s == 0 ? 1 : -1, ys = ty - e;
+                if (ys < 0 || ys >= nrows) continue;  // (uniform; beyond the tile: another box's terms)
+                const R* in = xch + ys * (STEP * kXchSlots * kXchRow);
+#pragma unroll
+                for (int f = -1; f <= 1; ++f) {
+                    const R* o = in + xch_slot(e, f) * kXchRow + 1 + lane;
+                    if (STEP == 2 || round == 0) sum[f + 1].rc += o[0];
+                    if (STEP == 2) sum[f + 1].dn += o[kXchSlots * kXchRow];
+                    else if (round == 1) sum[f + 1].dn += o[0];
                 }
-                const R* src = xch + ys * XROW + lane + 1 - L::cx[i];
-                va = src[(2 * xch_slot(i)) * kLeanRowPad];
-                vd = src[(2 * xch_slot(i) + 1) * kLeanRowPad];
-            } else {
-                const R a = weight<R>(i) + t[i];
-                if (L::cx[i] > 0) {
-                    va = from_left(a);
-                    vd = from_left(d[i]);
-                } else if (L::cx[i] < 0) {
-                    va = from_right(a);
-                    vd = from_right(d[i]);
-                } else {
-                    va = a;
-                    vd = d[i];
+                if (edge_lo || edge_hi) {
+                    const R* o = in + xch_slot(e, 0) * kXchRow;
+                    Part2<R>& lo = s == 0 ? up_lo : dn_lo;
+                    Part2<R>& hi = s == 0 ? up_hi : dn_hi;
+                    if (STEP == 2 || round == 0) {
+                        lo.rc = o[0];
+                        hi.rc = o[1 + xe];
+                    }
+                    if (STEP == 2) {
+                        lo.dn = o[kXchSlots * kXchRow];
+                        hi.dn = o[kXchSlots * kXchRow + 1 + xe];
+                    } else if (round == 1) {
+                        lo.dn = o[0];
+                        hi.dn = o[1 + xe];
+                    }
                 }
             }
-        };
-        // a site on an x or y face of the box keeps its own sums for the assembly
-        const bool face_xy =
-            lane == 0 || lane == TX - 1 || x == g.nx - 1 || ty == 0 || ty == TY - 1 || y == g.ny - 1;
-        const bool site_in = row_in && xin;
-        // destination cz - 1: sources in plane cz are its last group
-        if (cz - 1 >= za) {
-#pragma unroll
-            for (int i = 0; i < Q; ++i) {
-                if (L::cz[i] != -1) continue;
-                R va, vd;
-                from(i, va, vd);
-                prev_rc += va;
-                prev_dn += vd;
-            }
-            if (site_in) {
-                const unsigned row = (unsigned)(((cz - 1) * g.ny + y) * g.nx);
-                if (cz - 1 == za || face_xy)
-                    res_store(Part2<R>{prev_dn, prev_rc}, array_res(part_out, N), (unsigned)x * sizeof(Part2<R>),
-                              row * (unsigned)sizeof(Part2<R>));
-                else
-                    res_store_cached(prev_dn / prev_rc, array_res(phi_out, N), (unsigned)x * sizeof(R),
-                                     row * (unsigned)sizeof(R));
-            }
         }
-        // destination cz: in-plane sources
-#pragma unroll
-        for (int i = 0; i < Q; ++i) {
-            if (L::cz[i] != 0) continue;
-            R va, vd;
-            from(i, va, vd);
-            cur_rc += va;
-            cur_dn += vd;
+        if (edge_lo) xedge_rows<-1, R, TY>(g, up_lo, dn_lo, vs, ty, y, cz, k0, zb, bd_lo, array_res(part_out + g.N));
+        if (edge_hi) xedge_rows<1, R, TY>(g, up_hi, dn_hi, vs, ty, y, cz, k0, zb, bd_hi, array_res(part_out + g.N));
+        // destination cz - 1 is complete: sources in plane cz are its last group
+        if (cz - 1 >= za && site_in) {
+            const unsigned row = (unsigned)(cz - 1) * nxy + (unsigned)(y * g.nx);
+            if (cz - 1 == za || face_xy)
+                res_store(sum[0], array_res(part_out), (unsigned)x * (unsigned)sizeof(Part2<R>), row * (unsigned)sizeof(Part2<R>));
+            else
+                res_store_cached(sum[0].dn / sum[0].rc, array_res(phi_out), (unsigned)x * (unsigned)sizeof(R),
+                                 row * (unsigned)sizeof(R));
         }
-        // destination cz + 1: sources in plane cz are its first group
-        R next_dn = R(0), next_rc = R(0);
-        if (cz + 1 < zb) {
-#pragma unroll
-            for (int i = 0; i < Q; ++i) {
-                if (L::cz[i] != 1) continue;
-                R va, vd;
-                from(i, va, vd);
-                next_rc += va;
-                next_dn += vd;
-            }
-        }
-        prev_dn = cur_dn;
-        prev_rc = cur_rc;
-        cur_dn = next_dn;
-        cur_rc = next_rc;
+        prev_dn = sum[1].dn;
+        prev_rc = sum[1].rc;
+        cur_dn = sum[2].dn;
+        cur_rc = sum[2].rc;
         // the chunk's last plane has no own sources above it
         if (cz == zb - 1 && site_in)
-            res_store(Part2<R>{prev_dn, prev_rc}, array_res(part_out, N), (unsigned)x * sizeof(Part2<R>),
-                      (unsigned)((cz * g.ny + y) * g.nx) * (unsigned)sizeof(Part2<R>));
-        // no barrier here: the next staging overwrites ring slots that only
-        // this plane's collide read, and every thread passed the barrier after
-        // that collide before it gathers; the exchange rows are next written
-        // after the next staging's barrier
+            res_store(sum[1], array_res(part_out), (unsigned)x * (unsigned)sizeof(Part2<R>), own * (unsigned)sizeof(Part2<R>));
+        // no barrier here: the next staging overwrites ring slots that only this
+        // plane's pull and collide read, before the exchange's barrier, and the
+        // exchange rows are next written after the next staging's barrier
+        s0 = sp;
+        k0 = r1;
     }
 }
 
-// LDS of a lean tile: phase-field ring, record ring (16-bit storage),
-// exchange rows, x-face running sums.
-template <typename S, int TY, int H>
-__host__ __device__ constexpr size_t lean_lds_bytes() {
-    using R = typename S::R;
-    return ((phi_ring_bytes<R, kTX, H>(TY) + 15) & ~size_t(15)) + S::ring_bytes(TY) + lean_xch_bytes<R, TY>() +
-           (size_t)2 * 3 * TY * sizeof(Part2<R>);
-}
-
-template <typename S, int TY, int H, bool W, bool MV>
-__global__ __launch_bounds__(kTX * TY) void lean_kernel(Geom g, S st, Coeffs<typename S::R> c, FusedShape fs,
-                                                       const Part2<typename S::R>* __restrict__ part_in,
-                                                       Part2<typename S::R>* __restrict__ part_out,
-                                                       int moving_next) {
+template <typename S, typename D, int TY, int H, bool W, bool MV>
+__global__ __launch_bounds__(kTileX * TY) void lean_kernel(Geom g, S src, D dst, Coeffs<typename S::R> c, FusedShape fs,
+                                                           const Part2<typename S::R>* __restrict__ part_in,
+                                                           Part2<typename S::R>* __restrict__ part_out,
+                                                           int moving_next) {
     using R = typename S::R;
     extern __shared__ unsigned char lds_raw[];
-    R* ringb = reinterpret_cast<R*>(lds_raw);
-    size_t off = (phi_ring_bytes<R, kTX, H>(TY) + 15) & ~size_t(15);
-    if constexpr (S::split) {
-        st.ring = reinterpret_cast<f4*>(lds_raw + off);
-        st.TY = TY;
-    }
-    off += S::ring_bytes(TY);
-    R* xch = reinterpret_cast<R*>(lds_raw + off);
-    Part2<R>* vs = reinterpret_cast<Part2<R>*>(lds_raw + off + lean_xch_bytes<R, TY>());
     int x0, y0, za, zb;
-    tile_of_block(fs, kTX, g.nz, x0, y0, za, zb);
-    lean_tile<S, TY, H, W, MV>(g, st, c, ringb, xch, vs, x0, y0, za, zb,
-                           phi_of<kTX>(const_cast<Part2<R>*>(part_in), g), part_out, phi_of<kTX>(part_out, g),
-                           moving_next);
+    tile_of_block(fs, kTileX, g.nz, x0, y0, za, zb);
+    lean_tile<S, D, TY, H, W, MV>(g, src, dst, c, lds_raw, x0, y0, za, zb,
+                                  phi_of<kTileX>(const_cast<Part2<R>*>(part_in), g), part_out,
+                                  phi_of<kTileX>(part_out, g), moving_next);
 }
 
 }  // namespace lbm

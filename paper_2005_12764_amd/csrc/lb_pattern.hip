@@ -1,8 +1,9 @@
 // lb_pattern.hip -- lb_pattern_ms: the memory access pattern of the FP32
 // one-read step with no arithmetic, timed on the device.  A measurement aid
 // for the step's roofline: the rate at which HBM serves exactly this pattern
-// (19 pair streams read at the pull's upstream sites and 19 written, on the
-// step's tiles, chunks, workgroup-to-XCD mapping, barriers and LDS budget)
+// (19 streams of totals read at the pull's upstream sites, the colour records of
+// the tile and one site around it, and both written, on the step's tiles,
+// chunks, workgroup-to-XCD mapping, look-ahead loads, barriers and LDS budget)
 // bounds what the collide-and-stream kernel can reach.
 #include <hip/hip_runtime.h>
 
@@ -26,30 +27,42 @@ __global__ __launch_bounds__(kTX * TY) void pattern_kernel(Geom g, const float* 
     const int x = x0 + lane, y = y0 + ty;
     const bool in = x < g.nx && y < g.ny;
     const int xc = min(x, g.nx - 1), yc = min(y, g.ny - 1);
-    const size_t S = raw_stride((size_t)g.N);
-    using P = typename RawPair<float>::type;
-    float acc = 0.f;
-    for (int z = za; z < zb; ++z) {
-        P v[Q];
+    const size_t S = raw_stride((size_t)g.N), T0 = pack_t_offset<float>((size_t)g.N);
+    float v[Q];
+    f4 r, e{};
+    auto load = [&](int z) {
 #pragma unroll
         for (int i = 0; i < Q; ++i) {
             const int xs = wrap(xc - L::cx[i], g.nx), ys = wrap(yc - L::cy[i], g.ny), zs = wrap(z - L::cz[i], g.nz);
-            v[i] = raw_pair(fin, (size_t)g.N, i, site_of(g, xs, ys, zs));
+            v[i] = fin[T0 + (size_t)i * S + site_of(g, xs, ys, zs)];
         }
-        __syncthreads();
-        // every store depends on every load, as after a collision (k = 0)
+        const int zr = wrap(z + 1, g.nz);
+        r = *reinterpret_cast<const f4*>(fin + 4 * (size_t)site_of(g, xc, yc, zr));
+        // the rows around the tile
+        if (ty < 2)
+            e = *reinterpret_cast<const f4*>(
+                fin + 4 * (size_t)site_of(g, xc, wrap(ty ? min(y0 + TY, g.ny) : y0 - 1, g.ny), zr));
+    };
+    load(za);
+    float acc = 0.f;
+    for (int z = za; z < zb; ++z) {
+        float w[Q];
 #pragma unroll
-        for (int i = 0; i < Q; ++i) acc = fmaf(v[i].x + v[i].y, k, acc);
+        for (int i = 0; i < Q; ++i) {
+            w[i] = v[i];
+            // every store depends on every load, as after a collision (k = 0)
+            acc = fmaf(v[i], k, acc);
+        }
+        const f4 c = {r.x + acc, r.y, r.z + e.x * k, r.w};
+        __syncthreads();
+        load(z + 1 < g.nz ? z + 1 : z);
+        __syncthreads();
         if (in) {
             const size_t s = (size_t)site_of(g, xc, yc, z);
+            __builtin_nontemporal_store(c, reinterpret_cast<f4*>(fout + 4 * s));
 #pragma unroll
-            for (int i = 0; i < Q; ++i) {
-                P w = v[i];
-                w.x += acc;
-                __builtin_nontemporal_store(w, reinterpret_cast<P*>(fout + 2 * ((size_t)i * S + s)));
-            }
+            for (int i = 0; i < Q; ++i) __builtin_nontemporal_store(w[i] + acc, fout + T0 + (size_t)i * S + s);
         }
-        __syncthreads();
     }
     if (k < -1e30f) lds_sink[threadIdx.x] = acc;  // never taken: the LDS allocation stays
 }
@@ -86,10 +99,10 @@ extern "C" int lb_pattern_ms(const lb_params* params, int32_t reps, double* ms) 
     if (params->bc[0] || params->bc[1] || params->bc[2]) return set_error(LB_EINVAL, "periodic lattices only");
     lb_params p = *params;
     p.storage = LB_STORE_F32;
-    const int TY = tile_rows(p, TILE_SINGLE);
+    const FusedShape fs = tile_shape(p, TILE_SINGLE);
+    const int TY = fs.TY;
     if (TY != kSingleTYSmall && TY != kSingleTY && TY != kSingleTYLarge)
         return set_error(LB_EINVAL, "the one-read step does not take this lattice");
-    const FusedShape fs = tile_shape(p, TILE_SINGLE);
     const Geom g = make_geom(p);
     const size_t lds = tile_lds(p, TILE_SINGLE, TY);
     const size_t bytes = pop_bytes(LB_STORE_F32, (size_t)g.N);

@@ -23,8 +23,10 @@
 //
 // Summation order is fixed, so results are reproducible: the own terms of a
 // site in four groups -- sources in plane z-1, bounce-backs from the site
-// itself, in-plane sources, sources in plane z+1 -- each in ascending
-// direction; then the foreign terms of the z and the y faces, each in
+// itself (ascending direction), in-plane sources, sources in plane z+1 -- the
+// groups of a plane by source row (the site's own, below, above), each row's
+// terms first summed over its columns (the site's own, left, right); then the
+// foreign terms of the z and the y faces, each in
 // ascending direction; then the x-face sums (lo face, then hi face), each
 // summed from zero in the group order of the own terms.  D and Rc are summed
 // term by term alike, so a pure component (d_i = +-(w_i + t_i)) gives
@@ -71,14 +73,34 @@ __device__ __forceinline__ bool on_face(const Geom& g, int x, int y, int z, int 
 
 // x-face sum of the site (x, y, z) on the lo (side 0, x = bx * TX) or hi
 // (side 1) x face of tile column bx, in the compact array after the own sums.
-__device__ __forceinline__ size_t xface_at(const Geom& g, int bx, int side, int y, int z) {
-    return ((size_t)(bx * 2 + side) * g.nz + z) * g.ny + y;
+__device__ __forceinline__ unsigned xface_at(const Geom& g, int bx, int side, int y, int z) {
+    return (unsigned)(((bx * 2 + side) * g.nz + z) * g.ny + y);
 }
 
-// Direction with velocity (cx, cy, cz).
+// Direction with velocity (cx, cy, cz), -1 if there is none (a switch, which
+// folds for constant arguments).
 __host__ __device__ constexpr int dir_of(int cx, int cy, int cz) {
-    for (int i = 0; i < Q; ++i)
-        if (Lattice::cx[i] == cx && Lattice::cy[i] == cy && Lattice::cz[i] == cz) return i;
+    switch ((cx + 1) + 3 * (cy + 1) + 9 * (cz + 1)) {
+        case 13: return 0;
+        case 14: return 1;
+        case 12: return 2;
+        case 16: return 3;
+        case 10: return 4;
+        case 22: return 5;
+        case 4: return 6;
+        case 17: return 7;
+        case 9: return 8;
+        case 11: return 9;
+        case 15: return 10;
+        case 23: return 11;
+        case 3: return 12;
+        case 5: return 13;
+        case 21: return 14;
+        case 25: return 15;
+        case 1: return 16;
+        case 7: return 17;
+        case 19: return 18;
+    }
     return -1;
 }
 
@@ -88,6 +110,8 @@ __host__ __device__ constexpr int dir_of(int cx, int cy, int cz) {
 constexpr int kSingleTY = 8;
 constexpr int kSingleTYSmall = 4;
 constexpr int kSingleTYLarge = 16;
+constexpr int kTileX = 64;             // columns of a tile: one wavefront per row
+constexpr size_t kLdsBytes = 163840;   // LDS of a workgroup on gfx950
 
 // Own box of a site: its tile column [x0, x1) x [y0, y1) and z chunk [z0, z1).
 struct OwnBox {
@@ -156,35 +180,55 @@ __global__ __launch_bounds__(256) void part_kernel(Geom g, Src src, int TZ, Part
     site_xyz(g, s, x, y, z);
     const OwnBox b = box_of<TX, TY>(g, TZ, x, y, z);
     R dn = R(0), rc = R(0);
+    // own terms from the row (y - e, z - f), summed over its columns
+    auto row_terms = [&](int e, int f) {
+        if (y - e < b.y0 || y - e >= b.y1 || z - f < b.z0 || z - f >= b.z1) return;
+        R rd = R(0), rr = R(0);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const int cx = k == 2 ? -1 : k, i = dir_of(cx, e, f);
+            if (i < 0) continue;
+            if (x - cx < b.x0 || x - cx >= b.x1) continue;
+            R t, d;
+            src.template pull_one<R>(i, site_of(g, x - cx, y - e, z - f), i, t, d);
+            rr += weight<R>(i) + t;
+            rd += d;
+        }
+        rc += rr;
+        dn += rd;
+    };
+    auto plane_terms = [&](int f) {
+        row_terms(0, f);
+        row_terms(1, f);
+        row_terms(-1, f);
+    };
+    plane_terms(1);
     R ph = R(0);  // own post-collision phase, for the moving-wall terms
     bool have_ph = false;
 #pragma unroll
-    for (int grp = 0; grp < 4; ++grp) {
-#pragma unroll
-        for (int i = 0; i < Q; ++i) {
-            int dir;
-            const int sr = pull_source(g, i, x, y, z, s, dir);
-            const bool refl = dir != i;
-            if (group_of(i, refl) != grp) continue;
-            if (!refl && !b.has(x - L::cx[i], y - L::cy[i], z - L::cz[i])) continue;
-            R t, d;
-            src.template pull_one<R>(i, sr, dir, t, d);
-            if constexpr (Src::moving) {
-                // a reflection off a moving wall, as the pull adds it
-                if (refl && g.moving) {
-                    if (!have_ph) {
-                        ph = src.template own_phase<R>(s);
-                        have_ph = true;
-                    }
-                    const R add = wall_term<R>(g, i, x, y, z);
-                    t += add;
-                    d += add * ph;
+    for (int i = 1; i < Q; ++i) {
+        int dir;
+        const int sr = pull_source(g, i, x, y, z, s, dir);
+        if (dir == i) continue;
+        R t, d;
+        src.template pull_one<R>(i, sr, dir, t, d);
+        if constexpr (Src::moving) {
+            // a reflection off a moving wall, as the pull adds it
+            if (g.moving) {
+                if (!have_ph) {
+                    ph = src.template own_phase<R>(s);
+                    have_ph = true;
                 }
+                const R add = wall_term<R>(g, i, x, y, z);
+                t += add;
+                d = fma_of(add, ph, d);
             }
-            rc += weight<R>(i) + t;
-            dn += d;
         }
+        rc += weight<R>(i) + t;
+        dn += d;
     }
+    plane_terms(0);
+    plane_terms(-1);
     if (on_face<TX, TY>(g, x, y, z, b.z0, b.z1)) part[s] = Part2<R>{dn, rc};
     else phi_of<TX>(part, g)[s] = dn / rc;
     // x-face sums of this site (beyond an x wall every term is a bounce-back)
@@ -342,25 +386,9 @@ __global__ __launch_bounds__(256) void assemble_kernel(Geom g, Src src, FaceSet 
     assemble_site<R, Src, TX, TY>(g, src, fs, part, blockIdx.x * blockDim.x + threadIdx.x);
 }
 
-// Exchange slot of a direction with c_y != 0 (the in-plane neighbours in
-// other rows go through LDS; rows are wavefronts, so c_y = 0 neighbours are
-// lane shuffles).
-__host__ __device__ constexpr int xch_slot(int i) {
-    return i == 3 ? 0 : i == 4 ? 1 : i == 7 ? 2 : i == 8 ? 3 : i == 9 ? 4 : i == 10 ? 5
-         : i == 15 ? 6 : i == 16 ? 7 : i == 17 ? 8 : i == 18 ? 9 : -1;
-}
-constexpr int kXchDirs = 10;
-
-template <typename R, int TX, int TY>
-__host__ __device__ constexpr size_t xch_bytes() {
-    return (size_t)2 * kXchDirs * TX * TY * sizeof(R);
-}
-// x-face sums an edge lane of a tile column accumulates for the face sites of
-// the neighbouring column: the lo edge lane (SX = -1) feeds the hi face of
-// the column on its left, the hi edge lane (SX = +1) the lo face of the one
-// on its right (periodic wrap; none beyond an x wall).  The running sums of
-// the destination planes z-1, z, z+1 of its row live in LDS, vs[side][plane
-// mod 3][row].
+// Column an edge lane's x-face sums go to: the lo edge lane (SX = -1) feeds the
+// hi face of the column on its left, the hi edge lane (SX = +1) the lo face of
+// the one on its right (periodic wrap; none beyond an x wall).
 template <int TX>
 __device__ __forceinline__ bool xface_dest(const Geom& g, int x0, int x1, int SX, int& bd) {
     if (SX < 0) {
@@ -377,256 +405,6 @@ __device__ __forceinline__ bool xface_dest(const Geom& g, int x0, int x1, int SX
     }
     bd = 0;
     return !g.wx;
-}
-
-// Before the exchange barrier: the lane's own terms of plane cz close the
-// sum of destination plane cz - 1 (stored), add the first in-plane term of
-// plane cz and open the sum of plane cz + 1.
-template <typename R, int TY, int SX>
-__device__ __forceinline__ void xedge_own(const Geom& g, const R (&t)[Q], const R (&d)[Q], Part2<R>* __restrict__ vs,
-                                          int ty, int y, int cz, int za, int zb, int bd, Part2<R>* __restrict__ xf) {
-    constexpr int im = dir_of(SX, 0, -1), i0 = dir_of(SX, 0, 0), ip = dir_of(SX, 0, 1);
-    constexpr int side = SX < 0 ? 0 : 1;
-    Part2<R>* v = vs + side * 3 * TY + ty;
-    if (cz - 1 >= za) {
-        Part2<R> P = v[((cz - 1 - za) % 3) * TY];
-        P.rc += weight<R>(im) + t[im];
-        P.dn += d[im];
-        xf[xface_at(g, bd, 1 - side, y, cz - 1)] = P;
-    }
-    Part2<R> P = cz == za ? Part2<R>{R(0), R(0)} : v[((cz - za) % 3) * TY];
-    P.rc += weight<R>(i0) + t[i0];
-    P.dn += d[i0];
-    v[((cz - za) % 3) * TY] = P;
-    if (cz + 1 < zb) v[((cz + 1 - za) % 3) * TY] = Part2<R>{R(0) + d[ip], R(0) + (weight<R>(ip) + t[ip])};
-}
-
-// After the exchange barrier: the in-plane terms from the rows above and
-// below (ascending direction); the chunk's last plane is then complete.
-template <typename R, int TX, int TY, int SX>
-__device__ __forceinline__ void xedge_rows(const Geom& g, const R* __restrict__ xch, Part2<R>* __restrict__ vs, int ty,
-                                           int tx, int nrows, int y, int cz, int za, int zb, int bd,
-                                           Part2<R>* __restrict__ xf) {
-    using L = Lattice;
-    constexpr int NT = TX * TY;
-    constexpr int side = SX < 0 ? 0 : 1;
-    Part2<R>* v = vs + side * 3 * TY + ty;
-    Part2<R> P = v[((cz - za) % 3) * TY];
-#pragma unroll
-    for (int i = 1; i < Q; ++i) {
-        if (L::cx[i] != SX || L::cz[i] != 0 || L::cy[i] == 0) continue;
-        const int ys = ty - L::cy[i];
-        if (ys < 0 || ys >= nrows) continue;
-        P.rc += xch[(2 * xch_slot(i)) * NT + ys * TX + tx];
-        P.dn += xch[(2 * xch_slot(i) + 1) * NT + ys * TX + tx];
-    }
-    if (cz == zb - 1) xf[xface_at(g, bd, 1 - side, y, cz)] = P;
-    else v[((cz - za) % 3) * TY] = P;
-}
-
-// One tile of the one-read step: columns [x0, x0+TX) x [y0, y0+TY), planes
-// [za, zb); blockDim.x == TX * TY and TX is the wavefront size.  Every thread
-// of the workgroup must call it (it holds barriers).
-template <typename R, typename Src, typename Dst, int TX, int TY, int H>
-__device__ __forceinline__ void single_tile(const Geom& g, const Src& src, const Dst& dst, const Coeffs<R>& c,
-                                            const PhiRing<R, TX, H>& ring, const RecRing<TX>& rr,
-                                            R* __restrict__ xch, Part2<R>* __restrict__ vs, int x0, int y0,
-                                            int za, int zb, const R* __restrict__ phi_in,
-                                            Part2<R>* __restrict__ part_out, R* __restrict__ phi_out) {
-    using L = Lattice;
-    constexpr int LX = TX + 2 * H;
-    constexpr int NP = 2 * H + 1;
-    constexpr int NT = TX * TY;
-    constexpr int LY = TY + 2 * H;
-    const int tid = threadIdx.x;
-    const int ty_ = tid / TX, tx_ = tid - (tid / TX) * TX;
-    const int x_ = x0 + tx_, y_ = y0 + ty_;
-    const bool active = x_ < g.nx && y_ < g.ny;
-    const int x1 = min(x0 + TX, g.nx), y1 = min(y0 + TY, g.ny);
-    // edge lanes and the columns their x-face sums go to
-    Part2<R>* const xf = part_out + g.N;
-    int bd_lo = 0, bd_hi = 0;
-    const bool edge_lo = active && tx_ == 0 && xface_dest<TX>(g, x0, x1, -1, bd_lo);
-    const bool edge_hi = active && x_ == x1 - 1 && xface_dest<TX>(g, x0, x1, 1, bd_hi);
-    // own sums of the destination planes cz - 1 (prev), cz (cur)
-    R prev_dn = R(0), prev_rc = R(0), cur_dn = R(0), cur_rc = R(0);
-
-    for (int p = za - H; p < zb + H; ++p) {
-        const int slot = (p - (za - H)) % NP;
-        // ---- phase field of plane p on the tile and its halo
-        {
-            R* dstp = ring.plane(slot);
-            const int zz = halo_coord(p, g.nz, g.wz);
-            for (int q = tid; q < LY * LX; q += NT) {
-                const int ly = q / LX, lx = q - ly * LX;
-                const int xx = halo_coord(x0 - H + lx, g.nx, g.wx);
-                const int yy = halo_coord(y0 - H + ly, g.ny, g.wy);
-                dstp[q] = phi_in[site_of(g, xx, yy, zz)];
-            }
-        }
-        if constexpr (Src::ring) {
-            const int qr = p - H + 1;
-            if (qr >= za - 1 && qr <= zb) load_rec_plane<Src, TX>(g, src, rr, (qr - za + 1) % 3, x0, y0, qr);
-        }
-        __syncthreads();
-        const int cz = p - H;
-        if (cz >= za) {
-            // ---- collide (x, y, cz)
-            R t[Q], d[Q];
-#pragma unroll
-            for (int i = 0; i < Q; ++i) t[i] = d[i] = R(0);
-            if (active) {
-                // the site's coordinates, re-read each plane: kept loop-invariant, the
-                // compiler hoists every stencil address out of the z loop and runs out
-                // of registers
-                int x = x_, y = y_, tx = tx_, ty = ty_;
-                asm volatile("" : "+v"(x), "+v"(y), "+v"(tx), "+v"(ty));
-                const int s0 = (cz - (za - H)) % NP;
-                const int sm = (s0 + NP - 1) % NP, sp = (s0 + 1) % NP;
-                const int s = site_of(g, x, y, cz);
-                if constexpr (Src::ring) {
-                    const f4* const planes[3] = {rr.plane((cz - za) % 3), rr.plane((cz - za + 1) % 3),
-                                                 rr.plane((cz - za + 2) % 3)};
-                    src.pull_ring(g, s, x, y, cz, t, d, planes, ty + 1, tx + 1, RecRing<TX>::LX, rr.half());
-                } else {
-                    src.pull(g, s, x, y, cz, t, d);
-                }
-                const int ly = ty + H, lx = tx + H;
-                R gx, gy, gz;
-                lds_gradient<R, TX, H>(ring, sm, s0, sp, ly, lx, gx, gy, gz);
-                R Fx = c.fx, Fy = c.fy, Fz = c.fz;
-                if (H > 1 && c.nc_range > 0)
-                    ring_near_contact<R, TX, H>(g, ring, s0, x, y, cz, ly, lx, gx, gy, gz, c, Fx, Fy, Fz);
-                SiteTotals<R> tot;
-                collide<R>(t, d, gx, gy, gz, Fx, Fy, Fz, c, &tot);
-                dst.store_as_read(s, t, d, tot);
-                // bounce-backs into this site: its own values, before the in-plane group
-                const WallFlags wf = wall_flags(g, x, y, cz);
-#pragma unroll
-                for (int i = 1; i < Q; ++i) {
-                    if (!reflected(i, wf)) continue;
-                    cur_rc += weight<R>(i) + t[L::opp[i]];
-                    cur_dn += d[L::opp[i]];
-                }
-            }
-            // ---- hand the stored values to the destinations of this plane's
-            // populations: other rows through LDS, the same row by shuffles
-            R sh_t[Q], sh_d[Q];
-#pragma unroll
-            for (int i = 0; i < Q; ++i) {
-                const R a = weight<R>(i) + t[i];
-                if (L::cy[i] != 0) {
-                    xch[(2 * xch_slot(i)) * NT + tid] = a;
-                    xch[(2 * xch_slot(i) + 1) * NT + tid] = d[i];
-                } else if (L::cx[i] > 0) {
-                    sh_t[i] = __shfl_up(a, 1, TX);
-                    sh_d[i] = __shfl_up(d[i], 1, TX);
-                } else if (L::cx[i] < 0) {
-                    sh_t[i] = __shfl_down(a, 1, TX);
-                    sh_d[i] = __shfl_down(d[i], 1, TX);
-                } else {
-                    sh_t[i] = a;
-                    sh_d[i] = d[i];
-                }
-            }
-            if (edge_lo) xedge_own<R, TY, -1>(g, t, d, vs, ty_, y_, cz, za, zb, bd_lo, xf);
-            if (edge_hi) xedge_own<R, TY, 1>(g, t, d, vs, ty_, y_, cz, za, zb, bd_hi, xf);
-            __syncthreads();
-            if (edge_lo) xedge_rows<R, TX, TY, -1>(g, xch, vs, ty_, tx_, y1 - y0, y_, cz, za, zb, bd_lo, xf);
-            if (edge_hi) xedge_rows<R, TX, TY, 1>(g, xch, vs, ty_, tx_, y1 - y0, y_, cz, za, zb, bd_hi, xf);
-            if (active) {
-                int x = x_, y = y_, tx = tx_, ty = ty_;
-                asm volatile("" : "+v"(x), "+v"(y), "+v"(tx), "+v"(ty));
-                // a site on an x or y face of the box keeps its own sums for the assembly
-                const bool face_xy =
-                    tx == 0 || tx == TX - 1 || x == g.nx - 1 || ty == 0 || ty == TY - 1 || y == g.ny - 1;
-                // value of direction i from the source (x - cx, y - cy) in plane cz
-                auto from = [&](int i, R& va, R& vd) {
-                    if (L::cy[i] != 0) {
-                        const int at = (ty - L::cy[i]) * TX + tx - L::cx[i];
-                        va = xch[(2 * xch_slot(i)) * NT + at];
-                        vd = xch[(2 * xch_slot(i) + 1) * NT + at];
-                    } else {
-                        va = sh_t[i];
-                        vd = sh_d[i];
-                    }
-                };
-                auto in_tile = [&](int i) {
-                    const int xs = x - L::cx[i], ys = y - L::cy[i];
-                    return xs >= x0 && xs < x1 && ys >= y0 && ys < y1;
-                };
-                // destination cz - 1: sources in plane cz are its last group
-                if (cz - 1 >= za) {
-                    const WallFlags wm = wall_flags(g, x, y, cz - 1);
-#pragma unroll
-                    for (int i = 0; i < Q; ++i) {
-                        if (L::cz[i] != -1) continue;
-                        if (reflected(i, wm) || !in_tile(i)) continue;
-                        R va, vd;
-                        from(i, va, vd);
-                        prev_rc += va;
-                        prev_dn += vd;
-                    }
-                    const int sm1 = site_of(g, x, y, cz - 1);
-                    if (cz - 1 == za || face_xy) part_out[sm1] = Part2<R>{prev_dn, prev_rc};
-                    else phi_out[sm1] = prev_dn / prev_rc;
-                }
-                // destination cz: in-plane sources
-                const WallFlags w0 = wall_flags(g, x, y, cz);
-#pragma unroll
-                for (int i = 0; i < Q; ++i) {
-                    if (L::cz[i] != 0) continue;
-                    if (reflected(i, w0) || !in_tile(i)) continue;
-                    R va, vd;
-                    from(i, va, vd);
-                    cur_rc += va;
-                    cur_dn += vd;
-                }
-                // destination cz + 1: sources in plane cz are its first group
-                R next_dn = R(0), next_rc = R(0);
-                if (cz + 1 < zb) {
-                    const WallFlags wp = wall_flags(g, x, y, cz + 1);
-#pragma unroll
-                    for (int i = 0; i < Q; ++i) {
-                        if (L::cz[i] != 1) continue;
-                        if (reflected(i, wp) || !in_tile(i)) continue;
-                        R va, vd;
-                        from(i, va, vd);
-                        next_rc += va;
-                        next_dn += vd;
-                    }
-                }
-                prev_dn = cur_dn;
-                prev_rc = cur_rc;
-                cur_dn = next_dn;
-                cur_rc = next_rc;
-                // the chunk's last plane has no own sources above it
-                if (cz == zb - 1) part_out[site_of(g, x, y, cz)] = Part2<R>{prev_dn, prev_rc};
-            }
-        }
-        // no barrier here: the next staging overwrites ring and record slots
-        // that only this plane's collide read, and every thread passed the
-        // barrier after that collide before it gathers; the exchange buffer is
-        // next written after the next staging's barrier
-    }
-}
-
-template <typename R, typename Src, typename Dst, int TX, int TY, int H>
-__global__ __launch_bounds__(TX * TY) void single_kernel(Geom g, Src src, Dst dst, Coeffs<R> c, FusedShape fs,
-                                                        const Part2<R>* __restrict__ part_in,
-                                                        Part2<R>* __restrict__ part_out) {
-    extern __shared__ unsigned char lds_raw[];
-    PhiRing<R, TX, H> ring{reinterpret_cast<R*>(lds_raw), TY + 2 * H};
-    size_t off = (phi_ring_bytes<R, TX, H>(TY) + 15) & ~size_t(15);
-    RecRing<TX> rr{reinterpret_cast<f4*>(lds_raw + off), TY + 2};
-    if constexpr (Src::ring) off += rec_ring_bytes<TX>(TY);
-    R* xch = reinterpret_cast<R*>(lds_raw + off);
-    Part2<R>* vs = reinterpret_cast<Part2<R>*>(lds_raw + off + xch_bytes<R, TX, TY>());
-    int x0, y0, za, zb;
-    tile_of_block(fs, TX, g.nz, x0, y0, za, zb);
-    single_tile<R, Src, Dst, TX, TY, H>(g, src, dst, c, ring, rr, xch, vs, x0, y0, za, zb,
-                                        phi_of<TX>(const_cast<Part2<R>*>(part_in), g), part_out,
-                                        phi_of<TX>(part_out, g));
 }
 
 }  // namespace lbm
