@@ -12,7 +12,7 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "liblb.so")
 
 SOURCES = ["lb_api.hip", "lb_launch.hip", "lb_lean.hip", "lb_lean64.hip", "lb_lean16.hip", "lb_lean_first.hip",
-           "lb_batch.hip", "lb_noalloc.hip", "lb_pattern.hip"]
+           "lb_pull.hip", "lb_batch.hip", "lb_noalloc.hip", "lb_pattern.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",

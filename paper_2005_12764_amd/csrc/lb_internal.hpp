@@ -97,6 +97,11 @@ int launch_lean_first(const LatticeView& v, const Coeffs<T>& c, const FusedShape
 size_t lean_tile_lds(const lb_params& p, int TY);
 // Pair arrays of the current packed state (a checkpoint's form) into f.
 int launch_unpack(const LatticeView& v, void* f);
+// Moments, export and totals of a packed or 16-bit state through marching tiles
+// (lb_pull.hip); taken = false: the state has another form, nothing was done.
+int pull_moments(const LatticeView& v, void* rr, void* rb, void* j, int dtype, bool& taken);
+int pull_export(const LatticeView& v, void* out, int dtype, bool& taken);
+int pull_totals(const LatticeView& v, Neu* partial, int& blocks, bool& taken);
 int launch_init(const LatticeView& v, const void* rr, const void* rb, const void* u, int dtype);
 int launch_import(const LatticeView& v, const void* f, int dtype);
 int launch_export(const LatticeView& v, void* out, int dtype);

@@ -625,17 +625,12 @@ __global__ __launch_bounds__(256) void export_kernel(Geom g, Src src, Out* __res
     }
 }
 
-// Moments rho_r, rho_b, j of the post-streaming state (any output may be null).
-template <typename R, typename Src, typename Out>
-__global__ __launch_bounds__(256) void moments_kernel(Geom g, Src src, Out* rr_out, Out* rb_out,
-                                                      Out* j_out) {
+// Moments rho_r, rho_b, j of site s from its pulled values (any output may be
+// null).
+template <typename R, typename Out>
+__device__ __forceinline__ void put_moments(const Geom& g, int s, const R (&t)[Q], const R (&d)[Q], Out* rr_out,
+                                            Out* rb_out, Out* j_out) {
     using L = Lattice;
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= g.N) return;
-    int x, y, z;
-    site_xyz(g, s, x, y, z);
-    R t[Q], d[Q];
-    src.pull(g, s, x, y, z, t, d);
     R st = R(0), sd = R(0), jx = R(0), jy = R(0), jz = R(0);
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
@@ -654,6 +649,17 @@ __global__ __launch_bounds__(256) void moments_kernel(Geom g, Src src, Out* rr_o
         j_out[N + s] = Out(jy);
         j_out[2 * N + s] = Out(jz);
     }
+}
+template <typename R, typename Src, typename Out>
+__global__ __launch_bounds__(256) void moments_kernel(Geom g, Src src, Out* rr_out, Out* rb_out,
+                                                      Out* j_out) {
+    const int s = blockIdx.x * blockDim.x + threadIdx.x;
+    if (s >= g.N) return;
+    int x, y, z;
+    site_xyz(g, s, x, y, z);
+    R t[Q], d[Q];
+    src.pull(g, s, x, y, z, t, d);
+    put_moments<R>(g, s, t, d, rr_out, rb_out, j_out);
 }
 
 // Initial densities from a droplet list: phi0 = max(background,
@@ -706,9 +712,9 @@ __device__ __forceinline__ void neu_merge(Neu& a, const Neu& b) {
     a.c += b.c;
 }
 
-// Block-level fixed-order reduction: wave shuffles, then the 4 wave results
+// Block-level fixed-order reduction: wave shuffles, then the wave results
 // through LDS in wave order.  Every thread must call it.
-__device__ __forceinline__ void block_reduce(Neu (&acc)[NTOT], Neu* lds /* [4][NTOT] */) {
+__device__ __forceinline__ void block_reduce(Neu (&acc)[NTOT], Neu* lds /* [waves][NTOT] */) {
 #pragma unroll
     for (int q = 0; q < NTOT; ++q) {
         for (int off = 32; off >= 1; off >>= 1) {
@@ -731,9 +737,34 @@ __device__ __forceinline__ void block_reduce(Neu (&acc)[NTOT], Neu* lds /* [4][N
     }
 }
 
+// One site's pulled values into the running totals.
+template <typename R>
+__device__ __forceinline__ void add_site_totals(const R (&t)[Q], const R (&d)[Q], Neu (&acc)[NTOT]) {
+    using L = Lattice;
+    double st = 0, sd = 0, jx = 0, jy = 0, jz = 0;
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+        st += double(t[i]);
+        sd += double(d[i]);
+        const double ti = double(t[i]);
+        if (L::cx[i]) jx += L::cx[i] > 0 ? ti : -ti;
+        if (L::cy[i]) jy += L::cy[i] > 0 ? ti : -ti;
+        if (L::cz[i]) jz += L::cz[i] > 0 ? ti : -ti;
+    }
+    const double rr = 0.5 * (1.0 + st + sd), rb = 0.5 * (1.0 + st - sd);
+    const double rho = rr + rb;
+    const bool bad = !(rho > 0.0) || !isfinite(rho) || !isfinite(jx) || !isfinite(jy) || !isfinite(jz);
+    neu_add(acc[0], rr);
+    neu_add(acc[1], rb);
+    neu_add(acc[2], jx);
+    neu_add(acc[3], jy);
+    neu_add(acc[4], jz);
+    neu_add(acc[5], bad ? 0.0 : 0.5 * (jx * jx + jy * jy + jz * jz) / rho);
+    neu_add(acc[6], bad ? 1.0 : 0.0);
+}
+
 template <typename R, typename Src>
 __global__ __launch_bounds__(256) void totals_kernel(Geom g, Src src, Neu* __restrict__ partial) {
-    using L = Lattice;
     __shared__ Neu lds[4 * NTOT];
     Neu acc[NTOT];
 #pragma unroll
@@ -743,27 +774,7 @@ __global__ __launch_bounds__(256) void totals_kernel(Geom g, Src src, Neu* __res
         site_xyz(g, s, x, y, z);
         R t[Q], d[Q];
         src.pull(g, s, x, y, z, t, d);
-        double st = 0, sd = 0, jx = 0, jy = 0, jz = 0;
-#pragma unroll
-        for (int i = 0; i < Q; ++i) {
-            st += double(t[i]);
-            sd += double(d[i]);
-            const double ti = double(t[i]);
-            if (L::cx[i]) jx += L::cx[i] > 0 ? ti : -ti;
-            if (L::cy[i]) jy += L::cy[i] > 0 ? ti : -ti;
-            if (L::cz[i]) jz += L::cz[i] > 0 ? ti : -ti;
-        }
-        const double rr = 0.5 * (1.0 + st + sd), rb = 0.5 * (1.0 + st - sd);
-        const double rho = rr + rb;
-        const bool bad = !(rho > 0.0) || !isfinite(rho) || !isfinite(jx) || !isfinite(jy) ||
-                         !isfinite(jz);
-        neu_add(acc[0], rr);
-        neu_add(acc[1], rb);
-        neu_add(acc[2], jx);
-        neu_add(acc[3], jy);
-        neu_add(acc[4], jz);
-        neu_add(acc[5], bad ? 0.0 : 0.5 * (jx * jx + jy * jy + jz * jz) / rho);
-        neu_add(acc[6], bad ? 1.0 : 0.0);
+        add_site_totals<R>(t, d, acc);
     }
     block_reduce(acc, lds);
     if (threadIdx.x == 0)

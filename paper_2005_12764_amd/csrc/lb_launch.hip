@@ -276,18 +276,23 @@ static bool single_rows_fit(const lb_params& p, int ty) {
 // Estimated microseconds of a one-read step with TY rows and chunks of TZ
 // planes: workgroups run in rounds of as many as the 256 CUs hold at once (LDS
 // and registers); a workgroup starts its rings (8 us with the launch) and then
-// takes a plane in a + b w with w wavefronts per SIMD (a: the latency of a plane
-// that nothing overlaps, b: the issue of one more row); the assembly takes 8 us
-// or 16 ns per thousand face sites.  Fitted to the times of 64^3 to 384^3 in
-// each storage (64^3 FP32, tile only: 41 us with 4 rows and 8 planes, 26 with 4
-// planes, 21 with 2; 256^3 FP32: 693 us with 8 rows and 128 planes, 740 with 64,
-// 701 with 4 rows and 32 planes; 384^3 bf16: 2.05 ms with 48 planes, 9 whole
-// rounds, 3.90 ms with 384, 1.1 rounds).
+// takes a plane in max(a + b w, f w) with w wavefronts per SIMD (a + b: the
+// latency of a row that nothing overlaps, f: the issue of one row); the assembly
+// takes 8 us or 16 ns per thousand face sites.  Fitted to the times of 64^3 to
+// 384^3 in each storage (64^3 FP32, tile only: 41 us with 4 rows and 8 planes, 26
+// with 4 planes, 21 with 2; 256^3 FP32: 693 us with 8 rows and 128 planes, 740
+// with 64, 701 with 4 rows and 32 planes, whose assembly takes 64 us more;
+// 512x128x64 with walls: 210 us with 8 rows and 32 planes, 387 with 64; 384^3
+// bf16: 2.05 ms with 48 planes, 9 whole rounds, 3.90 ms with 384, 1.1 rounds).
 static double single_cost(const lb_params& p, int TY, int TZ) {
     const int H = tile_halo(p);
-    const double a = p.storage == LB_STORE_F64 ? 1.0 : (split_storage(p) ? 2.6 : 2.2);
-    const double b = p.storage == LB_STORE_F64 ? 5.6 : (split_storage(p) ? 1.7 : 1.5);
-    const int waves = p.storage == LB_STORE_F32 ? 3 : (split_storage(p) || H == 1 ? 2 : 1);  // per SIMD, by registers
+    const bool f64 = p.storage == LB_STORE_F64, walls = p.bc[0] || p.bc[1] || p.bc[2];
+    double a = f64 ? 1.0 : (split_storage(p) ? 2.6 : 2.5), b = f64 ? 5.6 : (split_storage(p) ? 1.7 : 1.4);
+    double f = f64 ? 6.6 : (split_storage(p) ? 3.0 : 2.65);
+    // no probe without near contact; wall tests; 8 rows of FP64 spill
+    const double scale = (H == 1 ? 0.8 : 1.0) * (walls ? 1.2 : 1.0) * (f64 && H > 1 && TY > 4 ? 1.15 : 1.0);
+    // wavefronts a SIMD holds, by registers
+    const int waves = f64 ? (H == 1 ? 2 : 1) : (split_storage(p) || walls ? 2 : 3);
     const int per_simd = std::max(1, TY / 4);
     const int hold = std::max(1, std::min((int)(kLdsBytes / tile_lds(p, TILE_SINGLE, TY)), waves / per_simd));
     const double tiles = double((p.nx + kTX - 1) / kTX) * ((p.ny + TY - 1) / TY);
@@ -296,7 +301,8 @@ static double single_cost(const lb_params& p, int TY, int TZ) {
     const double resident = std::min<double>(hold, per_cu);
     // (rounds beyond the second start as CUs become free)
     const double rounds = per_cu <= 2 * hold ? std::ceil(per_cu / resident) : per_cu / resident;
-    const double tile = rounds * (8.0 + TZ * (a + b * per_simd * resident));
+    const double w = per_simd * resident;
+    const double tile = rounds * (8.0 + TZ * scale * std::max(a + b * w, f * w));
     auto faces = [](double n, int T) { return std::min(n, 2.0 * std::ceil(n / T)); };
     const double fx = faces(p.nx, kTX) / p.nx, fy = faces(p.ny, TY) / p.ny, fz = faces(p.nz, TZ) / p.nz;
     const double sites = double(p.nx) * p.ny * p.nz * (1.0 - (1.0 - fx) * (1.0 - fy) * (1.0 - fz));
@@ -473,6 +479,9 @@ int launch_import(const LatticeView& v, const void* f, int dtype) {
 }
 
 int launch_export(const LatticeView& v, void* out, int dtype) {
+    bool taken = false;
+    const int rc = pull_export(v, out, dtype, taken);
+    if (rc || taken) return rc;
     const unsigned grid = grid_for(v.g.N);
     return with_state(v, [&](auto rt, auto src, const auto&) {
         using R = decltype(rt);
@@ -486,6 +495,9 @@ int launch_export(const LatticeView& v, void* out, int dtype) {
 }
 
 int launch_moments(const LatticeView& v, void* rr, void* rb, void* j, int dtype) {
+    bool taken = false;
+    const int rc = pull_moments(v, rr, rb, j, dtype, taken);
+    if (rc || taken) return rc;
     const unsigned grid = grid_for(v.g.N);
     return with_state(v, [&](auto rt, auto src, const auto&) {
         using R = decltype(rt);
@@ -541,15 +553,17 @@ int launch_droplets(hipStream_t st, const Geom& g, const double* cen, const doub
 }
 
 int launch_totals(const LatticeView& v, Neu* partial, double* dtot) {
-    const unsigned grid = (unsigned)std::min<int>(kTotalsBlocks, (int)grid_for(v.g.N));
-    int rc = with_state(v, [&](auto rt, auto src, const auto&) {
+    int grid = std::min<int>(kTotalsBlocks, (int)grid_for(v.g.N));
+    bool taken = false;
+    int rc = pull_totals(v, partial, grid, taken);
+    if (!rc && !taken) rc = with_state(v, [&](auto rt, auto src, const auto&) {
         using R = decltype(rt);
         using S = decltype(src);
         hipLaunchKernelGGL((totals_kernel<R, S>), dim3(grid), dim3(kBlock), 0, v.stream, v.g, src, partial);
         return launch_status("totals_kernel");
     });
     if (rc) return rc;
-    hipLaunchKernelGGL(totals_final_kernel, dim3(1), dim3(kBlock), 0, v.stream, partial, (int)grid, dtot);
+    hipLaunchKernelGGL(totals_final_kernel, dim3(1), dim3(kBlock), 0, v.stream, partial, grid, dtot);
     return launch_status("totals_final_kernel");
 }
 

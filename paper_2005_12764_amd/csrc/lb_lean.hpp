@@ -172,6 +172,46 @@ struct LeanLane {
         return (Lattice::cx[i] > 0 && xlo) || (Lattice::cx[i] < 0 && xhi);
     }
 };
+// Clamped coordinates (xc, yc): lanes and rows beyond the lattice compute on a
+// valid site and store nothing.
+__device__ __forceinline__ LeanLane lean_lane(const Geom& g, bool walls, int xc, int lane, int ty) {
+    LeanLane o;
+    o.wx = walls && g.wx;
+    o.c0 = (unsigned)xc;
+    o.cm = (unsigned)(xc == 0 ? (o.wx ? 0 : g.nx - 1) : xc - 1);
+    o.cp = (unsigned)(xc == g.nx - 1 ? (o.wx ? xc : 0) : xc + 1);
+    o.xlo = o.wx && xc == 0;
+    o.xhi = o.wx && xc == g.nx - 1;
+    o.lane = lane;
+    o.ty = ty;
+    o.x = xc;
+    return o;
+}
+// The rows around row yc of any plane, from loop-invariant parts.
+template <bool W>
+struct LeanRowSet {
+    unsigned yr[3], nxy;
+    bool ylo, yhi, wz;
+    int nz;
+    __device__ __forceinline__ LeanRowSet(const Geom& g, int yc)
+        : yr{(unsigned)(yc == 0 ? g.ny - 1 : yc - 1) * (unsigned)g.nx, (unsigned)(yc * g.nx),
+             (unsigned)(yc == g.ny - 1 ? 0 : yc + 1) * (unsigned)g.nx},
+          nxy((unsigned)g.nxy), ylo(W && g.wy && yc == 0), yhi(W && g.wy && yc == g.ny - 1), wz(W && g.wz), nz(g.nz) {}
+    __device__ __forceinline__ LeanRows at(int z) const {  // z in [0, nz)
+        LeanRows o;
+        const unsigned zr[3] = {(unsigned)(z == 0 ? nz - 1 : z - 1) * nxy, (unsigned)z * nxy,
+                                (unsigned)(z == nz - 1 ? 0 : z + 1) * nxy};
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+#pragma unroll
+            for (int b = 0; b < 3; ++b) o.r[a][b] = zr[a] + yr[b];
+        o.ylo = ylo;
+        o.yhi = yhi;
+        o.zlo = wz && z == 0;
+        o.zhi = wz && z == nz - 1;
+        return o;
+    }
+};
 // Offsets of direction i's source value: site = row (scalar) + column (lane),
 // in array a.  Off a y or z wall the wavefront reads the opposite direction of
 // its own row; with x walls the lanes next to one do (W only).
@@ -214,9 +254,66 @@ struct RecPlanes {
     C* base;
     static constexpr int half = (TY + 2) * kRecRow;
     static constexpr int plane = NC * half;
-    static constexpr size_t bytes = (size_t)3 * plane * sizeof(C);
+    static constexpr size_t plane_bytes = (size_t)plane * sizeof(C);
     // piece k of ring entry e of slot s
     __device__ __forceinline__ C& at(int s, int k, int e) const { return base[s * plane + k * half + e]; }
+};
+
+// Staging of the record ring: every thread loads its own site's record of a
+// plane and, the first RE of them, one of the halo around the tile.
+template <typename S, int TY>
+struct RecStage {
+    using C = typename S::C;
+    static constexpr int NC = S::NC, NCA = NC > 0 ? NC : 1;
+    static constexpr int RE = 2 * kRecRow + 2 * TY;
+    static_assert(RE <= kTileX * TY, "a tile's record halo exceeds its threads");
+    using Planes = RecPlanes<C, NCA, TY>;
+    unsigned main_at, halo_at;  // sites within a plane
+    int main_lds, halo_lds;
+    bool halo_on;
+    struct Regs {
+        C m[NCA], h[NCA];
+    };
+    __device__ __forceinline__ RecStage(const Geom& g, int x0, int y0, int lane, int ty, unsigned own_at)
+        : main_at(own_at), halo_at(0), main_lds((ty + 1) * kRecRow + lane + 1), halo_lds(0),
+          halo_on(NC > 0 && (int)threadIdx.x < RE) {
+        if (NC == 0) return;
+        const int e = min((int)threadIdx.x, RE - 1);
+        int r, q;
+        if (e < 2 * kRecRow) {
+            r = e < kRecRow ? 0 : TY + 1;
+            q = e < kRecRow ? e : e - kRecRow;
+        } else {
+            const int e2 = e - 2 * kRecRow;
+            r = 1 + (e2 >> 1);
+            q = (e2 & 1) ? kTileX + 1 : 0;
+        }
+        halo_at = (unsigned)(halo_coord(y0 - 1 + r, g.ny, g.wy) * g.nx + halo_coord(x0 - 1 + q, g.nx, g.wx));
+        halo_lds = r * kRecRow + q;
+    }
+    __device__ __forceinline__ void load(const Geom& g, const S& src, int plane, Regs& s) const {
+        if constexpr (NC > 0) {
+            constexpr unsigned RB = 16u * NC;
+            const __amdgpu_buffer_rsrc_t rr = src.rec_res();
+            const unsigned so = (unsigned)halo_plane(plane, g.nz, g.wz) * (unsigned)g.nxy * RB;
+#pragma unroll
+            for (int k = 0; k < NC; ++k) s.m[k] = res_load_chunk<C>(rr, main_at * RB + 16u * k, so);
+            if (halo_on) {
+#pragma unroll
+                for (int k = 0; k < NC; ++k) s.h[k] = res_load_chunk<C>(rr, halo_at * RB + 16u * k, so);
+            }
+        }
+    }
+    __device__ __forceinline__ void put(const Planes& rp, int slot, const Regs& s) const {
+        if constexpr (NC > 0) {
+#pragma unroll
+            for (int k = 0; k < NC; ++k) rp.at(slot, k, main_lds) = s.m[k];
+            if (halo_on) {
+#pragma unroll
+                for (int k = 0; k < NC; ++k) rp.at(slot, k, halo_lds) = s.h[k];
+            }
+        }
+    }
 };
 
 // ------------------------------------------------------------- pair arrays
@@ -537,6 +634,27 @@ struct LeanSplit {
     __device__ __forceinline__ float kept_phase(const float (&)[Q], const Kept& k) const { return k.rb.x; }
 };
 
+// Off a moving wall each reflected direction of the pulled site (ln.x, yc, cz)
+// gains the wall term, shared between the components by the site's own phase.
+// s0: record slot of its plane.
+template <typename S, int TY, typename Planes>
+__device__ __forceinline__ void add_moving_terms(const Geom& g, const S& src, const LeanRows& rw, const LeanLane& ln,
+                                                 const Planes& rp, int s0, int yc, int cz, typename S::R (&t)[Q],
+                                                 typename S::R (&d)[Q]) {
+#pragma clang fp contract(off)
+    using R = typename S::R;
+    const bool wyz = rw.ylo || rw.yhi || rw.zlo || rw.zhi;
+    if (!g.moving || !(wyz || ln.xlo || ln.xhi)) return;
+    const R ph = src.template own_phase<TY>(g, rw.own(), ln, rp, s0);
+#pragma unroll
+    for (int i = 1; i < Q; ++i) {
+        if (!(rw.beyond(i) || ln.beyond(i))) continue;
+        const R add = wall_term<R>(g, i, ln.x, yc, cz);
+        t[i] += add;
+        d[i] = fma_of(add, ph, d[i]);
+    }
+}
+
 // ------------------------------------------------------------ phase sums
 // What a row sends to the rows above and below it, summed over the columns it
 // comes from: slot (e, f) for direction velocities c_y = e, c_z = f.
@@ -550,7 +668,7 @@ template <typename S, int TY, int H>
 struct LeanLds {
     using R = typename S::R;
     static constexpr size_t phi = (phi_ring_bytes<R, kTileX, H>(TY) + 15) & ~size_t(15);
-    static constexpr size_t rec = RecPlanes<typename S::C, S::NC, TY>::bytes;
+    static constexpr size_t rec = 3 * RecPlanes<typename S::C, S::NC, TY>::plane_bytes;
     static constexpr size_t half = (size_t)TY * kXchSlots * kXchRow * sizeof(R);
     static constexpr size_t vs = (size_t)2 * 3 * TY * sizeof(Part2<R>);
     static constexpr int rounds = phi + rec + 2 * half + vs <= kLdsBytes ? 1 : 2;
@@ -624,7 +742,7 @@ __device__ __forceinline__ void lean_tile(const Geom& g, const S& src, const D& 
     using Lds = LeanLds<S, TY, H>;
     constexpr int TX = kTileX, NT = TX * TY;
     constexpr int LX = TX + 2 * H, LY = TY + 2 * H, NP = 2 * H + 1, PLANE = LY * LX;
-    constexpr int NC = S::NC, NCA = NC > 0 ? NC : 1;
+    constexpr int NCA = S::NC > 0 ? S::NC : 1;
     R* const ring = reinterpret_cast<R*>(lds);
     const RecPlanes<C, NCA, TY> rp{reinterpret_cast<C*>(lds + Lds::phi)};
     R* const xch = reinterpret_cast<R*>(lds + Lds::phi + Lds::rec);
@@ -637,44 +755,14 @@ __device__ __forceinline__ void lean_tile(const Geom& g, const S& src, const D& 
     const int nrows = y1 - y0;
     const bool xin = x < g.nx, row_in = y < g.ny, site_in = xin && row_in;
     const bool ragged = x1 - x0 < TX;
-    // clamped coordinates: lanes and rows beyond the lattice compute on a valid
-    // site and store nothing
     const int xc = xin ? x : g.nx - 1, yc = row_in ? y : g.ny - 1;
-    const bool WX = W && g.wx;
-    LeanLane ln;
-    ln.c0 = (unsigned)xc;
-    ln.cm = (unsigned)(xc == 0 ? (WX ? 0 : g.nx - 1) : xc - 1);
-    ln.cp = (unsigned)(xc == g.nx - 1 ? (WX ? xc : 0) : xc + 1);
-    ln.wx = WX;
-    ln.xlo = WX && xc == 0;
-    ln.xhi = WX && xc == g.nx - 1;
-    ln.lane = lane;
-    ln.ty = ty;
-    ln.x = xc;
+    const LeanLane ln = lean_lane(g, W, xc, lane, ty);
     const unsigned nxy = (unsigned)g.nxy;
-    const unsigned yr[3] = {(unsigned)(yc == 0 ? g.ny - 1 : yc - 1) * (unsigned)g.nx, (unsigned)(yc * g.nx),
-                            (unsigned)(yc == g.ny - 1 ? 0 : yc + 1) * (unsigned)g.nx};
-    const bool ylo = W && g.wy && yc == 0, yhi = W && g.wy && yc == g.ny - 1;
-    auto rows_of = [&](int z) {  // z in [0, nz)
-        LeanRows o;
-        const unsigned zr[3] = {(unsigned)(z == 0 ? g.nz - 1 : z - 1) * nxy, (unsigned)z * nxy,
-                                (unsigned)(z == g.nz - 1 ? 0 : z + 1) * nxy};
-#pragma unroll
-        for (int a = 0; a < 3; ++a)
-#pragma unroll
-            for (int b = 0; b < 3; ++b) o.r[a][b] = zr[a] + yr[b];
-        o.ylo = ylo;
-        o.yhi = yhi;
-        o.zlo = W && g.wz && z == 0;
-        o.zhi = W && g.wz && z == g.nz - 1;
-        return o;
-    };
+    const LeanRowSet<W> rows(g, yc);
 
     // ---- staging of the rings: every thread loads its own site's entry and its
     // share of the halo entries around the tile
     constexpr int PE = LY * LX - TX * TY, NE = (PE + NT - 1) / NT;  // phase halo
-    constexpr int RE = 2 * kRecRow + 2 * TY;                        // record halo, at most one per thread
-    static_assert(RE <= NT, "a tile's record halo exceeds its threads");
     const unsigned main_at = (unsigned)(halo_coord(y0 + ty, g.ny, g.wy) * g.nx + halo_coord(x, g.nx, g.wx));
     const int main_lds = (ty + H) * LX + lane + H;
     unsigned pe_at[NE];
@@ -696,27 +784,10 @@ __device__ __forceinline__ void lean_tile(const Geom& g, const S& src, const D& 
         pe_at[k] = (unsigned)(halo_coord(y0 - H + r, g.ny, g.wy) * g.nx + halo_coord(x0 - H + q, g.nx, g.wx));
         pe_lds[k] = r * LX + q;
     }
-    unsigned re_at = 0;
-    int re_lds = 0;
-    const bool re_on = NC > 0 && (int)threadIdx.x < RE;
-    if (NC > 0) {
-        const int e = min((int)threadIdx.x, RE - 1);
-        int r, q;
-        if (e < 2 * kRecRow) {
-            r = e < kRecRow ? 0 : TY + 1;
-            q = e < kRecRow ? e : e - kRecRow;
-        } else {
-            const int e2 = e - 2 * kRecRow;
-            r = 1 + (e2 >> 1);
-            q = (e2 & 1) ? TX + 1 : 0;
-        }
-        re_at = (unsigned)(halo_coord(y0 - 1 + r, g.ny, g.wy) * g.nx + halo_coord(x0 - 1 + q, g.nx, g.wx));
-        re_lds = r * kRecRow + q;
-    }
-    const int rmain_lds = (ty + 1) * kRecRow + lane + 1;
+    const RecStage<S, TY> recs(g, x0, y0, lane, ty, main_at);
     struct Stage {
         R m, e[NE];
-        C rm[NCA], re[NCA];
+        typename RecStage<S, TY>::Regs rec;
     };
     auto load_phi = [&](int q, Stage& s) {
         const unsigned so = (unsigned)halo_plane(q, g.nz, g.wz) * nxy * (unsigned)sizeof(R);
@@ -731,30 +802,6 @@ __device__ __forceinline__ void lean_tile(const Geom& g, const S& src, const D& 
 #pragma unroll
         for (int k = 0; k < NE; ++k) p[pe_lds[k]] = s.e[k];
     };
-    auto load_rec = [&](int q, Stage& s) {
-        if constexpr (NC > 0) {
-            constexpr unsigned RB = 16u * NC;
-            const __amdgpu_buffer_rsrc_t rr = src.rec_res();
-            const unsigned so = (unsigned)halo_plane(q, g.nz, g.wz) * nxy * RB;
-#pragma unroll
-            for (int k = 0; k < NC; ++k) s.rm[k] = res_load_chunk<C>(rr, main_at * RB + 16u * k, so);
-            if (re_on) {
-#pragma unroll
-                for (int k = 0; k < NC; ++k) s.re[k] = res_load_chunk<C>(rr, re_at * RB + 16u * k, so);
-            }
-        }
-    };
-    auto put_rec = [&](int slot, const Stage& s) {
-        if constexpr (NC > 0) {
-#pragma unroll
-            for (int k = 0; k < NC; ++k) rp.at(slot, k, rmain_lds) = s.rm[k];
-            if (re_on) {
-#pragma unroll
-                for (int k = 0; k < NC; ++k) rp.at(slot, k, re_lds) = s.re[k];
-            }
-        }
-    };
-
     // edge lanes of the row and the columns their x-face sums go to
     int bd_lo = 0, bd_hi = 0;
     const bool edge_lo = row_in && lane == 0 && xface_dest<TX>(g, x0, x1, -1, bd_lo);
@@ -769,16 +816,16 @@ __device__ __forceinline__ void lean_tile(const Geom& g, const S& src, const D& 
         Stage s[2 * H];
 #pragma unroll
         for (int k = 0; k < 2 * H; ++k) load_phi(za - H + k, s[k]);
-        load_rec(za - 1, s[0]);
-        load_rec(za, s[1]);
+        recs.load(g, src, za - 1, s[0].rec);
+        recs.load(g, src, za, s[1].rec);
         load_phi(za + H, st);
-        load_rec(za + 1, st);
-        LeanRows rw = rows_of(za);
+        recs.load(g, src, za + 1, st.rec);
+        const LeanRows rw = rows.at(za);
         src.template fetch<W>(g, rw, ln, pre);
 #pragma unroll
         for (int k = 0; k < 2 * H; ++k) put_phi(k, s[k]);
-        put_rec(0, s[0]);
-        put_rec(1, s[1]);
+        recs.put(rp, 0, s[0].rec);
+        recs.put(rp, 1, s[1].rec);
     }
     R prev_dn = R(0), prev_rc = R(0), cur_dn = R(0), cur_rc = R(0);
     int s0 = H;  // ring slot of plane cz
@@ -790,40 +837,26 @@ __device__ __forceinline__ void lean_tile(const Geom& g, const S& src, const D& 
             int sh = s0 + H;
             sh = sh >= NP ? sh - NP : sh;
             put_phi(sh, st);
-            put_rec(r2, st);
+            recs.put(rp, r2, st.rec);
         }
         __syncthreads();
         // ---- pull (x, y, cz), then load what the next plane needs: always, at
         // the same point and for a plane clamped into the lattice, so that a
         // value the loop carries has one source and nothing at the loop head
         // waits for its load
-        const LeanRows rw = rows_of(cz);
+        const LeanRows rw = rows.at(cz);
         const unsigned own = rw.own();
         R t[Q], d[Q];
         src.template values<W, TY>(g, rw, ln, rp, k0, r1, r2, pre, t, d);
-        if constexpr (W && MV) {
-            // off a moving wall each reflected direction gains the wall term,
-            // shared between the components by the site's own phase
-            const bool wyz = rw.ylo || rw.yhi || rw.zlo || rw.zhi;
-            if (g.moving && (wyz || ln.xlo || ln.xhi)) {
-                const R ph = src.template own_phase<TY>(g, own, ln, rp, r1);
-#pragma unroll
-                for (int i = 1; i < Q; ++i) {
-                    if (!(rw.beyond(i) || ln.beyond(i))) continue;
-                    const R add = wall_term<R>(g, i, ln.x, yc, cz);
-                    t[i] += add;
-                    d[i] = fma_of(add, ph, d[i]);
-                }
-            }
-        }
+        if constexpr (W && MV) add_moving_terms<S, TY>(g, src, rw, ln, rp, r1, yc, cz, t, d);
         SiteSums<R> m;
 #pragma unroll
         for (int i = 0; i < Q; ++i) m.add(i, t[i], weight<R>(i) + t[i], d[i]);
         {
             const int zn = min(cz + 1, g.nz - 1);
             load_phi(cz + 1 + H, st);
-            load_rec(cz + 2, st);
-            const LeanRows rn = rows_of(zn);
+            recs.load(g, src, cz + 2, st.rec);
+            const LeanRows rn = rows.at(zn);
             src.template fetch<W>(g, rn, ln, pre);
         }
         // ---- colour gradient and near contact from the ring
