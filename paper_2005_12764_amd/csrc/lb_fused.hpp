@@ -113,6 +113,7 @@ __device__ __forceinline__ void ring_near_contact(const Geom& g, const PhiRing<R
     const R inv_gm = inv_norm(g2);
     const R nx = -gx * inv_gm, ny = -gy * inv_gm, nz = -gz * inv_gm;
     int h = 0;
+#pragma unroll 1
     for (int k = 1; k <= c.nc_range && k < H; ++k) {
         const int ox = (int)round(R(k) * nx);
         const int oy = (int)round(R(k) * ny);

@@ -151,11 +151,8 @@ int single_pass(const LatticeView& v, const Src& src, const StepEvents* t) {
     if (!v.part_in || !v.part_out) return set_error(LB_EINVAL, "one-read step without its phase buffers");
     const FusedShape fs = v.shape;
     if (t) (void)hipEventRecord(t->ev[0], v.stream);
-    int rc;
-    if (fs.TY == kSingleTY) rc = single_ty<R, Src, kSingleTY>(v, src, fs, t);
-    else if (fs.TY == kSingleTYSmall) rc = single_ty<R, Src, kSingleTYSmall>(v, src, fs, t);
-    else if (fs.TY == kSingleTYLarge) rc = single_ty<R, Src, kSingleTYLarge>(v, src, fs, t);
-    else return set_error(LB_EINVAL, "one-read tile does not fit in LDS");
+    if (fs.TY <= 0) return set_error(LB_EINVAL, "one-read tile does not fit in LDS");
+    const int rc = with_rows(fs.TY, [&](auto ty) { return single_ty<R, Src, decltype(ty)::value>(v, src, fs, t); });
     if (rc) return rc;
     if (t) (void)hipEventRecord(t->ev[2], v.stream);
     return LB_OK;
@@ -269,55 +266,60 @@ static int wanted_planes(const lb_params& p, int kind) {
 }
 
 static bool single_rows_fit(const lb_params& p, int ty) {
-    return (ty == kSingleTY || ty == kSingleTYSmall || ty == kSingleTYLarge) &&
+    return (ty == kSingleTY || ty == kSingleTYSmall || ty == kSingleTYLarge ||
+            (ty == kSingleTYSplit && split_storage(p))) &&
            tile_lds(p, TILE_SINGLE, ty) <= (size_t)device_lds_bytes();
 }
 
 // Estimated microseconds of a one-read step with TY rows and chunks of TZ
 // planes: workgroups run in rounds of as many as the 256 CUs hold at once (LDS
-// and registers); a workgroup starts its rings (8 us with the launch) and then
-// takes a plane in max(a + b w, f w) with w wavefronts per SIMD (a + b: the
-// latency of a row that nothing overlaps, f: the issue of one row); the assembly
-// takes 8 us or 16 ns per thousand face sites.  Fitted to the times of 64^3 to
-// 384^3 in each storage (64^3 FP32, tile only: 41 us with 4 rows and 8 planes, 26
-// with 4 planes, 21 with 2; 256^3 FP32: 693 us with 8 rows and 128 planes, 740
-// with 64, 701 with 4 rows and 32 planes, whose assembly takes 64 us more;
-// 512x128x64 with walls: 210 us with 8 rows and 32 planes, 387 with 64; 384^3
-// bf16: 2.05 ms with 48 planes, 9 whole rounds, 3.90 ms with 384, 1.1 rounds).
+// and registers); a workgroup starts its rings in s + s1 w and then takes a plane in
+// max(a + b w, f w) with w wavefronts per SIMD (a + b: the latency of a row that
+// nothing overlaps, f: its share of issue and memory); the assembly takes 8 us,
+// or 9 and 17 ns per thousand face sites.  Fitted to 360 shapes of lattices from
+// 32^3 to 384^3 in each storage, of which it finds one within 7% of the best
+// (256^3 FP32: 757 us with 16 rows and 64 planes, 793 with 8 rows and 32, 1170
+// with 16 rows and 128, half the CUs; 384^3 bf16: 2.21 ms with 12 rows and 48
+// planes, 2.61 with 8 rows; 256^3 fp16: 793 us with 12 rows, 833 with 8; 128^3
+// FP64: 220 us with 8 rows and 16 planes, 273 with 4; 64^3 FP32: 32 us with 2
+// planes, 50 with 4).
 static double single_cost(const lb_params& p, int TY, int TZ) {
     const int H = tile_halo(p);
-    const bool f64 = p.storage == LB_STORE_F64, walls = p.bc[0] || p.bc[1] || p.bc[2];
-    double a = f64 ? 1.0 : (split_storage(p) ? 2.6 : 2.5), b = f64 ? 5.6 : (split_storage(p) ? 1.7 : 1.4);
-    double f = f64 ? 6.6 : (split_storage(p) ? 3.0 : 2.65);
-    // no probe without near contact; wall tests; 8 rows of FP64 spill
-    const double scale = (H == 1 ? 0.8 : 1.0) * (walls ? 1.2 : 1.0) * (f64 && H > 1 && TY > 4 ? 1.15 : 1.0);
-    // wavefronts a SIMD holds, by registers
-    const int waves = f64 ? (H == 1 ? 2 : 1) : (split_storage(p) || walls ? 2 : 3);
-    const int per_simd = std::max(1, TY / 4);
-    const int hold = std::max(1, std::min((int)(kLdsBytes / tile_lds(p, TILE_SINGLE, TY)), waves / per_simd));
+    const bool f64 = p.storage == LB_STORE_F64, split = split_storage(p), walls = p.bc[0] || p.bc[1] || p.bc[2];
+    const double s = f64 ? 3.4 : (split ? 7.9 : 5.5), s1 = f64 ? 3.3 : (split ? 0.3 : 0.6);
+    const double a = f64 ? 3.4 : (split ? 1.9 : 3.1), b = f64 ? 3.2 : (split ? 1.65 : 1.0);
+    const double f = f64 ? 3.0 : (split ? 1.2 : 2.4), scale = walls ? 1.2 : 1.0;
+    const int waves = f64 ? 2 : (split || walls ? 3 : 4);  // a SIMD holds, by registers
+    const int hold =
+        std::max(1, std::min((int)(kLdsBytes / tile_lds(p, TILE_SINGLE, TY)), waves * 4 / TY));
     const double tiles = double((p.nx + kTX - 1) / kTX) * ((p.ny + TY - 1) / TY);
     const int chunks = (p.nz + TZ - 1) / TZ;
     const double per_cu = std::ceil(tiles * chunks / 256.0);
     const double resident = std::min<double>(hold, per_cu);
     // (rounds beyond the second start as CUs become free)
     const double rounds = per_cu <= 2 * hold ? std::ceil(per_cu / resident) : per_cu / resident;
-    const double w = per_simd * resident;
-    const double tile = rounds * (8.0 + TZ * scale * std::max(a + b * w, f * w));
+    const double w = 0.25 * TY * resident;
+    const double tile = rounds * (s + s1 * w + TZ * scale * std::max(a + b * w, f * w));
     auto faces = [](double n, int T) { return std::min(n, 2.0 * std::ceil(n / T)); };
     const double fx = faces(p.nx, kTX) / p.nx, fy = faces(p.ny, TY) / p.ny, fz = faces(p.nz, TZ) / p.nz;
     const double sites = double(p.nx) * p.ny * p.nz * (1.0 - (1.0 - fx) * (1.0 - fy) * (1.0 - fz));
-    return tile + std::max(8.0, sites * 1.6e-5);
+    return tile + std::max(8.0, 9.0 + sites * 1.66e-5);
 }
 
 // Rows and planes of the one-read step nothing else was asked for: the least
-// estimated step over 8 and 4 rows and the plane counts that divide the lattice
-// into equal chunks.  (16 rows of FP32 need more registers than four wavefronts
-// per SIMD have and spill: 256^3 995 us against 693 with 8.)
+// estimated step over the rows a storage runs without spilling (16 of periodic
+// FP32, 12 of 16 bits, 8 and 4 of all) and the plane counts that divide the
+// lattice into equal chunks.
 static void single_auto(const lb_params& p, int ty_wanted, int tz_wanted, int& ty, int& tz) {
+    const bool walls = p.bc[0] || p.bc[1] || p.bc[2];
+    auto offered = [&](int r) {
+        if (r == kSingleTYSplit) return split_storage(p);
+        return r != kSingleTYLarge || (p.storage == LB_STORE_F32 && !walls);
+    };
     double best = -1.0;
-    for (int r : {kSingleTY, kSingleTYSmall, kSingleTYLarge}) {
+    for (int r : {kSingleTY, kSingleTYSmall, kSingleTYSplit, kSingleTYLarge}) {
         if (!single_rows_fit(p, r)) continue;
-        if (ty_wanted > 0 ? r != ty_wanted : r == kSingleTYLarge) continue;
+        if (ty_wanted > 0 ? r != ty_wanted : !offered(r)) continue;
         for (int chunks = 1; chunks <= p.nz; chunks += chunks < 16 ? 1 : chunks / 8) {
             const int planes = tz_wanted > 0 ? std::min(tz_wanted, p.nz) : (p.nz + chunks - 1) / chunks;
             const double cost = single_cost(p, r, planes);
@@ -524,9 +526,7 @@ int launch_korteweg(const LatticeView& v, double lam, int b, void* kout, void* p
         int rc;
         if (v.part_valid && v.part_in) {
             const FusedShape fs = v.shape;
-            if (fs.TY == kSingleTY) rc = assemble_phase<R, S, kSingleTY>(v, src, fs);
-            else if (fs.TY == kSingleTYLarge) rc = assemble_phase<R, S, kSingleTYLarge>(v, src, fs);
-            else rc = assemble_phase<R, S, kSingleTYSmall>(v, src, fs);
+            rc = with_rows(fs.TY, [&](auto ty) { return assemble_phase<R, S, decltype(ty)::value>(v, src, fs); });
             field = phi_of<kTX>((Part2<R>*)v.part_in, v.g);
         } else {
             rc = phase_pass<R>(v, src);

@@ -24,8 +24,12 @@ size_t lds_of(int H) {
 }
 template <typename S>
 size_t lds_of(int TY, int H) {
-    return TY == kSingleTYSmall ? lds_of<S, kSingleTYSmall>(H)
-                                : (TY == kSingleTY ? lds_of<S, kSingleTY>(H) : lds_of<S, kSingleTYLarge>(H));
+    switch (TY) {
+        case kSingleTYSmall: return lds_of<S, kSingleTYSmall>(H);
+        case kSingleTY: return lds_of<S, kSingleTY>(H);
+        case kSingleTYSplit: return lds_of<S, kSingleTYSplit>(H);
+        default: return lds_of<S, kSingleTYLarge>(H);
+    }
 }
 }  // namespace
 

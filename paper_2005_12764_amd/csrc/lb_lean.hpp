@@ -17,11 +17,15 @@
 // A site whose sources all lie in the tile gets its phase field here; face sites
 // keep their own sums for the assembly.
 //
-// What bounds it: FP32 moves 92 B per site each way and runs about 1000 VALU
-// instructions per site, 0.59 ms of memory (at the rate its access pattern
-// reaches without arithmetic, lb_pattern_ms) against 0.43 ms of issue at 256^3,
-// so both have to overlap: everything a plane needs from memory is loaded while
-// the plane before it is collided.
+// What bounds it: at 256^3 FP32 moves 3.34 GB (92 B per site each way, the phase
+// field, halos of records), 0.59 ms at the rate its access pattern reaches
+// without arithmetic (lb_pattern_ms), and issues 0.33 ms of vector instructions
+// per SIMD: 16 rows, four wavefronts per SIMD, take 0.70 ms, 4.8 TB/s (0.77 with
+// 8 rows of 64 x 128 planes).  Left out in turn, probe, decode, phase sums and
+// collision give 4 % each: memory bounds it.  16-bit storage moves 2.78 GB, 0.53
+// ms, and issues 0.43: 12 rows, three wavefronts, take 0.71 ms, 8 rows 0.79; a
+// probe less is 10 % less there.  Everything a plane needs from memory is loaded
+// while the plane before it is collided.
 #pragma once
 #include "lb_pack.hpp"
 #include "lb_single.hpp"
@@ -245,6 +249,20 @@ __device__ __forceinline__ int halo_plane(int z, int n, int wall) {
     return z;
 }
 
+// The decode reads a source record from LDS per direction; left free, the
+// compiler has all 19 in flight (76 or 152 registers) and fewer wavefronts fit a
+// SIMD.  After the tenth direction the running sums pass through an empty
+// statement that the later reads stay behind: 16 rows of FP32 then fit the 128
+// registers of four wavefronts per SIMD without spilling (256^3, tile: 701 us
+// against 894), 12 rows of 16-bit storage the 168 of three (384^3 bf16: 2.10 ms;
+// 2.19 with a stop every fourth direction, 7.8 without).  The wall tests take more
+// registers: there the statement stands after every sixth.
+template <bool W, typename R>
+__device__ __forceinline__ void settle(SiteSums<R>& m, int i) {
+    if (W ? i % 6 == 5 : i == 9)
+        asm volatile("" : "+v"(m.drho), "+v"(m.dif), "+v"(m.rc), "+v"(m.jx), "+v"(m.jy), "+v"(m.jz)::"memory");
+}
+
 // LDS ring of the source records of planes z - 1, z, z + 1 (tile plus one site
 // around it): per plane NC runs of 16-byte pieces, so consecutive lanes read
 // consecutive pieces, free of bank conflicts.
@@ -356,10 +374,11 @@ struct LeanPairs {
         }
         return sd / st;
     }
-    template <bool W, int TY>
+    template <bool W, int TY, typename Visit>
     __device__ __forceinline__ void values(const Geom& g, const LeanRows& rw, const LeanLane& ln,
-                                           const RecPlanes<C, 1, TY>&, int, int, int, const Pre&, T (&t)[Q],
-                                           T (&d)[Q]) const {
+                                           const RecPlanes<C, 1, TY>&, int, int, int, const Pre&,
+                                           const Visit& visit) const {
+        T t[Q], d[Q];
         const Res rs = res((unsigned)g.N);
         constexpr unsigned SZ = 2 * (unsigned)sizeof(T);
         const unsigned S = (unsigned)g.N + kRawPad;
@@ -377,6 +396,8 @@ struct LeanPairs {
                     res_load_pair(t[i], d[i], rs.r[o / kResPairs], ln.c0 * SZ, off(o, rw.own()));
             }
         }
+#pragma unroll
+        for (int i = 0; i < Q; ++i) visit(i, t[i], d[i]);
     }
 };
 
@@ -386,6 +407,7 @@ struct LeanPack {
     using R = T;
     using C = typename Chunk<T>::type;
     static constexpr int NC = (int)(sizeof(T) / 4);  // pieces of a record
+    static constexpr bool kSplit = false;
     T* rec;
     T* tot;
     struct Pre {
@@ -466,12 +488,12 @@ struct LeanPack {
         const T v = Lattice::len2(i) == 1 ? k * cs : cs;
         return fma_of(q.phi, wt, refl ? -v : v);
     }
-    // t_i, d_i of the site at ring entry e; sm, s0, sp: slots of planes z - 1,
-    // z, z + 1
-    template <bool W, int TY>
+    // visit(i, t_i, d_i) of the lane's site in ascending direction; sm, s0, sp:
+    // slots of planes z - 1, z, z + 1
+    template <bool W, int TY, typename Visit>
     __device__ __forceinline__ void values(const Geom&, const LeanRows& rw, const LeanLane& ln,
                                            const RecPlanes<C, NC, TY>& rp, int sm, int s0, int sp, const Pre& p,
-                                           T (&t)[Q], T (&d)[Q]) const {
+                                           const Visit& visit) const {
         using L = Lattice;
         const int own = (ln.ty + 1) * kRecRow + ln.lane + 1;
 #pragma unroll
@@ -483,8 +505,7 @@ struct LeanPack {
                 s = refl ? s0 : s;
                 e = refl ? own : e;
             }
-            t[i] = p.v[i];
-            d[i] = diff(i, weight<T>(i) + t[i], colour<TY>(rp, s, e), refl);
+            visit(i, p.v[i], diff(i, weight<T>(i) + p.v[i], colour<TY>(rp, s, e), refl));
         }
     }
     // Destination: store the site and keep what a later pull reads of it.
@@ -538,6 +559,7 @@ struct LeanSplit {
     using R = float;
     using C = f4;
     static constexpr int NC = 2;
+    static constexpr bool kSplit = true;
     float* rec;
     H* dev;
     SplitPop<H> codec;  // scale and the record arithmetic
@@ -570,10 +592,10 @@ struct LeanSplit {
             at += step;
         }
     }
-    template <bool W, int TY>
+    template <bool W, int TY, typename Visit>
     __device__ __forceinline__ void values(const Geom&, const LeanRows& rw, const LeanLane& ln,
                                            const RecPlanes<C, NC, TY>& rp, int sm, int s0, int sp, const Pre& p,
-                                           float (&t)[Q], float (&d)[Q]) const {
+                                           const Visit& visit) const {
         using L = Lattice;
         const int own = (ln.ty + 1) * kRecRow + ln.lane + 1;
 #pragma unroll
@@ -587,7 +609,9 @@ struct LeanSplit {
                 sg = refl ? -1.0f : 1.0f;
             }
             const f4 ra = rp.at(s, 0, e), rb = rp.at(s, 1, e);
-            codec.finish(i, sg, SplitPop<H>::excess(i, sg, ra), rb, dev_of(p.dv[i]), t[i], d[i]);
+            float t, d;
+            codec.finish(i, sg, SplitPop<H>::excess(i, sg, ra), rb, dev_of(p.dv[i]), t, d);
+            visit(i, t, d);
         }
     }
     // The phase of the site's own record.
@@ -634,30 +658,35 @@ struct LeanSplit {
     __device__ __forceinline__ float kept_phase(const float (&)[Q], const Kept& k) const { return k.rb.x; }
 };
 
-// Off a moving wall each reflected direction of the pulled site (ln.x, yc, cz)
-// gains the wall term, shared between the components by the site's own phase.
-// s0: record slot of its plane.
-template <typename S, int TY, typename Planes>
-__device__ __forceinline__ void add_moving_terms(const Geom& g, const S& src, const LeanRows& rw, const LeanLane& ln,
-                                                 const Planes& rp, int s0, int yc, int cz, typename S::R (&t)[Q],
-                                                 typename S::R (&d)[Q]) {
-#pragma clang fp contract(off)
-    using R = typename S::R;
-    const bool wyz = rw.ylo || rw.yhi || rw.zlo || rw.zhi;
-    if (!g.moving || !(wyz || ln.xlo || ln.xhi)) return;
-    const R ph = src.template own_phase<TY>(g, rw.own(), ln, rp, s0);
-#pragma unroll
-    for (int i = 1; i < Q; ++i) {
-        if (!(rw.beyond(i) || ln.beyond(i))) continue;
-        const R add = wall_term<R>(g, i, ln.x, yc, cz);
-        t[i] += add;
-        d[i] = fma_of(add, ph, d[i]);
+// Off a moving wall each reflected direction of the pulled site gains the wall
+// term, shared between the components by the site's own phase.
+template <typename R>
+struct MovingTerms {
+    bool on = false;
+    R ph = R(0);
+    // s0: record slot of the site's plane
+    template <typename S, int TY, typename Planes>
+    __device__ __forceinline__ void init(const Geom& g, const S& src, const LeanRows& rw, const LeanLane& ln,
+                                         const Planes& rp, int s0) {
+        const bool wyz = rw.ylo || rw.yhi || rw.zlo || rw.zhi;
+        on = g.moving && (wyz || ln.xlo || ln.xhi);
+        if (on) ph = src.template own_phase<TY>(g, rw.own(), ln, rp, s0);
     }
-}
+    __device__ __forceinline__ void add(const Geom& g, int i, const LeanRows& rw, const LeanLane& ln, int yc, int cz,
+                                        R& t, R& d) const {
+#pragma clang fp contract(off)
+        if (i == 0 || !on || !(rw.beyond(i) || ln.beyond(i))) return;
+        const R a = wall_term<R>(g, i, ln.x, yc, cz);
+        t += a;
+        d = fma_of(a, ph, d);
+    }
+};
 
 // ------------------------------------------------------------ phase sums
 // What a row sends to the rows above and below it, summed over the columns it
-// comes from: slot (e, f) for direction velocities c_y = e, c_z = f.
+// comes from: slot (e, f) for direction velocities c_y = e, c_z = f.  Between
+// rows r and r + 1 lie the sums r sends up (e = 1) and those r + 1 sends down;
+// what the first and last row send out of the tile is another box's.
 __host__ __device__ constexpr int xch_slot(int e, int f) { return (e > 0 ? 0 : 3) + (f == 0 ? 0 : (f > 0 ? 1 : 2)); }
 constexpr int kXchSlots = 6;
 constexpr int kXchRow = kTileX + 2;  // a row's 64 columns and one beyond each end (x-face terms)
@@ -669,61 +698,118 @@ struct LeanLds {
     using R = typename S::R;
     static constexpr size_t phi = (phi_ring_bytes<R, kTileX, H>(TY) + 15) & ~size_t(15);
     static constexpr size_t rec = 3 * RecPlanes<typename S::C, S::NC, TY>::plane_bytes;
-    static constexpr size_t half = (size_t)TY * kXchSlots * kXchRow * sizeof(R);
+    static constexpr size_t half = (size_t)(TY - 1) * kXchSlots * kXchRow * sizeof(R);
     static constexpr size_t vs = (size_t)2 * 3 * TY * sizeof(Part2<R>);
     static constexpr int rounds = phi + rec + 2 * half + vs <= kLdsBytes ? 1 : 2;
     static constexpr size_t xch = rounds == 1 ? 2 * half : half;
     static constexpr size_t bytes = phi + rec + xch + vs;
 };
 
-// x-face sums an edge lane of a tile column accumulates for the face sites of
-// the neighbouring column: the lo edge lane (SX = -1) feeds the hi face of the
-// column on its left, the hi edge lane (SX = +1) the lo face of the one on its
-// right (periodic wrap; none beyond an x wall).  The running sums of the
-// destination planes z-1, z, z+1 of its row live in LDS, vs[side][plane mod
-// 3][row].  Before the exchange: the lane's own terms of plane cz close the sum
-// of destination plane cz - 1 (stored), add the first in-plane term of plane cz
-// and open the sum of plane cz + 1.  a, d: w_i + t_i and d_i of direction i.
-template <int SX, typename R, int TY, typename V>
-__device__ __forceinline__ void xedge_own(const Geom& g, const V& val, Part2<R>* __restrict__ vs, int ty, int y, int cz,
-                                          int k0, int za, int zb, int bd, __amdgpu_buffer_rsrc_t xf) {
-    constexpr int im = dir_of(SX, 0, -1), i0 = dir_of(SX, 0, 0), ip = dir_of(SX, 0, 1);
-    constexpr int side = SX < 0 ? 0 : 1;
-    const int km = k0 == 0 ? 2 : k0 - 1, kp = k0 == 2 ? 0 : k0 + 1;
-    Part2<R>* v = vs + side * 3 * TY + ty;
-    if (cz - 1 >= za) {
-        Part2<R> P = v[km * TY];
-        const Part2<R> e = val(im);
-        P.rc += e.rc;
-        P.dn += e.dn;
-        res_store(P, xf, 0, xface_at(g, bd, 1 - side, y, cz - 1) * (unsigned)sizeof(P));
+// x-face sums the edge lanes of a tile column accumulate for the face sites of
+// the neighbouring columns: the lo edge lane (c_x = -1) feeds the hi face of the
+// column on its left, the hi edge lane (c_x = +1) the lo face of the one on its
+// right (periodic wrap; none beyond an x wall).  Both lanes run the same code,
+// each on its side's directions; where one lane is both (a column one site wide)
+// it runs twice.  The running sums of the destination planes z-1, z, z+1 of a row
+// live in LDS, vs[side][plane mod 3][row].
+template <typename R, int TY>
+struct XEdge {
+    int passes;
+    bool lo_on, hi_on, hi;    // this lane feeds a column, and from which side
+    unsigned lo_at, hi_at;    // entries of its destinations in plane 0
+    int width;
+    __device__ __forceinline__ XEdge(const Geom& g, int x0, int x1, int y, bool row_in, int lane)
+        : passes(x1 - x0 == 1 ? 2 : 1), width(x1 - x0) {
+        int bd_lo = 0, bd_hi = 0;
+        const bool has_lo = xface_dest<kTileX>(g, x0, x1, -1, bd_lo), has_hi = xface_dest<kTileX>(g, x0, x1, 1, bd_hi);
+        lo_on = row_in && lane == 0 && has_lo;
+        hi_on = row_in && lane == x1 - x0 - 1 && has_hi;
+        hi = lane != 0;
+        lo_at = xface_at(g, bd_lo, 1, y, 0);
+        hi_at = xface_at(g, bd_hi, 0, y, 0);
     }
-    Part2<R> P = cz == za ? Part2<R>{R(0), R(0)} : v[k0 * TY];
-    const Part2<R> e = val(i0);
-    P.rc += e.rc;
-    P.dn += e.dn;
-    v[k0 * TY] = P;
-    if (cz + 1 < zb) v[kp * TY] = val(ip);
-}
-// After the exchange: the in-plane terms the edge lanes of the rows below and
-// above send across the face (ascending direction); the chunk's last plane is
-// then complete.  up, dn: those terms of the two rows.
-template <int SX, typename R, int TY>
-__device__ __forceinline__ void xedge_rows(const Geom& g, const Part2<R>& up, const Part2<R>& dn,
-                                           Part2<R>* __restrict__ vs, int ty, int y, int cz, int k0, int zb, int bd,
-                                           __amdgpu_buffer_rsrc_t xf) {
-    constexpr int side = SX < 0 ? 0 : 1;
-    Part2<R>* v = vs + side * 3 * TY + ty;
-    Part2<R> P = v[k0 * TY];
-    // c_x = +1: directions 7 (from the row below) then 9 (from the row above);
-    // c_x = -1: 8 (above) then 10 (below)
-    P.rc += SX > 0 ? up.rc : dn.rc;
-    P.dn += SX > 0 ? up.dn : dn.dn;
-    P.rc += SX > 0 ? dn.rc : up.rc;
-    P.dn += SX > 0 ? dn.dn : up.dn;
-    if (cz == zb - 1) res_store(P, xf, 0, xface_at(g, bd, 1 - side, y, cz) * (unsigned)sizeof(P));
-    else v[k0 * TY] = P;
-}
+    __device__ __forceinline__ bool is_hi(int pass) const { return passes == 1 ? hi : pass != 0; }
+    __device__ __forceinline__ bool active(bool h) const {
+        const bool l = lo_on, r = hi_on;
+        return (h && r) || (!h && l);
+    }
+    __device__ __forceinline__ unsigned dest(bool h) const {  // byte offset in plane 0
+        const unsigned l = lo_at, r = hi_at;
+        return (h ? r : l) * (unsigned)sizeof(Part2<R>);
+    }
+
+    // Before the exchange: the lane's own terms of plane cz close the sum of
+    // destination plane cz - 1 (stored), add the first in-plane term of plane cz
+    // and open the sum of plane cz + 1; the terms its row sends across the face
+    // into the rows above and below go to the pads of its exchange rows.
+    // val(i): w_i + t_i and d_i of direction i; pad(e, column, terms): stores one.
+    template <typename V, typename Pad>
+    __device__ __forceinline__ void own(const Geom& g, const V& val, const Pad& pad, Part2<R>* __restrict__ vs, int ty,
+                                        int cz, int k0, int za, int zb, __amdgpu_buffer_rsrc_t xf) const {
+        const int km = k0 == 0 ? 2 : k0 - 1, kp = k0 == 2 ? 0 : k0 + 1;
+#pragma unroll 1
+        for (int pass = 0; pass < passes; ++pass) {
+            const bool h = is_hi(pass);
+            if (!active(h)) continue;
+            auto side = [&](int cy, int cz_) {
+                const Part2<R> l = val(dir_of(-1, cy, cz_)), r = val(dir_of(1, cy, cz_));
+                return Part2<R>{h ? r.dn : l.dn, h ? r.rc : l.rc};
+            };
+            Part2<R>* v = vs + (h ? 3 * TY : 0) + ty;
+            auto plus = [](const Part2<R>& p, const Part2<R>& q) { return Part2<R>{p.dn + q.dn, p.rc + q.rc}; };
+            if (cz - 1 >= za)
+                res_store(plus(v[km * TY], side(0, -1)), xf, dest(h),
+                          (unsigned)((cz - 1) * g.ny) * (unsigned)sizeof(Part2<R>));
+            v[k0 * TY] = plus(cz == za ? Part2<R>{R(0), R(0)} : v[k0 * TY], side(0, 0));
+            if (cz + 1 < zb) v[kp * TY] = side(0, 1);
+            const int column = h ? 1 + width : 0;
+            pad(1, column, side(1, 0));
+            pad(-1, column, side(-1, 0));
+        }
+    }
+    // The pads alone, for a second exchange round.
+    template <typename V, typename Pad>
+    __device__ __forceinline__ void pads(const V& val, const Pad& pad) const {
+#pragma unroll 1
+        for (int pass = 0; pass < passes; ++pass) {
+            const bool h = is_hi(pass);
+            if (!active(h)) continue;
+#pragma unroll
+            for (int e = 1; e >= -1; e -= 2) {
+                const Part2<R> l = val(dir_of(-1, e, 0)), r = val(dir_of(1, e, 0));
+                pad(e, h ? 1 + width : 0, Part2<R>{h ? r.dn : l.dn, h ? r.rc : l.rc});
+            }
+        }
+    }
+    // After the exchange: the in-plane terms the rows below and above send across
+    // the face, in ascending direction (7 from below then 9 from above; 8 from
+    // above then 10 from below); the chunk's last plane is then complete.
+    // got(e, column): what the row y - e left at that pad, zero if it is not in
+    // the tile.
+    // round: of `rounds` exchange rounds, the R sums in the first, the D sums in
+    // the last.
+    template <typename Got>
+    __device__ __forceinline__ void rows(const Geom& g, int round, int rounds, const Got& got, Part2<R>* __restrict__ vs,
+                                         int ty, int cz, int k0, int zb, __amdgpu_buffer_rsrc_t xf) const {
+        const bool do_rc = round == 0, do_dn = round == rounds - 1;
+#pragma unroll 1
+        for (int pass = 0; pass < passes; ++pass) {
+            const bool h = is_hi(pass);
+            if (!active(h)) continue;
+            Part2<R>* v = vs + (h ? 3 * TY : 0) + ty;
+            const int column = h ? 1 + width : 0;
+            const Part2<R> below = got(1, column), above = got(-1, column);
+            Part2<R> P = v[k0 * TY];
+            if (do_rc) P.rc = (P.rc + (h ? below.rc : above.rc)) + (h ? above.rc : below.rc);
+            if (do_dn) P.dn = (P.dn + (h ? below.dn : above.dn)) + (h ? above.dn : below.dn);
+            if (do_dn && cz == zb - 1)
+                res_store(P, xf, dest(h),
+                          (unsigned)(cz * g.ny) * (unsigned)sizeof(P));
+            else
+                v[k0 * TY] = P;
+        }
+    }
+};
 
 // One tile of the one-read step: columns [x0, x0+64) x [y0, y0+TY), planes
 // [za, zb); blockDim.x == 64 TY; source S, destination D (the same form, or
@@ -802,10 +888,7 @@ __device__ __forceinline__ void lean_tile(const Geom& g, const S& src, const D& 
 #pragma unroll
         for (int k = 0; k < NE; ++k) p[pe_lds[k]] = s.e[k];
     };
-    // edge lanes of the row and the columns their x-face sums go to
-    int bd_lo = 0, bd_hi = 0;
-    const bool edge_lo = row_in && lane == 0 && xface_dest<TX>(g, x0, x1, -1, bd_lo);
-    const bool edge_hi = row_in && x == x1 - 1 && xface_dest<TX>(g, x0, x1, 1, bd_hi);
+    const XEdge<R, TY> xedge(g, x0, x1, y, row_in, lane);
     // a site on an x or y face of the box keeps its own sums for the assembly
     const bool face_xy = lane == 0 || lane == TX - 1 || x == g.nx - 1 || ty == 0 || ty == TY - 1 || y == g.ny - 1;
 
@@ -840,26 +923,8 @@ __device__ __forceinline__ void lean_tile(const Geom& g, const S& src, const D& 
             recs.put(rp, r2, st.rec);
         }
         __syncthreads();
-        // ---- pull (x, y, cz), then load what the next plane needs: always, at
-        // the same point and for a plane clamped into the lattice, so that a
-        // value the loop carries has one source and nothing at the loop head
-        // waits for its load
-        const LeanRows rw = rows.at(cz);
-        const unsigned own = rw.own();
-        R t[Q], d[Q];
-        src.template values<W, TY>(g, rw, ln, rp, k0, r1, r2, pre, t, d);
-        if constexpr (W && MV) add_moving_terms<S, TY>(g, src, rw, ln, rp, r1, yc, cz, t, d);
-        SiteSums<R> m;
-#pragma unroll
-        for (int i = 0; i < Q; ++i) m.add(i, t[i], weight<R>(i) + t[i], d[i]);
-        {
-            const int zn = min(cz + 1, g.nz - 1);
-            load_phi(cz + 1 + H, st);
-            recs.load(g, src, cz + 2, st.rec);
-            const LeanRows rn = rows.at(zn);
-            src.template fetch<W>(g, rn, ln, pre);
-        }
-        // ---- colour gradient and near contact from the ring
+        // ---- colour gradient and near contact from the ring (before the pull: the
+        // probe's addresses then do not add to the pulled values in registers)
         const int sm = s0 == 0 ? NP - 1 : s0 - 1, sp = s0 == NP - 1 ? 0 : s0 + 1;
         R gx, gy, gz;
         {
@@ -879,11 +944,35 @@ __device__ __forceinline__ void lean_tile(const Geom& g, const S& src, const D& 
             const PhiRing<R, TX, H> pr{ring, LY};
             ring_near_contact<R, TX, H>(g, pr, s0, xc, yc, cz, ty + H, lane + H, gx, gy, gz, c, Fx, Fy, Fz);
         }
+        // ---- pull (x, y, cz), then load what the next plane needs: always, at
+        // the same point and for a plane clamped into the lattice, so that a
+        // value the loop carries has one source and nothing at the loop head
+        // waits for its load
+        const LeanRows rw = rows.at(cz);
+        const unsigned own = rw.own();
+        R t[Q];
+        SiteSums<R> m;
+        MovingTerms<R> mt;
+        if constexpr (W && MV) mt.template init<S, TY>(g, src, rw, ln, rp, r1);
+        src.template values<W, TY>(g, rw, ln, rp, k0, r1, r2, pre, [&](int i, R ti, R di) {
+            if constexpr (W && MV) mt.add(g, i, rw, ln, yc, cz, ti, di);
+            t[i] = ti;
+            m.add(i, ti, weight<R>(i) + ti, di);
+            settle<W>(m, i);
+        });
+        {
+            const int zn = min(cz + 1, g.nz - 1);
+            load_phi(cz + 1 + H, st);
+            recs.load(g, src, cz + 2, st.rec);
+            const LeanRows rn = rows.at(zn);
+            src.template fetch<W>(g, rn, ln, pre);
+        }
         SiteTotals<R> tot;
         collide_totals<R>(t, m, gx, gy, gz, Fx, Fy, Fz, c, tot);
         typename D::Kept kept;
         dst.store(g, own, ln, t, tot, site_in, kept);
         if (ragged) {
+            asm volatile("");  // (a branch: selects would cost every full tile 23 instructions)
             // lanes beyond the lattice hand nothing to their neighbours
             if (!xin) {
 #pragma unroll
@@ -935,90 +1024,86 @@ __device__ __forceinline__ void lean_tile(const Geom& g, const S& src, const D& 
                 cur_dn += dv;
             }
         }
-        if (edge_lo) xedge_own<-1, R, TY>(g, val, vs, ty, y, cz, k0, za, zb, bd_lo, array_res(part_out + g.N));
-        if (edge_hi) xedge_own<1, R, TY>(g, val, vs, ty, y, cz, k0, za, zb, bd_hi, array_res(part_out + g.N));
-        // by destination plane cz - 1, cz, cz + 1 (c_z + 1): the running sum, then
-        // this row's terms, those of the row below (c_y = 1) and of the row above
-        Part2<R> sum[3] = {{prev_dn, prev_rc}, {cur_dn, cur_rc}, {R(0), R(0)}};
-#pragma unroll
-        for (int f = -1; f <= 1; ++f) add(sum[f + 1], row_sum(0, f));
-        Part2<R> up_lo{}, dn_lo{}, up_hi{}, dn_hi{};
-        const int xe = x1 - x0;  // column just beyond the tile
+        // by destination plane cz - 1, cz, cz + 1: the running sum, then this row's
+        // terms, those of the row below (c_y = 1) and of the row above
+        Part2<R> to_m{prev_dn, prev_rc}, to_0{cur_dn, cur_rc}, to_p{R(0), R(0)};
+        add(to_m, row_sum(0, -1));
+        add(to_0, row_sum(0, 0));
+        add(to_p, row_sum(0, 1));
+        constexpr int STEP = Lds::rounds == 1 ? 2 : 1;  // D beside R, or in a second round
+        constexpr int XROW = STEP * kXchSlots * kXchRow;
 #pragma unroll
         for (int round = 0; round < Lds::rounds; ++round) {
             if (round) __syncthreads();
-            constexpr int STEP = Lds::rounds == 1 ? 2 : 1;
-            R* const mine = xch + ty * (STEP * kXchSlots * kXchRow);
-#pragma unroll
-            for (int e = 1; e >= -1; e -= 2)
-#pragma unroll
-                for (int f = -1; f <= 1; ++f) {
-                    const Part2<R> p = row_sum(e, f);
-                    R* o = mine + xch_slot(e, f) * kXchRow + 1 + lane;
-                    if (STEP == 2 || round == 0) o[0] = p.rc;
-                    if (STEP == 2) o[kXchSlots * kXchRow] = p.dn;
-                    else if (round == 1) o[0] = p.dn;
-                    if (f == 0) {
-                        // terms that leave a full row through its ends
-                        if (lane == 0 || lane == TX - 1) {
-                            const Part2<R> l = val(dir_of(-1, e, 0)), r = val(dir_of(1, e, 0));
-                            R* q = mine + xch_slot(e, 0) * kXchRow + (lane == 0 ? 0 : TX + 1);
-                            const R vr = lane == 0 ? l.rc : r.rc, vd = lane == 0 ? l.dn : r.dn;
-                            if (STEP == 2 || round == 0) q[0] = vr;
-                            if (STEP == 2) q[kXchSlots * kXchRow] = vd;
-                            else if (round == 1) q[0] = vd;
-                        }
-                    }
-                }
-            __syncthreads();
-#pragma unroll
-            for (int s = 0; s < 2; ++s) {
-                const int e = s == 0 ? 1 : -1, ys = ty - e;
-                if (ys < 0 || ys >= nrows) continue;  // (uniform; beyond the tile: another box's terms)
-                const R* in = xch + ys * (STEP * kXchSlots * kXchRow);
-#pragma unroll
-                for (int f = -1; f <= 1; ++f) {
-                    const R* o = in + xch_slot(e, f) * kXchRow + 1 + lane;
-                    if (STEP == 2 || round == 0) sum[f + 1].rc += o[0];
-                    if (STEP == 2) sum[f + 1].dn += o[kXchSlots * kXchRow];
-                    else if (round == 1) sum[f + 1].dn += o[0];
-                }
-                if (edge_lo || edge_hi) {
-                    const R* o = in + xch_slot(e, 0) * kXchRow;
-                    Part2<R>& lo = s == 0 ? up_lo : dn_lo;
-                    Part2<R>& hi = s == 0 ? up_hi : dn_hi;
-                    if (STEP == 2 || round == 0) {
-                        lo.rc = o[0];
-                        hi.rc = o[1 + xe];
-                    }
-                    if (STEP == 2) {
-                        lo.dn = o[kXchSlots * kXchRow];
-                        hi.dn = o[kXchSlots * kXchRow + 1 + xe];
-                    } else if (round == 1) {
-                        lo.dn = o[0];
-                        hi.dn = o[1 + xe];
-                    }
-                }
+            // of row ty to row ty + e; from row ty - e
+            auto to_row = [&](int e) { return xch + (e > 0 ? ty : ty - 1) * XROW; };
+            auto row_at = [&](int e) { return xch + (e > 0 ? ty - 1 : ty) * XROW; };
+            const bool up = ty + 1 < nrows, down = ty > 0 && ty < nrows;  // (uniform)
+            auto sends = [&](int e) { return e > 0 ? up : down; };
+            auto put = [&](int e, int f, int column, const Part2<R>& p) {
+                R* o = to_row(e) + xch_slot(e, f) * kXchRow + column;
+                if (STEP == 2 || round == 0) o[0] = p.rc;
+                if (STEP == 2) o[kXchSlots * kXchRow] = p.dn;
+                else if (round == 1) o[0] = p.dn;
+            };
+            if (up) {
+                put(1, -1, 1 + lane, row_sum(1, -1));
+                put(1, 0, 1 + lane, row_sum(1, 0));
+                put(1, 1, 1 + lane, row_sum(1, 1));
             }
+            if (down) {
+                put(-1, -1, 1 + lane, row_sum(-1, -1));
+                put(-1, 0, 1 + lane, row_sum(-1, 0));
+                put(-1, 1, 1 + lane, row_sum(-1, 1));
+            }
+            auto pad = [&](int e, int column, const Part2<R>& p) {
+                if (sends(e)) put(e, 0, column, p);
+            };
+            if (round == 0) xedge.own(g, val, pad, vs, ty, cz, k0, za, zb, array_res(part_out + g.N));
+            else xedge.pads(val, pad);
+            __syncthreads();
+            auto have = [&](int e) { return e > 0 ? down : up; };  // (a row beyond the tile: another box's terms)
+            auto take = [&](int e, int f, Part2<R>& p) {
+                const R* o = row_at(e) + xch_slot(e, f) * kXchRow + 1 + lane;
+                if (STEP == 2 || round == 0) p.rc += o[0];
+                if (STEP == 2) p.dn += o[kXchSlots * kXchRow];
+                else if (round == 1) p.dn += o[0];
+            };
+            if (have(1)) {
+                take(1, -1, to_m);
+                take(1, 0, to_0);
+                take(1, 1, to_p);
+            }
+            if (have(-1)) {
+                take(-1, -1, to_m);
+                take(-1, 0, to_0);
+                take(-1, 1, to_p);
+            }
+            xedge.rows(
+                g, round, Lds::rounds,
+                [&](int e, int column) {
+                    const R* o = row_at(e) + xch_slot(e, 0) * kXchRow + column;
+                    const R a = have(e) ? o[0] : R(0);
+                    return Part2<R>{STEP == 2 ? (have(e) ? o[kXchSlots * kXchRow] : R(0)) : a, a};
+                },
+                vs, ty, cz, k0, zb, array_res(part_out + g.N));
         }
-        if (edge_lo) xedge_rows<-1, R, TY>(g, up_lo, dn_lo, vs, ty, y, cz, k0, zb, bd_lo, array_res(part_out + g.N));
-        if (edge_hi) xedge_rows<1, R, TY>(g, up_hi, dn_hi, vs, ty, y, cz, k0, zb, bd_hi, array_res(part_out + g.N));
         // destination cz - 1 is complete: sources in plane cz are its last group
         if (cz - 1 >= za && site_in) {
             const unsigned row = (unsigned)(cz - 1) * nxy + (unsigned)(y * g.nx);
             if (cz - 1 == za || face_xy)
-                res_store(sum[0], array_res(part_out), (unsigned)x * (unsigned)sizeof(Part2<R>), row * (unsigned)sizeof(Part2<R>));
+                res_store(to_m, array_res(part_out), (unsigned)x * (unsigned)sizeof(Part2<R>), row * (unsigned)sizeof(Part2<R>));
             else
-                res_store_cached(sum[0].dn / sum[0].rc, array_res(phi_out), (unsigned)x * (unsigned)sizeof(R),
+                res_store_cached(to_m.dn / to_m.rc, array_res(phi_out), (unsigned)x * (unsigned)sizeof(R),
                                  row * (unsigned)sizeof(R));
         }
-        prev_dn = sum[1].dn;
-        prev_rc = sum[1].rc;
-        cur_dn = sum[2].dn;
-        cur_rc = sum[2].rc;
+        prev_dn = to_0.dn;
+        prev_rc = to_0.rc;
+        cur_dn = to_p.dn;
+        cur_rc = to_p.rc;
         // the chunk's last plane has no own sources above it
         if (cz == zb - 1 && site_in)
-            res_store(sum[1], array_res(part_out), (unsigned)x * (unsigned)sizeof(Part2<R>), own * (unsigned)sizeof(Part2<R>));
+            res_store(to_0, array_res(part_out), (unsigned)x * (unsigned)sizeof(Part2<R>), own * (unsigned)sizeof(Part2<R>));
         // no barrier here: the next staging overwrites ring slots that only this
         // plane's pull and collide read, before the exchange's barrier, and the
         // exchange rows are next written after the next staging's barrier

@@ -85,8 +85,10 @@ int launch(const LatticeView& v, const S& src, const D& dst, const Coeffs<typena
         case kSingleTYSmall: return launch_ty<S, D, kSingleTYSmall>(v, src, dst, c, fs);
         case kSingleTY: return launch_ty<S, D, kSingleTY>(v, src, dst, c, fs);
         case kSingleTYLarge: return launch_ty<S, D, kSingleTYLarge>(v, src, dst, c, fs);
+        case kSingleTYSplit:
+            if constexpr (D::kSplit) return launch_ty<S, D, kSingleTYSplit>(v, src, dst, c, fs);
     }
-    return set_error(LB_EINVAL, "one-read tile rows must be 4, 8 or 16");
+    return set_error(LB_EINVAL, "one-read tile rows outside the storage's choices");
 }
 
 // 32-bit byte offsets within the buffer resources.

@@ -75,8 +75,13 @@ __device__ __forceinline__ void pull_tile(const Geom& g, const S& src, unsigned 
         __syncthreads();
         const LeanRows rw = rows.at(cz);
         R t[Q], d[Q];
-        src.template values<W, TY>(g, rw, ln, rp, k, k1, k2, pre, t, d);
-        if constexpr (W && MV) add_moving_terms<S, TY>(g, src, rw, ln, rp, k1, yc, cz, t, d);
+        MovingTerms<R> mt;
+        if constexpr (W && MV) mt.template init<S, TY>(g, src, rw, ln, rp, k1);
+        src.template values<W, TY>(g, rw, ln, rp, k, k1, k2, pre, [&](int i, R ti, R di) {
+            if constexpr (W && MV) mt.add(g, i, rw, ln, yc, cz, ti, di);
+            t[i] = ti;
+            d[i] = di;
+        });
         recs.load(g, src, cz + 2, next);
         src.template fetch<W>(g, rows.at(min(cz + 1, g.nz - 1)), ln, pre);
         if (site_in) read((int)(rw.own() + ln.c0), t, d);

@@ -32,6 +32,8 @@
 // term by term alike, so a pure component (d_i = +-(w_i + t_i)) gives
 // phi = +-1 exactly, as in the collision.
 #pragma once
+#include <type_traits>
+
 #include "lb_fused.hpp"
 
 namespace lbm {
@@ -104,12 +106,23 @@ __host__ __device__ constexpr int dir_of(int cx, int cy, int cz) {
     return -1;
 }
 
-// Rows of the one-read tile (one site per thread and plane): 8, or 4 when
-// the LDS of 8 rows exceeds the workgroup's budget (FP64 with a wide halo),
-// or 16 (a 1024-thread workgroup, one per CU) when chosen by tile setting.
+// Rows of the one-read tile (one site per thread and plane); 12 in 16-bit
+// storage only, whose records leave no LDS for 16 with a near-contact halo.
 constexpr int kSingleTY = 8;
 constexpr int kSingleTYSmall = 4;
+constexpr int kSingleTYSplit = 12;
 constexpr int kSingleTYLarge = 16;
+// f(std::integral_constant<int, TY>) for a row count of the one-read tile.
+template <typename F>
+int with_rows(int TY, const F& f) {
+    switch (TY) {
+        case kSingleTYSmall: return f(std::integral_constant<int, kSingleTYSmall>());
+        case kSingleTY: return f(std::integral_constant<int, kSingleTY>());
+        case kSingleTYSplit: return f(std::integral_constant<int, kSingleTYSplit>());
+        case kSingleTYLarge: return f(std::integral_constant<int, kSingleTYLarge>());
+    }
+    return -1;
+}
 constexpr int kTileX = 64;             // columns of a tile: one wavefront per row
 constexpr size_t kLdsBytes = 163840;   // LDS of a workgroup on gfx950
 
