@@ -177,25 +177,69 @@ int phase_pass(const LatticeView& v, const Src& src) {
 // Two passes: the phase pass writes phi; the collide pass z-marches tiles
 // with phi in an LDS ring (or, when the ring does not fit, reads phi from
 // global memory site by site).
+// Tiles of the one-pass Shan-Chen step: one workgroup per CU (a workgroup pulls
+// two planes more than it writes; 128^3: 162 us with 16 planes, 174 with 8, 207
+// with 12, 236 with 32; 256^3: 1.07 ms with 128, 1.16 with 16; 32^3: 23 us with
+// 1 plane, 27 with 2).
+FusedShape sc_shape(const Geom& g) {
+    FusedShape fs;
+    fs.TY = kScRows;
+    fs.tiles_x = (g.nx + kTX - 1) / kTX;
+    fs.tiles_y = (g.ny + kScRows - 1) / kScRows;
+    const int tiles = fs.tiles_x * fs.tiles_y;
+    const int chunks = std::max(1, 256 / tiles);
+    fs.TZ = (g.nz + chunks - 1) / chunks;
+    fs.chunks = (g.nz + fs.TZ - 1) / fs.TZ;
+    fs.nblocks = tiles * fs.chunks;
+    return fs;
+}
+bool sc_fits(const Geom& g) {
+    return (uint64_t)kResArrays * sizeof(float) * (uint64_t)raw_stride((size_t)g.N) < ((uint64_t)1 << 32);
+}
+
 // Shan-Chen step (raw storage): density pass, then the collide tiles with the
 // density pairs in an LDS ring.
 template <typename R, typename Src, typename Dst>
-int sc_two_pass(const LatticeView& v, const Src& src, const Dst& dst, const Coeffs<R>& c, const StepEvents* t) {
+int sc_two_pass(const LatticeView& v, const Src& src, const Dst& dst, const Coeffs<R>& c) {
+    RhoPair<R>* rho2 = (RhoPair<R>*)v.phi;
+    hipLaunchKernelGGL((sc_density_kernel<R, Src>), dim3(grid_for(v.g.N)), dim3(kBlock), 0, v.stream, v.g, src, rho2);
+    int rc = launch_status("sc_density_kernel");
+    if (rc) return rc;
+    const FusedShape fs = tile_shape(*v.p, TILE_COLLIDE);
+    const size_t lds = sc_ring_bytes<R>(fs.TY, kTX);
+    hipLaunchKernelGGL((sc_collide_kernel<R, Src, Dst, kTX>), dim3(fs.nblocks), dim3(kBlock), lds, v.stream, v.g, src,
+                       dst, c, fs, (const RhoPair<R>*)rho2);
+    return launch_status("sc_collide_kernel");
+}
+
+template <typename R, typename Src, typename Dst, bool W>
+int sc_one_pass(const LatticeView& v, const Src& src, const Dst& dst, const Coeffs<R>& c) {
+    const FusedShape fs = sc_shape(v.g);
+    hipLaunchKernelGGL((sc_step_kernel<R, Src, Dst, W>), dim3(fs.nblocks), dim3(kTX * kScRows), sc_step_bytes<R>(),
+                       v.stream, v.g, src, LeanPairs<R>{(const R*)v.cur}, dst, c, fs);
+    return launch_status("sc_step_kernel");
+}
+
+// One pass for FP32 without moving walls within the 32-bit offsets of the row
+// loads; two passes otherwise.  (In FP64 the values of two sites and a third's in
+// flight exceed the registers, 440 B spill and 128^3 takes 636 us against 387; the
+// terms of moving walls spill too.)
+template <typename R, typename Src, typename Dst>
+int sc_step(const LatticeView& v, const Src& src, const Dst& dst, const Coeffs<R>& c, const StepEvents* t) {
     if constexpr (Src::ring || Dst::ring) {
         return set_error(LB_EINVAL, "the Shan-Chen model needs raw storage");
     } else {
         if (t) (void)hipEventRecord(t->ev[0], v.stream);
-        RhoPair<R>* rho2 = (RhoPair<R>*)v.phi;
-        hipLaunchKernelGGL((sc_density_kernel<R, Src>), dim3(grid_for(v.g.N)), dim3(kBlock), 0, v.stream, v.g, src,
-                           rho2);
-        int rc = launch_status("sc_density_kernel");
-        if (rc) return rc;
         if (t) (void)hipEventRecord(t->ev[1], v.stream);
-        const FusedShape fs = tile_shape(*v.p, TILE_COLLIDE);
-        const size_t lds = sc_ring_bytes<R>(fs.TY, kTX);
-        hipLaunchKernelGGL((sc_collide_kernel<R, Src, Dst, kTX>), dim3(fs.nblocks), dim3(kBlock), lds, v.stream, v.g,
-                           src, dst, c, fs, (const RhoPair<R>*)rho2);
-        rc = launch_status("sc_collide_kernel");
+        int rc = LB_OK;
+        bool one = false;
+        if constexpr (sizeof(R) == 4 && !Src::moving) {
+            one = sc_fits(v.g);
+            if (one)
+                rc = v.g.wx || v.g.wy || v.g.wz ? sc_one_pass<R, Src, Dst, true>(v, src, dst, c)
+                                                : sc_one_pass<R, Src, Dst, false>(v, src, dst, c);
+        }
+        if (!one) rc = sc_two_pass<R>(v, src, dst, c);
         if (t) (void)hipEventRecord(t->ev[2], v.stream);
         return rc;
     }
@@ -204,7 +248,7 @@ int sc_two_pass(const LatticeView& v, const Src& src, const Dst& dst, const Coef
 template <typename R, typename Src, typename Dst>
 int two_pass(const LatticeView& v, const Src& src, const Dst& dst, const Coeffs<R>& c, const StepEvents* t) {
     if (!v.phi) return set_error(LB_EINVAL, "two-pass step without a phase-field buffer");
-    if (v.p->model == LB_MODEL_SHAN_CHEN) return sc_two_pass<R>(v, src, dst, c, t);
+    if (v.p->model == LB_MODEL_SHAN_CHEN) return sc_step<R>(v, src, dst, c, t);
     if (t) (void)hipEventRecord(t->ev[0], v.stream);
     int rc = phase_pass<R>(v, src);
     if (rc) return rc;
@@ -366,8 +410,13 @@ FusedShape tile_shape(const lb_params& p, int kind) {
     fs.tiles_y = (p.ny + fs.TY - 1) / fs.TY;
     const int tiles = fs.tiles_x * fs.tiles_y;
     // the autotuner's choices for the 256^3 emulsion on MI355X: 16-plane chunks
-    // for the 16-bit phase pass and the raw-storage two-pass collide
-    if (tz <= 0 && (kind == TILE_PHASE || (kind == TILE_COLLIDE && !split_storage(p)))) tz = 16;
+    // for the 16-bit phase pass and the raw-storage two-pass collide, the latter
+    // shorter where that leaves less than 2048 tile rows (two-pass steps: 32^3
+    // FP32 91 -> 25 us, FP64 173 -> 31; 64^3 101 -> 37, 191 -> 57; 128^3 and
+    // larger take 16 planes, FP64 387 us against 404 with 8)
+    if (tz <= 0 && kind == TILE_PHASE) tz = 16;
+    if (tz <= 0 && kind == TILE_COLLIDE && !split_storage(p))
+        tz = (int)std::min<int64_t>(16, std::max<int64_t>(1, (int64_t)p.nz * tiles * fs.TY / 2048));
     if (tz <= 0) {
         // aim for 1024 workgroups, keeping chunks a few halos deep
         const int want_chunks = std::max(1, 1024 / std::max(1, tiles));
