@@ -23,11 +23,19 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
-# algorithmic bytes per site update, read + write: raw storage 2 components x
+# algorithmic bytes per site update, read + write: one-read steps of raw storage
+# 23 values (19 totals, phase, recolouring vector), two-pass steps 2 components x
 # 19 populations; 16-bit moment-split storage a 32-byte FP32 record plus 19
 # 16-bit deviations per site (the plain 16-bit form of the same state would
 # be 2 x 19 x 2 x 2 = 152 B)
-ALGO_BYTES = {0: 2 * 19 * 2 * 8, 1: 2 * 19 * 2 * 4, 2: 2 * (32 + 19 * 2), 3: 2 * (32 + 19 * 2)}
+ALGO_BYTES = {0: 2 * 23 * 8, 1: 2 * 23 * 4, 2: 2 * (32 + 19 * 2), 3: 2 * (32 + 19 * 2)}
+PAIR_BYTES = {0: 2 * 19 * 2 * 8, 1: 2 * 19 * 2 * 4}
+
+
+def algo_bytes(storage, kernel):
+    return PAIR_BYTES.get(storage, ALGO_BYTES[storage]) if kernel == 1 else ALGO_BYTES[storage]
+
+
 STORE_NAME = {0: "f64", 1: "f32", 2: "f16", 3: "bf16"}
 
 
@@ -356,9 +364,9 @@ def main():
         st = codes[name]
         r = gpu_variant(w, st, args.steps, args.warmup, stream, args.kernel)
         r["mlups"] = w.sites / (r["ms_per_step"] * 1e-3) / 1e6
-        r["algo_gbs"] = r["mlups"] * 1e6 * ALGO_BYTES[st] / 1e9
+        r["algo_gbs"] = r["mlups"] * 1e6 * algo_bytes(st, r["kernel"]) / 1e9
         # the tile kernel alone (pass_ms[1]) against its algorithmic bytes
-        r["tile_algo_gbs"] = ALGO_BYTES[st] * w.sites / (r["pass_ms"][1] * 1e-3) / 1e9
+        r["tile_algo_gbs"] = algo_bytes(st, r["kernel"]) * w.sites / (r["pass_ms"][1] * 1e-3) / 1e9
         results[name] = r
         log("%s: %.3f ms/step, %.0f MLUPS, %.0f GB/s algorithmic, passes %s"
             % (name, r["ms_per_step"], r["mlups"], r["algo_gbs"], r["pass_ms"]))
@@ -369,7 +377,8 @@ def main():
     # dominant kernel: the collide-and-stream pass (pass_ms[1]; pass_ms[0] is the
     # phase pass of two-pass steps or the phase assembly of one-read steps)
     dom_ms = head["pass_ms"][1]
-    achieved = ALGO_BYTES[st] * w.sites / (dom_ms * 1e-3) / 1e9
+    per_site = algo_bytes(st, head["kernel"])
+    achieved = per_site * w.sites / (dom_ms * 1e-3) / 1e9
     traffic = measured_traffic("collide_" + head_name, args.n)
     roof = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(achieved / HBM_PEAK_GBS, 4),
@@ -378,7 +387,7 @@ def main():
             "kernel": ("collide pass (z-marching fused_kernel, phase field from the phase pass)"
                        if head["kernel"] == 1 else
                        "one-read tile (lean_kernel; face-site phase field completed by assemble_kernel)"),
-            "algo_bytes_per_site": ALGO_BYTES[st], "sites_per_launch": w.sites,
+            "algo_bytes_per_site": per_site, "sites_per_launch": w.sites,
             "kernel_ms": round(dom_ms, 4)}
 
     copy_gbs = copy_bandwidth(stream)
@@ -390,7 +399,7 @@ def main():
         # (lb_pattern_ms): the ceiling of that pattern on this device
         from paper_2005_12764_amd import lb
         pat_ms = lb.lb_pattern_ms(dict(w.params, storage=W.F32), 20)
-        pat_gbs = ALGO_BYTES[st] * w.sites / (pat_ms * 1e-3) / 1e9
+        pat_gbs = per_site * w.sites / (pat_ms * 1e-3) / 1e9
         log("one-read access pattern without arithmetic: %.3f ms, %.0f GB/s" % (pat_ms, pat_gbs))
         roof["pattern_gbs"] = round(pat_gbs, 1)
         roof["frac_of_pattern"] = round(achieved / pat_gbs, 4)
