@@ -138,6 +138,8 @@ struct lb_t {
     int device;
     void* buf[2];      // post-collision populations, ping-pong
     void* pending;     // raw FP32 state of a 16-bit lattice before its first step
+    void* spare;       // its buffer afterwards, kept for a lattice whose state is set again
+    int raw_states;    // states set so far
     void* phi;         // phase field of the two-pass step (double for F64, float otherwise)
     void* part[2];     // phase sums and phase field of the one-read step, ping-pong
     int part_cur;      // part[part_cur] belongs to the current state ...
@@ -187,6 +189,30 @@ lbm::LatticeView view_of(lb_t* h) {
     return v;
 }
 
+// Buffer of a 16-bit lattice's raw state.  The first state's is given back after
+// the step that reads it, so a run holds its 16-bit buffers alone; a lattice whose
+// state is set again keeps it (lb_footprint_bytes counts it): an allocation and a
+// free of 770 MB per restart took 1 ms, and 19 ms after some 130 of them, besides
+// the wait for the step.
+int own_pending(lb_t* h) {
+    ++h->raw_states;
+    if (h->spare) {
+        h->pending = h->spare;
+        h->spare = nullptr;
+        return LB_OK;
+    }
+    return check_hip(hipMalloc(&h->pending, pop_bytes(LB_STORE_F32, (size_t)h->g.N)), "hipMalloc initial state");
+}
+void drop_pending(lb_t* h) {
+    if (h->raw_states > 1) {
+        h->spare = h->pending;  // (the stream orders the next state's writes after this one's reads)
+    } else {
+        (void)hipStreamSynchronize(h->stream);
+        (void)hipFree(h->pending);
+    }
+    h->pending = nullptr;
+}
+
 // The view that setting the state writes through: pair arrays in the current
 // buffer (16-bit lattices: in the pending one).
 lbm::LatticeView set_view_of(lb_t* h) {
@@ -200,6 +226,7 @@ void release(lb_t* h) {
     if (h->buf[0]) (void)hipFree(h->buf[0]);
     if (h->buf[1]) (void)hipFree(h->buf[1]);
     if (h->pending) (void)hipFree(h->pending);
+    if (h->spare) (void)hipFree(h->spare);
     if (h->phi) (void)hipFree(h->phi);
     if (h->part[0]) (void)hipFree(h->part[0]);
     if (h->part[1]) (void)hipFree(h->part[1]);
@@ -324,7 +351,7 @@ int lb_init_fields(lb_t* h, const void* rho_r, const void* rho_b, const void* u,
     // 16-bit lattices keep the initial state raw (FP32) until their first step.
     const bool split = h->p.storage >= LB_STORE_F16;
     if (split && !h->pending) {
-        int rc = check_hip(hipMalloc(&h->pending, pop_bytes(LB_STORE_F32, N)), "hipMalloc initial state");
+        int rc = own_pending(h);
         if (rc) return rc;
     }
     void *d_rr = nullptr, *d_rb = nullptr, *d_u = nullptr, *scratch = nullptr;
@@ -364,7 +391,7 @@ int lb_init_droplets(lb_t* h, const double* centres, const double* radii, int32_
     const size_t N = (size_t)h->g.N;
     const bool split = h->p.storage >= LB_STORE_F16;
     if (split && !h->pending) {
-        int rc = check_hip(hipMalloc(&h->pending, pop_bytes(LB_STORE_F32, N)), "hipMalloc initial state");
+        int rc = own_pending(h);
         if (rc) return rc;
     }
     double* tmp = nullptr;
@@ -403,12 +430,7 @@ static int advance(lb_t* h, const StepEvents* t, int* used) {
     const int kernel = (h->kernel == LB_KERNEL_FUSED && first16) ? LB_KERNEL_TWOPASS : h->kernel;
     int rc = launch_step(v, kernel, t);
     if (rc) return rc;
-    if (h->pending) {
-        // the first step consumed the raw initial state
-        (void)hipStreamSynchronize(h->stream);
-        (void)hipFree(h->pending);
-        h->pending = nullptr;
-    }
+    if (h->pending) drop_pending(h);  // the first step consumed the raw initial state
     h->cur ^= 1;
     h->steps++;
     h->fresh = false;
@@ -580,7 +602,7 @@ int lb_set_state(lb_t* h, const void* f, int32_t dtype, int32_t on_device) {
     const size_t bytes = 2 * Q * N * (dtype == LB_DTYPE_F64 ? 8 : 4);
     const bool split = h->p.storage >= LB_STORE_F16;
     if (split && !h->pending) {
-        int rc = check_hip(hipMalloc(&h->pending, pop_bytes(LB_STORE_F32, N)), "hipMalloc raw state");
+        int rc = own_pending(h);
         if (rc) return rc;
     }
     const void* in = f;
@@ -636,11 +658,7 @@ int lb_load_raw(lb_t* h, const void* src, int32_t on_device) {
     int rc = check_hip(hipMemcpyAsync(h->buf[h->cur], src, b, on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, h->stream), "copy raw state");
     if (!rc && !on_device) rc = check_hip(hipStreamSynchronize(h->stream), "sync");
     if (rc) return rc;
-    if (h->pending) {
-        (void)hipStreamSynchronize(h->stream);
-        (void)hipFree(h->pending);
-        h->pending = nullptr;
-    }
+    if (h->pending) drop_pending(h);
     h->initialised = true;
     h->fresh = false;
     h->pairs = true;
