@@ -203,6 +203,10 @@ int lb_moments(lb_t* h, void* rho_r, void* rho_b, void* mom, int32_t dtype, int3
  * (device outputs only), so that b calls over b consecutive steps give the
  * space-time block of B = b^4 values once divided by b.  Uses the handle's
  * phase-field scratch; allocates only when staging host outputs.
+ * Between moving walls phi is that of the populations with their wall terms, as
+ * lb_moments sums them.  (Until moving-wall lattices took the one-read step, the
+ * call returned blocks of a field that no step had written for them: K and phi of
+ * moving-wall lattices saved by such a library are not usable.)
  * Errors: LB_EINVAL (arguments), LB_ESTATE (before lb_init_fields). */
 int lb_korteweg(lb_t* h, double lambda, int32_t b, void* k_blocks, void* phi_blocks, int32_t dtype,
                 int32_t on_device, int32_t accumulate);
