@@ -173,7 +173,8 @@ int lb_step(lb_t* h, int32_t n);
  * blocks until the n steps are done.  kernel_ms (host, 3 values) receives the
  * mean milliseconds per step of: [0] the phase-field pass (two-pass) or the
  * phase-field assembly (one-read), [1] the collide-and-stream pass, [2] the
- * whole step. */
+ * whole step.  Shan-Chen lattices: [0] the density pass, an empty interval where
+ * the step takes one pass (FP32 without moving walls). */
 int lb_step_timed(lb_t* h, int32_t n, double kernel_ms[3]);
 
 /* Moments of the current state (Sec. 2, eq:eq2): rho_r, rho_b (N each) and the

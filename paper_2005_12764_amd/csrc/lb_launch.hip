@@ -200,11 +200,12 @@ bool sc_fits(const Geom& g) {
 // Shan-Chen step (raw storage): density pass, then the collide tiles with the
 // density pairs in an LDS ring.
 template <typename R, typename Src, typename Dst>
-int sc_two_pass(const LatticeView& v, const Src& src, const Dst& dst, const Coeffs<R>& c) {
+int sc_two_pass(const LatticeView& v, const Src& src, const Dst& dst, const Coeffs<R>& c, const StepEvents* t) {
     RhoPair<R>* rho2 = (RhoPair<R>*)v.phi;
     hipLaunchKernelGGL((sc_density_kernel<R, Src>), dim3(grid_for(v.g.N)), dim3(kBlock), 0, v.stream, v.g, src, rho2);
     int rc = launch_status("sc_density_kernel");
     if (rc) return rc;
+    if (t) (void)hipEventRecord(t->ev[1], v.stream);
     const FusedShape fs = tile_shape(*v.p, TILE_COLLIDE);
     const size_t lds = sc_ring_bytes<R>(fs.TY, kTX);
     hipLaunchKernelGGL((sc_collide_kernel<R, Src, Dst, kTX>), dim3(fs.nblocks), dim3(kBlock), lds, v.stream, v.g, src,
@@ -230,16 +231,17 @@ int sc_step(const LatticeView& v, const Src& src, const Dst& dst, const Coeffs<R
         return set_error(LB_EINVAL, "the Shan-Chen model needs raw storage");
     } else {
         if (t) (void)hipEventRecord(t->ev[0], v.stream);
-        if (t) (void)hipEventRecord(t->ev[1], v.stream);
         int rc = LB_OK;
         bool one = false;
         if constexpr (sizeof(R) == 4 && !Src::moving) {
             one = sc_fits(v.g);
-            if (one)
+            if (one) {
+                if (t) (void)hipEventRecord(t->ev[1], v.stream);  // (no pass before the collide pass)
                 rc = v.g.wx || v.g.wy || v.g.wz ? sc_one_pass<R, Src, Dst, true>(v, src, dst, c)
                                                 : sc_one_pass<R, Src, Dst, false>(v, src, dst, c);
+            }
         }
-        if (!one) rc = sc_two_pass<R>(v, src, dst, c);
+        if (!one) rc = sc_two_pass<R>(v, src, dst, c, t);
         if (t) (void)hipEventRecord(t->ev[2], v.stream);
         return rc;
     }
