@@ -166,7 +166,13 @@ int lb_init_droplets(lb_t* h, const double* centres, const double* radii, int32_
  * (Sec. 4, F_rep equation), the colour-gradient perturbation and recolouring
  * (or the Shan-Chen force of Sec. 2.1, eq. shanchen_force, per lb_params.model),
  * then streaming (Sec. 2, after eq:eq3) with periodic or bounce-back axes.
- * LB_ESTATE before lb_init_fields; LB_EDEVICE when a launch fails. */
+ * Steps may be captured into a graph (an even number, so that a replay starts where
+ * the last one ended).  Raw lattices whose steps read once hold pairs until the first
+ * step after a state was set: one whose steps or readings are captured before that
+ * step takes two-pass steps from then on; step first to capture the one-read step, and
+ * take an even number of steps after every state set between replays.  A 16-bit
+ * lattice's first step can be captured only in the graph that sets the state.
+ * LB_ESTATE before lb_init_fields, or for that step; LB_EDEVICE when a launch fails. */
 int lb_step(lb_t* h, int32_t n);
 
 /* As lb_step, timing every pass with HIP events on the handle's stream;

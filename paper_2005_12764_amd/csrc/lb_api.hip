@@ -154,12 +154,39 @@ struct lb_t {
     bool fresh;        // the state was set (init/import), no collision since: no wall terms
     bool packed;       // raw storage stepped with one read: steps write the packed form ...
     bool pairs;        // ... and the current state, set or loaded, still is in pair arrays
+    unsigned long long set_capture;  // graph capture the state was set in (0: in none)
     int kernel;        // LB_KERNEL_TWOPASS or LB_KERNEL_FUSED
     Coeffs<double> cd;
     Coeffs<float> cf;
 };
 
 namespace {
+
+// Graph capture the handle's stream is in, 0 for none (the legacy stream cannot be
+// captured).
+unsigned long long capture_of(const lb_t* h) {
+    if (!h->stream) return 0;
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    unsigned long long id = 0;
+    if (hipStreamGetCaptureInfo(h->stream, &status, &id) != hipSuccess) {
+        (void)hipGetLastError();
+        return 0;
+    }
+    return status == hipStreamCaptureStatusActive ? id : 0;
+}
+
+// A replay reads the state in the form it had when the call was captured.  Pair
+// arrays become the packed form with the first step after a state was set, so a
+// lattice one of whose calls is captured on pair arrays keeps them from then on: its
+// steps take two passes, which read and write pairs.  (Not where the same capture
+// sets the state: every replay then sets it again.)
+void keep_captured_form(lb_t* h) {
+    if (!h->packed || !h->pairs) return;
+    const unsigned long long id = capture_of(h);
+    if (!id || id == h->set_capture) return;
+    h->packed = false;
+    h->kernel = LB_KERNEL_TWOPASS;
+}
 
 lbm::LatticeView view_of(lb_t* h) {
     lbm::LatticeView v;
@@ -203,8 +230,9 @@ int own_pending(lb_t* h) {
     }
     return check_hip(hipMalloc(&h->pending, pop_bytes(LB_STORE_F32, (size_t)h->g.N)), "hipMalloc initial state");
 }
+// (nothing is waited for or freed under capture)
 void drop_pending(lb_t* h) {
-    if (h->raw_states > 1) {
+    if (h->raw_states > 1 || capture_of(h)) {
         h->spare = h->pending;  // (the stream orders the next state's writes after this one's reads)
     } else {
         (void)hipStreamSynchronize(h->stream);
@@ -374,6 +402,7 @@ int lb_init_fields(lb_t* h, const void* rho_r, const void* rho_b, const void* u,
     h->initialised = true;
     h->fresh = true;
     h->pairs = true;
+    h->set_capture = capture_of(h);
     h->part_valid = false;
     h->steps = 0;
     return LB_OK;
@@ -415,6 +444,7 @@ int lb_init_droplets(lb_t* h, const double* centres, const double* radii, int32_
     h->initialised = true;
     h->fresh = true;
     h->pairs = true;
+    h->set_capture = capture_of(h);
     h->part_valid = false;
     h->steps = 0;
     return LB_OK;
@@ -423,6 +453,10 @@ int lb_init_droplets(lb_t* h, const double* centres, const double* radii, int32_
 // One step of lattice h (events t may be null); `used` receives the kernel
 // that ran.
 static int advance(lb_t* h, const StepEvents* t, int* used) {
+    keep_captured_form(h);
+    const unsigned long long capture = h->pending ? capture_of(h) : 0;
+    if (capture && capture != h->set_capture)
+        return fail(LB_ESTATE, "the first step of a 16-bit lattice's state can be captured only with the call that sets it");
     LatticeView v = view_of(h);
     // the one-read step takes a 16-bit lattice's initial pair arrays through
     // 32-bit offsets of its own; beyond them that one step takes two passes
@@ -505,6 +539,7 @@ int lb_moments(lb_t* h, void* rho_r, void* rho_b, void* mom, int32_t dtype, int3
     if (dtype != LB_DTYPE_F64 && dtype != LB_DTYPE_F32) return fail(LB_EINVAL, "bad dtype");
     const size_t N = (size_t)h->g.N;
     const size_t es = dtype == LB_DTYPE_F64 ? 8 : 4;
+    keep_captured_form(h);
     LatticeView v = view_of(h);
     int rc = LB_OK;
     if (rho_r || rho_b || mom) {
@@ -550,6 +585,7 @@ int lb_korteweg(lb_t* h, double lambda, int32_t b, void* k_blocks, void* phi_blo
     if (!std::isfinite(lambda)) return fail(LB_EINVAL, "lambda must be finite");
     const size_t Nc = (size_t)(h->p.nx / b) * (h->p.ny / b) * (h->p.nz / b);
     const size_t es = dtype == LB_DTYPE_F64 ? 8 : 4;
+    keep_captured_form(h);
     LatticeView v = view_of(h);
     void* scratch = nullptr;
     if (!on_device) {
@@ -582,6 +618,7 @@ int lb_get_state(lb_t* h, void* f, int32_t dtype, int32_t on_device) {
         int rc = check_hip(hipMalloc(&out, bytes), "hipMalloc staging");
         if (rc) return rc;
     }
+    keep_captured_form(h);
     LatticeView v = view_of(h);
     int rc = launch_export(v, out, dtype);
     if (!rc && !on_device) {
@@ -626,6 +663,7 @@ int lb_set_state(lb_t* h, const void* f, int32_t dtype, int32_t on_device) {
     h->initialised = true;
     h->fresh = true;
     h->pairs = true;
+    h->set_capture = capture_of(h);
     h->part_valid = false;
     return LB_OK;
 }
@@ -642,6 +680,7 @@ int lb_save_raw(lb_t* h, void* dst, int32_t on_device) {
     const size_t b = pop_bytes(h->p.storage, (size_t)h->g.N);
     const void* from = h->buf[h->cur];
     int rc = LB_OK;
+    keep_captured_form(h);
     if (h->packed && !h->pairs) {
         // saved states are pair arrays: unpacked into the buffer the next step overwrites
         rc = launch_unpack(view_of(h), h->buf[h->cur ^ 1]);
@@ -662,6 +701,7 @@ int lb_load_raw(lb_t* h, const void* src, int32_t on_device) {
     h->initialised = true;
     h->fresh = false;
     h->pairs = true;
+    h->set_capture = capture_of(h);
     h->part_valid = false;
     return LB_OK;
 }
