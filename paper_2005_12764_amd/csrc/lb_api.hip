@@ -458,10 +458,10 @@ static int advance(lb_t* h, const StepEvents* t, int* used) {
     if (capture && capture != h->set_capture)
         return fail(LB_ESTATE, "the first step of a 16-bit lattice's state can be captured only with the call that sets it");
     LatticeView v = view_of(h);
-    // the one-read step takes a 16-bit lattice's initial pair arrays through
-    // 32-bit offsets of its own; beyond them that one step takes two passes
-    const bool first16 = h->pending && (uint64_t)40 * raw_stride((size_t)h->g.N) >= ((uint64_t)1 << 32);
-    const int kernel = (h->kernel == LB_KERNEL_FUSED && first16) ? LB_KERNEL_TWOPASS : h->kernel;
+    // a 16-bit lattice beyond the one-read step's 32-bit offsets that asked for it takes
+    // two passes from its initial state
+    const bool two = h->kernel == LB_KERNEL_FUSED && h->pending && !one_read_fits(h->p.storage, (size_t)h->g.N);
+    const int kernel = two ? LB_KERNEL_TWOPASS : h->kernel;
     int rc = launch_step(v, kernel, t);
     if (rc) return rc;
     if (h->pending) drop_pending(h);  // the first step consumed the raw initial state

@@ -95,6 +95,8 @@ int launch_lean_split(const LatticeView& v, const Coeffs<float>& c, const FusedS
 template <typename T>
 int launch_lean_first(const LatticeView& v, const Coeffs<T>& c, const FusedShape& fs);
 size_t lean_tile_lds(const lb_params& p, int TY);
+// The buffer offsets of the one-read step and of a state's first one fit 32 bits.
+bool one_read_fits(int storage, size_t N);
 // Pair arrays of the current packed state (a checkpoint's form) into f.
 int launch_unpack(const LatticeView& v, void* f);
 // Moments, export and totals of a packed or 16-bit state through marching tiles

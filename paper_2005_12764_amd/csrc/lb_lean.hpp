@@ -36,12 +36,13 @@ __device__ __forceinline__ int wave_uniform(int v) { return __builtin_amdgcn_rea
 
 // Values per buffer resource of the raw forms: the 19 arrays t_i as two
 // resources of 9 and 10 (a direction and its opposite in one), the 19 pair
-// arrays as four of up to five, so that a load or store is one buffer access
+// arrays as five of up to four, so that a load or store is one buffer access
 // with a scalar row offset and a per-lane column offset and needs no 64-bit
-// address arithmetic.  Needs 10 raw_stride(N) sizeof(T) < 2^32 (checked on the
-// host).
+// address arithmetic.  Needs 10 raw_stride(N) sizeof(T) < 2^32 for the totals and
+// 8 raw_stride(N) sizeof(T) < 2^32 for the pairs (checked on the host): the pairs of
+// every lattice whose 16-bit form fits its offsets (113 million sites) fit theirs.
 constexpr int kResArrays = 10;
-constexpr int kResPairs = kResArrays / 2;
+constexpr int kResPairs = 4;
 constexpr unsigned kRsrcWord3 = 0x00020000;  // raw 32-bit buffer on gfx9-family targets
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
@@ -349,15 +350,15 @@ struct LeanPairs {
     static constexpr int NC = 0;
     const T* f;
     struct Pre {};
-    // four resources of up to five arrays
+    // five resources of up to four arrays
     struct Res {
-        __amdgpu_buffer_rsrc_t r[4];
+        __amdgpu_buffer_rsrc_t r[5];
     };
     __device__ __forceinline__ Res res(unsigned N) const {
         const unsigned S = N + kRawPad;
         Res o;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) o.r[k] = array_res(f + (size_t)k * kResArrays * S);
+        for (int k = 0; k < 5; ++k) o.r[k] = array_res(f + (size_t)k * 2 * kResPairs * S);
         return o;
     }
     template <bool W>

@@ -96,6 +96,10 @@ template <typename T>
 bool raw_fits(size_t N) {
     return (uint64_t)kResArrays * sizeof(T) * (uint64_t)raw_stride(N) < ((uint64_t)1 << 32);
 }
+template <typename T>
+bool pairs_fit(size_t N) {
+    return (uint64_t)2 * kResPairs * sizeof(T) * (uint64_t)raw_stride(N) < ((uint64_t)1 << 32);
+}
 inline bool split_fits(size_t N) {
     return (uint64_t)32 * N < ((uint64_t)1 << 32) && (uint64_t)2 * Q * (uint64_t)dev_stride(N) < ((uint64_t)1 << 32);
 }
