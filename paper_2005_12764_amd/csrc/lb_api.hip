@@ -458,9 +458,11 @@ static int advance(lb_t* h, const StepEvents* t, int* used) {
     if (capture && capture != h->set_capture)
         return fail(LB_ESTATE, "the first step of a 16-bit lattice's state can be captured only with the call that sets it");
     LatticeView v = view_of(h);
-    // a 16-bit lattice beyond the one-read step's 32-bit offsets that asked for it takes
-    // two passes from its initial state
-    const bool two = h->kernel == LB_KERNEL_FUSED && h->pending && !one_read_fits(h->p.storage, (size_t)h->g.N);
+    // a lattice beyond the one-read step's 32-bit offsets that asked for it takes two
+    // passes where it can all the same: from a 16-bit lattice's initial state, and
+    // between moving walls once the state has been collided
+    const bool two = h->kernel == LB_KERNEL_FUSED && !one_read_fits(h->p.storage, (size_t)h->g.N) &&
+                     (h->pending || v.g.moving);
     const int kernel = two ? LB_KERNEL_TWOPASS : h->kernel;
     int rc = launch_step(v, kernel, t);
     if (rc) return rc;
@@ -468,7 +470,7 @@ static int advance(lb_t* h, const StepEvents* t, int* used) {
     h->cur ^= 1;
     h->steps++;
     h->fresh = false;
-    h->pairs = false;
+    h->pairs = h->packed && two;
     if (kernel == LB_KERNEL_FUSED) {
         h->part_cur ^= 1;
         h->part_valid = true;

@@ -41,3 +41,40 @@ def test_16_bit_job_near_the_limit_is_admitted():
     for a, b in zip(got, ref):
         assert float((a - b).abs().max()) <= 2e-4
     assert float(ref[0].amax()) > 0.9 and float(ref[1].amax()) > 0.9
+
+
+def test_moving_walls_beyond_the_limit_take_two_passes():
+    n = 484                                          # 113.4 million sites
+    p = W.base_params(n, n, n, bc=(0, 0, 1), storage=W.F16, tau_r=0.8, tau_b=0.8, A=0.005)
+    p["wall_velocity"] = ((0, 0, 0),) * 4 + ((-0.01, 0, 0), (0.01, 0, 0))
+    out = []
+    for kernel in (lb.KERNEL_FUSED, lb.KERNEL_TWOPASS):
+        with lb.Lattice(dict(p, kernel=kernel)) as L:
+            L.init_droplets(CENTRES, RADII).step(3)
+            out.append(_fields(lambda r, b: lb._check(lb.lib().lb_moments(L.h, r, b, None, lb.DTYPE_F32, 1, None)),
+                               (n, n, n)))
+    for a, b in zip(*out):
+        assert bool((a == b).all())
+
+
+def test_raw_moving_walls_beyond_the_limit_continue_a_saved_state():
+    import torch
+    n = 378                                          # 54.0 million sites, FP64
+    p = W.base_params(n, n, n, bc=(0, 0, 1), storage=W.F64, tau_r=0.8, tau_b=0.8, A=0.005)
+    p["wall_velocity"] = ((0, 0, 0),) * 4 + ((-0.01, 0, 0), (0.01, 0, 0))
+    out = []
+    with lb.Lattice(dict(p, kernel=lb.KERNEL_TWOPASS)) as L:
+        L.init_droplets(CENTRES, RADII).step(1)
+        image = torch.empty(L.state_bytes(), dtype=torch.uint8, device="cuda")
+        torch.cuda.synchronize()
+        lb._check(lb.lib().lb_save_raw(L.h, ctypes.c_void_p(image.data_ptr()), 1))
+        L.step(2)
+        out.append(_fields(lambda r, b: lb._check(lb.lib().lb_moments(L.h, r, b, None, lb.DTYPE_F32, 1, None)),
+                           (n, n, n)))
+    with lb.Lattice(dict(p, kernel=lb.KERNEL_FUSED)) as L:
+        lb._check(lb.lib().lb_load_raw(L.h, ctypes.c_void_p(image.data_ptr()), 1))
+        L.step(2)
+        out.append(_fields(lambda r, b: lb._check(lb.lib().lb_moments(L.h, r, b, None, lb.DTYPE_F32, 1, None)),
+                           (n, n, n)))
+    for a, b in zip(*out):
+        assert bool((a == b).all())
