@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cmath>
+#include <cstdint>
 #include <cstdio>
 #include <cstring>
 #include <new>
@@ -247,6 +248,16 @@ lbm::LatticeView set_view_of(lb_t* h) {
     lbm::LatticeView v = view_of(h);
     if (h->packed) v.pending = h->buf[h->cur];
     return v;
+}
+
+// Can a kernel on the handle's device store aligned pairs at dst?
+bool writable(const lb_t* h, const void* dst) {
+    hipPointerAttribute_t a;
+    if (hipPointerGetAttributes(&a, dst) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return a.type == hipMemoryTypeDevice && a.device == h->device && ((uintptr_t)dst & 15) == 0;
 }
 
 void release(lb_t* h) {
@@ -680,15 +691,19 @@ int lb_save_raw(lb_t* h, void* dst, int32_t on_device) {
     if (!h->initialised) return fail(LB_ESTATE, "no state yet");
     if (h->pending) return fail(LB_ESTATE, "16-bit lattice holds a raw initial state until its first step; use lb_get_state");
     const size_t b = pop_bytes(h->p.storage, (size_t)h->g.N);
-    const void* from = h->buf[h->cur];
+    void* from = h->buf[h->cur];
     int rc = LB_OK;
     keep_captured_form(h);
     if (h->packed && !h->pairs) {
-        // saved states are pair arrays: unpacked into the buffer the next step overwrites
-        rc = launch_unpack(view_of(h), h->buf[h->cur ^ 1]);
-        from = h->buf[h->cur ^ 1];
+        // saved states are pair arrays: unpacked where they go, or into the buffer the
+        // next step overwrites and copied from there
+        from = on_device && writable(h, dst) ? dst : h->buf[h->cur ^ 1];
+        rc = launch_unpack(view_of(h), from);
+    } else if (h->packed) {
+        // (a buffer that held packed states has values of theirs between its pair arrays)
+        rc = launch_clear_pads(view_of(h), from);
     }
-    if (!rc) rc = check_hip(hipMemcpyAsync(dst, from, b, on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, h->stream), "copy raw state");
+    if (!rc && from != dst) rc = check_hip(hipMemcpyAsync(dst, from, b, on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, h->stream), "copy raw state");
     if (!rc && !on_device) rc = check_hip(hipStreamSynchronize(h->stream), "sync");
     return rc;
 }

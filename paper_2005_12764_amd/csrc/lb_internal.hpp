@@ -99,6 +99,8 @@ size_t lean_tile_lds(const lb_params& p, int TY);
 bool one_read_fits(int storage, size_t N);
 // Pair arrays of the current packed state (a checkpoint's form) into f.
 int launch_unpack(const LatticeView& v, void* f);
+// Zeros between the pair arrays of f.
+int launch_clear_pads(const LatticeView& v, void* f);
 // Moments, export and totals of a packed or 16-bit state through marching tiles
 // (lb_pull.hip); taken = false: the state has another form, nothing was done.
 int pull_moments(const LatticeView& v, void* rr, void* rb, void* j, int dtype, bool& taken);

@@ -482,7 +482,7 @@ int launch_step(const LatticeView& v, int kernel, const StepEvents* t) {
 }
 
 int launch_unpack(const LatticeView& v, void* f) {
-    const unsigned grid = grid_for(v.g.N);
+    const unsigned grid = grid_for(v.g.N + kRawPad);
     const size_t N = (size_t)v.g.N;
     if (v.p->storage == LB_STORE_F64)
         hipLaunchKernelGGL(unpack_kernel<double>, dim3(grid), dim3(kBlock), 0, v.stream, v.g.N,
@@ -491,6 +491,15 @@ int launch_unpack(const LatticeView& v, void* f) {
         hipLaunchKernelGGL(unpack_kernel<float>, dim3(grid), dim3(kBlock), 0, v.stream, v.g.N,
                            pack_view<float>(v.cur, N), (float*)f);
     return launch_status("unpack_kernel");
+}
+
+int launch_clear_pads(const LatticeView& v, void* f) {
+    const size_t N = (size_t)v.g.N;
+    if (v.p->storage == LB_STORE_F64)
+        hipLaunchKernelGGL(clear_pads_kernel<double>, dim3(1), dim3(kRawPad * Q), 0, v.stream, N, (double*)f);
+    else
+        hipLaunchKernelGGL(clear_pads_kernel<float>, dim3(1), dim3(kRawPad * Q), 0, v.stream, N, (float*)f);
+    return launch_status("clear_pads_kernel");
 }
 
 // Initial state goes to raw storage: the current buffer for F64/F32, the
