@@ -148,7 +148,10 @@ int lb_create(const lb_params* params, void* hip_stream, lb_t** out);
 /* Set the initial state f^k_i = f^eq_i(rho_k, u) (Sec. 2, eq:equil).
  * rho_r, rho_b: N = nx*ny*nz component densities; u: 3N velocity (SoA) or
  * NULL for zero.  dtype: LB_DTYPE_*.  The densities must be >= 0 with
- * rho_r + rho_b > 0 (not checked on device pointers).  Resets the step count. */
+ * rho_r + rho_b > 0 (not checked on device pointers).  Resets the step count.
+ * A 16-bit lattice holds a state that was set in a raw FP32 buffer (152 B per site,
+ * counted by lb_footprint_bytes) until its first step; the buffer of the first state
+ * is given back then, those of states set later after 512 steps without another. */
 int lb_init_fields(lb_t* h, const void* rho_r, const void* rho_b, const void* u, int32_t dtype,
                    int32_t on_device);
 
@@ -223,7 +226,8 @@ int lb_korteweg(lb_t* h, double lambda, int32_t b, void* k_blocks, void* phi_blo
 int lb_get_state(lb_t* h, void* f, int32_t dtype, int32_t on_device);
 
 /* Import populations in the layout of lb_get_state (16-bit storage re-encodes
- * them).  Keeps the step count. */
+ * them, and holds them until the first step as lb_init_fields says).  Keeps the step
+ * count. */
 int lb_set_state(lb_t* h, const void* f, int32_t dtype, int32_t on_device);
 
 /* Raw storage of the current state (checkpoint): lb_state_bytes gives the

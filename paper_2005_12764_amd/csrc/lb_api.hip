@@ -141,6 +141,8 @@ struct lb_t {
     void* pending;     // raw FP32 state of a 16-bit lattice before its first step
     void* spare;       // its buffer afterwards, kept for a lattice whose state is set again
     int raw_states;    // states set so far
+    int spare_steps;   // steps taken since the spare buffer was last needed
+    bool spare_captured;  // a graph holds its address
     void* phi;         // phase field of the two-pass step (double for F64, float otherwise)
     void* part[2];     // phase sums and phase field of the one-read step, ping-pong
     int part_cur;      // part[part_cur] belongs to the current state ...
@@ -219,27 +221,48 @@ lbm::LatticeView view_of(lb_t* h) {
 
 // Buffer of a 16-bit lattice's raw state.  The first state's is given back after
 // the step that reads it, so a run holds its 16-bit buffers alone; a lattice whose
-// state is set again keeps it (lb_footprint_bytes counts it): an allocation and a
-// free of 770 MB per restart took 1 ms, and 19 ms after some 130 of them, besides
-// the wait for the step.
+// state is set again keeps it (lb_footprint_bytes counts it) until it has taken
+// kSpareSteps without: an allocation and a free of 770 MB per restart took 1 ms, and
+// 19 ms after some 130 of them, besides the wait for the step; 512 steps of that
+// lattice take over 100 ms.
+constexpr int kSpareSteps = 512;
 int own_pending(lb_t* h) {
-    ++h->raw_states;
     if (h->spare) {
         h->pending = h->spare;
         h->spare = nullptr;
-        return LB_OK;
+    } else {
+        const int rc =
+            check_hip(hipMalloc(&h->pending, pop_bytes(LB_STORE_F32, (size_t)h->g.N)), "hipMalloc initial state");
+        if (rc) return rc;
     }
-    return check_hip(hipMalloc(&h->pending, pop_bytes(LB_STORE_F32, (size_t)h->g.N)), "hipMalloc initial state");
+    ++h->raw_states;
+    return LB_OK;
 }
 // (nothing is waited for or freed under capture)
 void drop_pending(lb_t* h) {
     if (h->raw_states > 1 || capture_of(h)) {
         h->spare = h->pending;  // (the stream orders the next state's writes after this one's reads)
+        h->spare_steps = 0;
     } else {
         (void)hipStreamSynchronize(h->stream);
         (void)hipFree(h->pending);
     }
     h->pending = nullptr;
+}
+
+// After a step: gives the spare buffer back once it was not needed for long (never
+// where a replay may write it).
+void age_spare(lb_t* h) {
+    if (!h->spare || h->spare_captured || ++h->spare_steps < kSpareSteps || capture_of(h)) return;
+    (void)hipStreamSynchronize(h->stream);
+    (void)hipFree(h->spare);
+    h->spare = nullptr;
+}
+
+// A state was set: where it was captured, each replay sets it.
+void note_set(lb_t* h) {
+    h->set_capture = capture_of(h);
+    if (h->set_capture) h->spare_captured = true;
 }
 
 // The view that setting the state writes through: pair arrays in the current
@@ -413,7 +436,7 @@ int lb_init_fields(lb_t* h, const void* rho_r, const void* rho_b, const void* u,
     h->initialised = true;
     h->fresh = true;
     h->pairs = true;
-    h->set_capture = capture_of(h);
+    note_set(h);
     h->part_valid = false;
     h->steps = 0;
     return LB_OK;
@@ -455,7 +478,7 @@ int lb_init_droplets(lb_t* h, const double* centres, const double* radii, int32_
     h->initialised = true;
     h->fresh = true;
     h->pairs = true;
-    h->set_capture = capture_of(h);
+    note_set(h);
     h->part_valid = false;
     h->steps = 0;
     return LB_OK;
@@ -478,6 +501,7 @@ static int advance(lb_t* h, const StepEvents* t, int* used) {
     int rc = launch_step(v, kernel, t);
     if (rc) return rc;
     if (h->pending) drop_pending(h);  // the first step consumed the raw initial state
+    else age_spare(h);
     h->cur ^= 1;
     h->steps++;
     h->fresh = false;
@@ -676,7 +700,7 @@ int lb_set_state(lb_t* h, const void* f, int32_t dtype, int32_t on_device) {
     h->initialised = true;
     h->fresh = true;
     h->pairs = true;
-    h->set_capture = capture_of(h);
+    note_set(h);
     h->part_valid = false;
     return LB_OK;
 }
@@ -718,7 +742,7 @@ int lb_load_raw(lb_t* h, const void* src, int32_t on_device) {
     h->initialised = true;
     h->fresh = false;
     h->pairs = true;
-    h->set_capture = capture_of(h);
+    note_set(h);
     h->part_valid = false;
     return LB_OK;
 }
