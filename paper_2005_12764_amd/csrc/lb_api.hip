@@ -370,7 +370,7 @@ int lb_create(const lb_params* params, void* hip_stream, lb_t** out) {
         (rc = check_hip(hipMalloc(&h->phi, N * (h->p.storage == LB_STORE_F64 ? 8 : 4) *
                                                (h->p.model == LB_MODEL_SHAN_CHEN ? 2 : 1)),
                         "hipMalloc phase field")) ||
-        (rc = check_hip(hipMalloc((void**)&h->partial, sizeof(Neu) * NTOT * kTotalsBlocks), "hipMalloc partials")) ||
+        (rc = check_hip(hipMalloc((void**)&h->partial, sizeof(Neu) * NTOT * kPackTotalsBlocks), "hipMalloc partials")) ||
         (rc = check_hip(hipMalloc((void**)&h->dtot, sizeof(double) * 2 * NTOT), "hipMalloc totals"))) {
         release(h);
         return rc;

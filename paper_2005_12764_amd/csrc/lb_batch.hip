@@ -833,13 +833,13 @@ int lb_batch_moments(lb_batch_t* b, int32_t slot, void* rho_r, void* rho_b, void
     }
     if (totals) {
         // partials and totals live after the staging fields
-        const size_t need = 5 * N * 8 + sizeof(Neu) * NTOT * kTotalsBlocks + 2 * NTOT * sizeof(double) + 512;
+        const size_t need = 5 * N * 8 + sizeof(Neu) * NTOT * kPackTotalsBlocks + 2 * NTOT * sizeof(double) + 512;
         rc = ensure_staging(b, need);
         if (rc) return rc;
         char* base = (char*)b->staging + 5 * N * 8;
         base = (char*)(((uintptr_t)base + 255) & ~uintptr_t(255));
         Neu* partial = (Neu*)base;
-        double* dtot = (double*)(base + sizeof(Neu) * NTOT * kTotalsBlocks);
+        double* dtot = (double*)(base + sizeof(Neu) * NTOT * kPackTotalsBlocks);
         rc = launch_totals(v, partial, dtot);
         if (!rc) rc = bcheck(hipMemcpyAsync(totals, dtot, sizeof(double) * 2 * NTOT, hipMemcpyDeviceToHost, b->stream), "D2H totals");
         if (!rc) rc = bcheck(hipStreamSynchronize(b->stream), "sync");

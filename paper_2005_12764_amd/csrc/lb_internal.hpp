@@ -15,6 +15,10 @@ namespace lbm {
 // Blocks of the compensated-reduction kernel (fixed, so totals are bitwise
 // reproducible for a given lattice).
 constexpr int kTotalsBlocks = 512;
+// Most of the one that reads packed states site by site: as many as are resident at
+// once, four wavefronts per SIMD in FP32 (1x4096x4096 497 us, 560 with 512 blocks),
+// three off moving walls, two in FP64.  The partial sums' buffers hold as many.
+constexpr int kPackTotalsBlocks = 1024;
 
 // What a launch needs to know about one lattice.
 struct LatticeView {

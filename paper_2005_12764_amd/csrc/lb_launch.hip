@@ -613,7 +613,9 @@ int launch_droplets(hipStream_t st, const Geom& g, const double* cen, const doub
 }
 
 int launch_totals(const LatticeView& v, Neu* partial, double* dtot) {
-    int grid = std::min<int>(kTotalsBlocks, (int)grid_for(v.g.N));
+    const bool pack = v.packed && !v.pending;
+    const int fill = v.p->storage == LB_STORE_F64 ? 512 : (v.g.moving ? 768 : kPackTotalsBlocks);
+    int grid = std::min<int>(pack ? fill : kTotalsBlocks, (int)grid_for(v.g.N));
     bool taken = false;
     int rc = pull_totals(v, partial, grid, taken);
     if (!rc && !taken) rc = with_state(v, [&](auto rt, auto src, const auto&) {

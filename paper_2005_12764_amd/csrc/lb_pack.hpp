@@ -40,17 +40,95 @@ struct PackPop {
         t = R(v);
         d = R(cs);
     }
+    // The site's 19 values, for kernels whose consecutive lanes take consecutive
+    // sites: of the 19 source records a lane loads one per source row and takes those
+    // beside it from its neighbours' (lanes at the ends of a row or of the wavefront
+    // load theirs), and a value is addressed by one 32-bit offset.  Issue bound these
+    // readings: 1x2048x2048 FP32, totals 302 -> 154 us, moments 150 -> 118, export 292
+    // -> 248 against 19 record loads and 64-bit addresses (pair arrays: 152, 145, 247).
     template <typename R>
     __device__ __forceinline__ void pull(const Geom& g, int s, int x, int y, int z, R (&t)[Q], R (&d)[Q]) const {
+        if (MW || g.wx || g.wy || g.wz) pull_rows<true, R>(g, s, x, y, z, t, d);
+        else pull_rows<false, R>(g, s, x, y, z, t, d);
+    }
+    template <bool W, typename R>
+    __device__ __forceinline__ void pull_rows(const Geom& g, int s, int x, int y, int z, R (&t)[Q], R (&d)[Q]) const {
+#pragma clang fp contract(off)
+        using L = Lattice;
+        const int lane = threadIdx.x & 63;
+        const int xm = x == 0 ? g.nx - 1 : x - 1, xp = x == g.nx - 1 ? 0 : x + 1;
+        const bool first = lane == 0 || x == 0, last = lane == 63 || x == g.nx - 1;
+        const bool xlo = W && g.wx && x == 0, xhi = W && g.wx && x == g.nx - 1;
+        const Colour<T> own = colour(s);
 #pragma unroll
-        for (int i = 0; i < Q; ++i) {
-            int dir;
-            const int src = pull_source(g, i, x, y, z, s, dir);
-            pull_one<R>(i, src, dir, t[i], d[i]);
+        for (int row = 0; row < 9; ++row) {
+            const int e = row % 3 - 1, f = row / 3 - 1;  // c_y, c_z of the row's directions
+            bool beyond = false;
+            const int ys = e ? step_back(y, e, g.ny, g.wy, beyond) : y;
+            const int zs = f ? step_back(z, f, g.nz, g.wz, beyond) : z;
+            const int base = site_of(g, 0, ys, zs);
+            Colour<T> q[3] = {own, own, own};  // from the left, the own column, the right
+            if (e || f) q[1] = colour(W && beyond ? s : base + x);
+            if (!e || !f) {
+                q[0] = beside<0x138>(q[1]);
+                q[2] = beside<0x130>(q[1]);
+                if (first) q[0] = colour(base + xm);
+                if (last) q[2] = colour(base + xp);
+            }
+#pragma unroll
+            for (int cx = 1; cx >= -1; --cx) {
+                if (cx && e && f) continue;
+                const int i = dir_at(cx, e, f);
+                const bool refl = W && (beyond || (cx > 0 && xlo) || (cx < 0 && xhi));
+                // (of two runs of arrays, a direction and its opposite in one: a packed
+                // lattice is one whose 10 arrays span less than 2^32 bytes)
+                const int run = i < 9 ? 0 : 9;
+                const unsigned S = (unsigned)raw_stride(N);
+                const unsigned src = (unsigned)(base + (cx > 0 ? xm : (cx < 0 ? xp : x)));
+                const unsigned at = refl ? (unsigned)(L::opp[i] - run) * S + (unsigned)s : (unsigned)(i - run) * S + src;
+                const T v = *reinterpret_cast<const T*>(reinterpret_cast<const char*>(tot + (size_t)run * S) +
+                                                        (size_t)(at * (unsigned)sizeof(T)));
+                const Colour<T>& c = q[1 - cx];
+                t[i] = R(v);
+                d[i] = R(recoloured<T>(i, weight<T>(i) + v,
+                                       refl ? Colour<T>{own.phi, -own.sx, -own.sy, -own.sz} : c));
+            }
         }
         if constexpr (MW) {
-            if (g.moving) raw_wall_terms<R>(*this, g, s, x, y, z, t, d);
+            const bool ylo = g.wy && y == 0, yhi = g.wy && y == g.ny - 1, zlo = g.wz && z == 0, zhi = g.wz && z == g.nz - 1;
+            if (g.moving && (xlo || xhi || ylo || yhi || zlo || zhi)) {
+                const R ph = own_phase<R>(s);  // shares the walls' terms between the components
+#pragma unroll
+                for (int i = 1; i < Q; ++i) {
+                    const bool refl = (L::cx[i] > 0 && xlo) || (L::cx[i] < 0 && xhi) || (L::cy[i] > 0 && ylo) ||
+                                      (L::cy[i] < 0 && yhi) || (L::cz[i] > 0 && zlo) || (L::cz[i] < 0 && zhi);
+                    const R add = refl ? wall_term<R>(g, i, x, y, z) : R(0);
+                    t[i] = refl ? t[i] + add : t[i];
+                    d[i] = refl ? fma_of(add, ph, d[i]) : d[i];
+                }
+            }
         }
+    }
+    // the colour of the lane before (DPP 0x138) or after (0x130)
+    template <int DPP>
+    static __device__ __forceinline__ Colour<T> beside(const Colour<T>& q) {
+        return Colour<T>{shifted<DPP>(q.phi), shifted<DPP>(q.sx), shifted<DPP>(q.sy), shifted<DPP>(q.sz)};
+    }
+    template <int DPP>
+    static __device__ __forceinline__ T shifted(T v) {
+        if constexpr (sizeof(T) == 4) {
+            return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), DPP, 0xf, 0xf, true));
+        } else {
+            const long long b = __double_as_longlong(v);
+            const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffll), DPP, 0xf, 0xf, true);
+            const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), DPP, 0xf, 0xf, true);
+            return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+        }
+    }
+    static constexpr int dir_at(int cx, int cy, int cz) {
+        for (int i = 0; i < Q; ++i)
+            if (Lattice::cx[i] == cx && Lattice::cy[i] == cy && Lattice::cz[i] == cz) return i;
+        return -1;
     }
     // The site's own post-collision phase, summed as RawPop sums its pairs.
     template <typename R>

@@ -13,12 +13,36 @@ int status(const char* what) {
     return set_error(LB_EDEVICE, (std::string(what) + ": " + hipGetErrorString(e)).c_str());
 }
 
-// fn(policy) of the current state, or `otherwise` where the state is in pair
-// arrays or beyond the policies' 32-bit offsets.
+// Do tiles read this state sooner than a thread per site?  They read each record
+// once, but march planes and leave lanes beyond the lattice idle, so it depends on the
+// share of their lanes that are sites, and on the size.  16-bit states, whose decode
+// is long: from a quarter (16x512x512 fp16 moments 251 us against 625 site by site;
+// at an eighth 470 against 595, at a sixteenth it turns).  Raw states site by site
+// keep up with memory, and tiles save the records' traffic.  Moments and totals of
+// large lattices: from 0.7 (256^3 FP32 393 us against 442 and 375 against 555;
+// 80x458x458, 0.62, 591 against 447); smaller ones: moments from 0.8 without walls
+// (128x91x91 26 against 29, between walls 34 against 30), FP64 totals (64^3 45 against
+// 53).  Export is bound by its stores: from 0.9 (64x256x256 208 against 229;
+// 80x229x229 354 against 254).
+enum Reading { MOMENTS, EXPORT, TOTALS };
+bool tiles_pay(const LatticeView& v, Reading what) {
+    const bool split = v.p->storage >= LB_STORE_F16, f64 = v.p->storage == LB_STORE_F64;
+    const int rows = v.p->storage == LB_STORE_F32 ? pull_rows<LeanPack<float>>() : pull_rows<LeanPack<double>>();
+    auto share = [](int n, int T) { return double(n) / (double(T) * ((n + T - 1) / T)); };
+    const double used = share(v.g.nx, kTX) * share(v.g.ny, rows);
+    if (split) return used >= 0.25;
+    if (what == EXPORT) return v.g.N >= 1 << 20 && used >= 0.9;
+    if (v.g.N >= 1 << 21) return used >= 0.7;
+    if (what == TOTALS) return f64 && v.g.N >= 1 << 18 && used >= 0.8;
+    return v.g.N >= (f64 ? 1 << 18 : 1 << 19) && used >= 0.8 && !(v.g.wx || v.g.wy || v.g.wz);
+}
+
+// fn(policy) of the current state; taken = false where the state is in pair arrays,
+// beyond the policies' 32-bit offsets or read sooner site by site.
 template <typename Fn>
-int with_policy(const LatticeView& v, bool& taken, Fn&& fn) {
+int with_policy(const LatticeView& v, Reading what, bool& taken, Fn&& fn) {
     const size_t N = (size_t)v.g.N;
-    taken = !v.pending;
+    taken = !v.pending && tiles_pay(v, what);
     if (taken) switch (v.p->storage) {
             case LB_STORE_F64:
                 if ((taken = v.packed && lean_launch::raw_fits<double>(N))) return fn(lean_pack<double>(v.cur, N));
@@ -87,7 +111,7 @@ bool walls(const LatticeView& v) { return v.g.wx || v.g.wy || v.g.wz; }
 }  // namespace
 
 int pull_moments(const LatticeView& v, void* rr, void* rb, void* j, int dtype, bool& taken) {
-    return with_policy(v, taken, [&](auto src) {
+    return with_policy(v, MOMENTS, taken, [&](auto src) {
         if (dtype == LB_DTYPE_F64) return moments_of(v, src, (double*)rr, (double*)rb, (double*)j);
         return moments_of(v, src, (float*)rr, (float*)rb, (float*)j);
     });
@@ -97,7 +121,7 @@ int pull_moments(const LatticeView& v, void* rr, void* rb, void* j, int dtype, b
 // storage's arithmetic: those lattices keep the per-site kernels)
 int pull_export(const LatticeView& v, void* out, int dtype, bool& taken) {
     if ((taken = !v.g.moving) == false) return LB_OK;
-    return with_policy(v, taken, [&](auto src) {
+    return with_policy(v, EXPORT, taken, [&](auto src) {
         using S = decltype(src);
         if (dtype == LB_DTYPE_F64)
             return walls(v) ? run_export<S, true>(v, src, (double*)out) : run_export<S, false>(v, src, (double*)out);
@@ -107,7 +131,7 @@ int pull_export(const LatticeView& v, void* out, int dtype, bool& taken) {
 
 int pull_totals(const LatticeView& v, Neu* partial, int& blocks, bool& taken) {
     if ((taken = !v.g.moving) == false) return LB_OK;
-    return with_policy(v, taken, [&](auto src) {
+    return with_policy(v, TOTALS, taken, [&](auto src) {
         using S = decltype(src);
         return walls(v) ? run_totals<S, true>(v, src, partial, blocks) : run_totals<S, false>(v, src, partial, blocks);
     });

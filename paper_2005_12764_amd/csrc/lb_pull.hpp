@@ -1,9 +1,10 @@
 // lb_pull.hpp -- the post-streaming populations of a packed or 16-bit state,
-// handed site by site to a reader: moments, export, totals.
+// handed site by site to a reader: moments, export, totals, where tiles fill their
+// lanes (lb_pull.hip has the rule).
 //
 // A site's 19 values need the records of its 19 source sites.  Gathered per
-// site they cost 19 record reads from L2 (256^3 fp16: 2.38 ms for the moments,
-// more than two steps); here tiles march a z-chunk with the records of planes
+// site they cost 16-bit states 19 record reads from L2 (256^3 fp16: 2.38 ms for the
+// moments, more than two steps); here tiles march a z-chunk with the records of planes
 // z - 1, z, z + 1 in an LDS ring, as the step's tiles do, so that each value is
 // read once: 112 B per site and the fields written for FP32 moments.  Four ring
 // slots, so that one barrier per plane is enough: a slot is written two planes
