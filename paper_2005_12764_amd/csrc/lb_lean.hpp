@@ -35,8 +35,8 @@ namespace lbm {
 __device__ __forceinline__ int wave_uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
 // Values per buffer resource of the raw forms: the 19 arrays t_i as two
-// resources of 9 and 10 (a direction and its opposite in one), the 19 pair
-// arrays as five of up to four, so that a load or store is one buffer access
+// resources of 9 and 10, the 19 pair arrays as five of up to four (a direction and its
+// opposite in one), so that a load or store is one buffer access
 // with a scalar row offset and a per-lane column offset and needs no 64-bit
 // address arithmetic.  Needs 10 raw_stride(N) sizeof(T) < 2^32 for the totals and
 // 8 raw_stride(N) sizeof(T) < 2^32 for the pairs (checked on the host): the pairs of
@@ -225,10 +225,15 @@ struct LeanRowSet {
 };
 // Offsets of direction i's source value: site = row (scalar) + column (lane),
 // in array a.  Off a y or z wall the wavefront reads the opposite direction of
-// its own row; with x walls the lanes next to one do (W only).
+// its own row; off an x wall the lanes next to it do.  Lattices with walls (W) take
+// the lane offsets of c_x != 0 whether x is walled or not: behind a branch, the loads
+// of either side were waited for one by one (256x256x128 FP32 between walls on every
+// axis, 8 rows: 773 us a step against 489).  BRANCH keeps the branch, for tiles whose
+// registers spill either way (FP64 between moving walls with a near-contact halo:
+// 1140 us without it, 1038 with it).
 //   load(a, row, col): the value at that row and column of array a
 //   load_at(site_and_array offset per lane)
-template <bool W, typename Load, typename LoadLane>
+template <bool W, bool BRANCH, typename Load, typename LoadLane>
 __device__ __forceinline__ void source_of(int i, const LeanRows& rw, const LeanLane& ln, const Load& load,
                                           const LoadLane& load_lane) {
     using L = Lattice;
@@ -237,7 +242,7 @@ __device__ __forceinline__ void source_of(int i, const LeanRows& rw, const LeanL
         const int a = bb ? L::opp[i] : i;
         const unsigned row = bb ? rw.own() : rw.from(i);
         const unsigned col = bb ? ln.c0 : ln.col(i);
-        if (L::cx[i] != 0 && ln.wx) load_lane(a, row, col, L::opp[i], rw.own(), ln.c0, ln.beyond(i));
+        if (L::cx[i] != 0 && (!BRANCH || ln.wx)) load_lane(a, row, col, L::opp[i], rw.own(), ln.c0, ln.beyond(i));
         else load(a, row, col);
     } else {
         load(i, rw.from(i), ln.col(i));
@@ -350,18 +355,24 @@ struct LeanPairs {
     static constexpr int NC = 0;
     const T* f;
     struct Pre {};
-    // five resources of up to four arrays
+    // five resources of up to four arrays: 0-2, 3-6, ... 15-18
     struct Res {
         __amdgpu_buffer_rsrc_t r[5];
     };
+    static __device__ __forceinline__ constexpr int part(int i) { return (i + 1) / kResPairs; }
+    static __device__ __forceinline__ constexpr int first(int k) { return k == 0 ? 0 : kResPairs * k - 1; }
+    // offset of a site in array i of its resource
+    static __device__ __forceinline__ unsigned off(int i, unsigned S, unsigned site) {
+        return ((unsigned)(i - first(part(i))) * S + site) * 2u * (unsigned)sizeof(T);
+    }
     __device__ __forceinline__ Res res(unsigned N) const {
         const unsigned S = N + kRawPad;
         Res o;
 #pragma unroll
-        for (int k = 0; k < 5; ++k) o.r[k] = array_res(f + (size_t)k * 2 * kResPairs * S);
+        for (int k = 0; k < 5; ++k) o.r[k] = array_res(f + (size_t)first(k) * 2 * S);
         return o;
     }
-    template <bool W>
+    template <bool W, bool BR>
     __device__ __forceinline__ void fetch(const Geom&, const LeanRows&, const LeanLane&, Pre&) const {}
 
     // The own post-collision phase from the pairs of the site itself.
@@ -375,7 +386,7 @@ struct LeanPairs {
 #pragma unroll
         for (int j = 0; j < Q; ++j) {
             T tj, dj;
-            res_load_pair(tj, dj, rs.r[j / kResPairs], ln.c0 * SZ, ((unsigned)(j % kResPairs) * S + own) * SZ);
+            res_load_pair(tj, dj, rs.r[part(j)], ln.c0 * SZ, off(j, S, own));
             st += weight<T>(j) + tj;
             sd += dj;
         }
@@ -390,19 +401,16 @@ struct LeanPairs {
         constexpr unsigned SZ = 2 * (unsigned)sizeof(T);
         const unsigned S = (unsigned)g.N + kRawPad;
 #pragma unroll
-        for (int i = 0; i < Q; ++i) {
-            // (a direction and its opposite may lie in different resources)
-            auto off = [&](int a, unsigned row) { return ((unsigned)(a % kResPairs) * S + row) * SZ; };
-            const int o = Lattice::opp[i];
-            bool bb = false;
-            if constexpr (W) bb = rw.beyond(i);
-            if (bb) res_load_pair(t[i], d[i], rs.r[o / kResPairs], ln.c0 * SZ, off(o, rw.own()));
-            else res_load_pair(t[i], d[i], rs.r[i / kResPairs], ln.col(i) * SZ, off(i, rw.from(i)));
-            if constexpr (W) {
-                if (Lattice::cx[i] != 0 && ln.beyond(i))
-                    res_load_pair(t[i], d[i], rs.r[o / kResPairs], ln.c0 * SZ, off(o, rw.own()));
-            }
-        }
+        for (int i = 0; i < Q; ++i)
+            source_of<W, false>(
+                i, rw, ln,
+                [&](int a, unsigned row, unsigned col) {
+                    res_load_pair(t[i], d[i], rs.r[part(i)], col * SZ, off(a, S, row));
+                },
+                [&](int a, unsigned row, unsigned col, int o, unsigned own, unsigned c0, bool refl) {
+                    res_load_pair(t[i], d[i], rs.r[part(i)],
+                                  refl ? off(o, S, own) + c0 * SZ : off(a, S, row) + col * SZ, 0);
+                });
 #pragma unroll
         for (int i = 0; i < Q; ++i) visit(i, t[i], d[i]);
     }
@@ -432,7 +440,7 @@ struct LeanPack {
         return Res{{array_res(tot), array_res(tot + (size_t)kFirst * (N + kRawPad))}};
     }
     __device__ __forceinline__ __amdgpu_buffer_rsrc_t rec_res() const { return array_res(rec); }
-    template <bool W>
+    template <bool W, bool BR>
     __device__ __forceinline__ void fetch(const Geom& g, const LeanRows& rw, const LeanLane& ln, Pre& p) const {
         const Res rs = res((unsigned)g.N);
         const unsigned S = (unsigned)g.N + kRawPad;
@@ -441,7 +449,7 @@ struct LeanPack {
 #pragma unroll
         for (int i = 0; i < Q; ++i) {
             if (i == kFirst) at = 0;
-            source_of<W>(
+            source_of<W, BR>(
                 i, rw, ln,
                 [&](int a, unsigned row, unsigned col) {
                     if constexpr (W)
@@ -590,7 +598,7 @@ struct LeanSplit {
         return ((unsigned)i * S + site) * 2u;
     }
     __device__ __forceinline__ __amdgpu_buffer_rsrc_t rec_res() const { return array_res(rec); }
-    template <bool W>
+    template <bool W, bool BR>
     __device__ __forceinline__ void fetch(const Geom& g, const LeanRows& rw, const LeanLane& ln, Pre& p) const {
         const __amdgpu_buffer_rsrc_t rd = array_res(dev);
         const unsigned S = (unsigned)g.N + kDevPad;
@@ -598,7 +606,7 @@ struct LeanSplit {
         asm volatile("" : "+s"(step));
 #pragma unroll
         for (int i = 0; i < Q; ++i) {
-            source_of<W>(
+            source_of<W, BR>(
                 i, rw, ln,
                 [&](int a, unsigned row, unsigned col) {
                     p.dv[i] = __builtin_amdgcn_raw_buffer_load_b16(rd, col * 2u, W ? off(a, S, row) : at + 2u * row, 0);
@@ -847,6 +855,7 @@ __device__ __forceinline__ void lean_tile(const Geom& g, const S& src, const D& 
     constexpr int TX = kTileX, NT = TX * TY;
     constexpr int LX = TX + 2 * H, LY = TY + 2 * H, NP = 2 * H + 1, PLANE = LY * LX;
     constexpr int NCA = S::NC > 0 ? S::NC : 1;
+    constexpr bool BR = MV && H > 1 && sizeof(R) == 8;
     R* const ring = reinterpret_cast<R*>(lds);
     const RecPlanes<C, NCA, TY> rp{reinterpret_cast<C*>(lds + Lds::phi)};
     R* const xch = reinterpret_cast<R*>(lds + Lds::phi + Lds::rec);
@@ -922,7 +931,7 @@ __device__ __forceinline__ void lean_tile(const Geom& g, const S& src, const D& 
         load_phi(za + H, st);
         recs.load(g, src, za + 1, st.rec);
         const LeanRows rw = rows.at(za);
-        src.template fetch<W>(g, rw, ln, pre);
+        src.template fetch<W, BR>(g, rw, ln, pre);
 #pragma unroll
         for (int k = 0; k < 2 * H; ++k) put_phi(k, s[k]);
         recs.put(rp, 0, s[0].rec);
@@ -983,7 +992,7 @@ __device__ __forceinline__ void lean_tile(const Geom& g, const S& src, const D& 
             load_phi(cz + 1 + H, st);
             recs.load(g, src, cz + 2, st.rec);
             const LeanRows rn = rows.at(zn);
-            src.template fetch<W>(g, rn, ln, pre);
+            src.template fetch<W, BR>(g, rn, ln, pre);
         }
         SiteTotals<R> tot;
         collide_totals<R>(t, m, gx, gy, gz, Fx, Fy, Fz, c, tot);

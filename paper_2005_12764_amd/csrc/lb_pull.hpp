@@ -65,7 +65,7 @@ __device__ __forceinline__ void pull_tile(const Geom& g, const S& src, unsigned 
         recs.load(g, src, za - 1, a);
         recs.load(g, src, za, b);
         recs.load(g, src, za + 1, next);
-        src.template fetch<W>(g, rows.at(za), ln, pre);
+        src.template fetch<W, false>(g, rows.at(za), ln, pre);
         recs.put(rp, 0, a);
         recs.put(rp, 1, b);
     }
@@ -84,7 +84,7 @@ __device__ __forceinline__ void pull_tile(const Geom& g, const S& src, unsigned 
             d[i] = di;
         });
         recs.load(g, src, cz + 2, next);
-        src.template fetch<W>(g, rows.at(min(cz + 1, g.nz - 1)), ln, pre);
+        src.template fetch<W, false>(g, rows.at(min(cz + 1, g.nz - 1)), ln, pre);
         if (site_in) read((int)(rw.own() + ln.c0), t, d);
     }
 }
