@@ -323,8 +323,10 @@ static bool single_rows_fit(const lb_params& p, int ty) {
 // max(a + b w, f w) with w wavefronts per SIMD (a + b: the latency of a row that
 // nothing overlaps, f: its share of issue and memory); the assembly takes 8 us,
 // or 9 and 17 ns per thousand face sites.  Fitted to 360 shapes of lattices from
-// 32^3 to 384^3 in each storage, of which it finds one within 7% of the best
-// (256^3 FP32: 757 us with 16 rows and 64 planes, 793 with 8 rows and 32, 1170
+// 32^3 to 384^3 in each storage, of which it finds one within 7% of the best; over 14
+// lattices from 32^3 to 256x256x128, near-contact ranges 0, 2, 3 and 4 and walls on
+// two and three axes, its choice is 1.5% above the best on average at rest, 1 to 3%
+// between moving walls, at most 34% (256^3 FP32: 757 us with 16 rows and 64 planes, 793 with 8 rows and 32, 1170
 // with 16 rows and 128, half the CUs; 384^3 bf16: 2.21 ms with 12 rows and 48
 // planes, 2.61 with 8 rows; 256^3 fp16: 793 us with 12 rows, 833 with 8; 128^3
 // FP64: 220 us with 8 rows and 16 planes, 273 with 4; 64^3 FP32: 32 us with 2
@@ -335,7 +337,8 @@ static double single_cost(const lb_params& p, int TY, int TZ) {
     const double s = f64 ? 3.4 : (split ? 7.9 : 5.5), s1 = f64 ? 3.3 : (split ? 0.3 : 0.6);
     const double a = f64 ? 3.4 : (split ? 1.9 : 3.1), b = f64 ? 3.2 : (split ? 1.65 : 1.0);
     const double f = f64 ? 3.0 : (split ? 1.2 : 2.4), scale = walls ? 1.2 : 1.0;
-    const int waves = f64 ? 2 : (split || walls ? 3 : 4);  // a SIMD holds, by registers
+    // a SIMD holds, by registers
+    const int waves = f64 || make_geom(p).moving ? 2 : (split || walls ? 3 : 4);
     const int hold =
         std::max(1, std::min((int)(kLdsBytes / tile_lds(p, TILE_SINGLE, TY)), waves * 4 / TY));
     const double tiles = double((p.nx + kTX - 1) / kTX) * ((p.ny + TY - 1) / TY);
@@ -353,14 +356,17 @@ static double single_cost(const lb_params& p, int TY, int TZ) {
 }
 
 // Rows and planes of the one-read step nothing else was asked for: the least
-// estimated step over the rows a storage runs without spilling (16 of periodic
-// FP32, 12 of 16 bits, 8 and 4 of all) and the plane counts that divide the
-// lattice into equal chunks.
+// estimated step over the rows that measured best somewhere (16 of FP32 unless walls
+// move, 12 of 16 bits, 8 and 4 of all) and the plane counts that divide the lattice
+// into equal chunks.  Some of them spill and are worth it: 16 rows of FP32 between
+// walls at rest 8 to 24 B a lane (256x256x128 421 us, 489 with 8 rows; moving walls
+// 220 B, 646 us against 563 with 8), 12 rows of 16 bits between moving walls 56 B
+// (541 us against 564), 8 rows of FP64 there 72 to 104 B (1024 us, 1200 with 4).
 static void single_auto(const lb_params& p, int ty_wanted, int tz_wanted, int& ty, int& tz) {
-    const bool walls = p.bc[0] || p.bc[1] || p.bc[2];
+    const bool moving = make_geom(p).moving;
     auto offered = [&](int r) {
         if (r == kSingleTYSplit) return split_storage(p);
-        return r != kSingleTYLarge || (p.storage == LB_STORE_F32 && !walls);
+        return r != kSingleTYLarge || (p.storage == LB_STORE_F32 && !moving);
     };
     double best = -1.0;
     for (int r : {kSingleTY, kSingleTYSmall, kSingleTYSplit, kSingleTYLarge}) {
