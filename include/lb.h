@@ -69,8 +69,9 @@ extern "C" {
 #define LB_STORE_BF16 3 /* as LB_STORE_F16 with bf16 deviations (no scale) */
 
 /* Kernel selection for lb_step. */
-#define LB_KERNEL_AUTO 0    /* the one-read step, except (two-pass) for the Shan-Chen model
-                               and lattices too large for its 32-bit buffer offsets */
+#define LB_KERNEL_AUTO 0    /* the one-read step, except (two-pass) for the Shan-Chen model,
+                               lattices too large for its 32-bit buffer offsets and some
+                               FP64 ones between moving walls with the widest probe */
 #define LB_KERNEL_TWOPASS 1 /* phase-field pass, then collide-and-stream pass */
 #define LB_KERNEL_FUSED 2   /* one-read step: the collide-and-stream tiles also gather the
                                next phase field's sums, a light pass adds the terms

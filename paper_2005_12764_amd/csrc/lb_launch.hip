@@ -449,6 +449,15 @@ int choose_kernel(const lb_params& p) {
     const bool small =
         (uint64_t)kResArrays * real_size(p) * (uint64_t)raw_stride((size_t)p.nx * p.ny * p.nz) < ((uint64_t)1 << 32);
     if (!fits || !small || p.model != LB_MODEL_COLOUR_GRADIENT) return LB_KERNEL_TWOPASS;
+    // FP64 between moving walls with the widest near-contact halo has tiles of 4 rows
+    // and one wavefront per SIMD left: two passes are faster where a tenth of the lanes
+    // or more lie beyond the lattice (30x100x100 82 us against 124, 201x77x59 203
+    // against 226; 128^3 440 against 372), and on large lattices with an x wall too
+    // (512x128x64 874 against 947; 128^3 545 against 491)
+    const double lanes = double(p.nx) / (kTX * ((p.nx + kTX - 1) / kTX)), sites = double(p.nx) * p.ny * p.nz;
+    if (p.storage == LB_STORE_F64 && tile_halo(p) > LB_MAX_NC_RANGE && make_geom(p).moving &&
+        (lanes < 0.9 || (p.bc[0] && sites >= 1 << 22)))
+        return LB_KERNEL_TWOPASS;
     return LB_KERNEL_FUSED;
 }
 
