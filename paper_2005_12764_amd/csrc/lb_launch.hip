@@ -174,13 +174,9 @@ int phase_pass(const LatticeView& v, const Src& src) {
     return launch_status("phase_kernel");
 }
 
-// Two passes: the phase pass writes phi; the collide pass z-marches tiles
-// with phi in an LDS ring (or, when the ring does not fit, reads phi from
-// global memory site by site).
 // Tiles of the one-pass Shan-Chen step: one workgroup per CU (a workgroup pulls
 // two planes more than it writes; 128^3: 162 us with 16 planes, 174 with 8, 207
-// with 12, 236 with 32; 256^3: 1.07 ms with 128, 1.16 with 16; 32^3: 23 us with
-// 1 plane, 27 with 2).
+// with 12, 236 with 32; 256^3: 1.07 ms with 128, 1.16 with 16).
 FusedShape sc_shape(const Geom& g) {
     FusedShape fs;
     fs.TY = kScRows;
@@ -193,8 +189,13 @@ FusedShape sc_shape(const Geom& g) {
     fs.nblocks = tiles * fs.chunks;
     return fs;
 }
-bool sc_fits(const Geom& g) {
-    return (uint64_t)kResArrays * sizeof(float) * (uint64_t)raw_stride((size_t)g.N) < ((uint64_t)1 << 32);
+// Does one pass beat two?  Within the 32-bit offsets of its row loads, where chunks are
+// three planes or more (48^3 two planes: 22 us against 17 with two passes, 512x512x1
+// 33 against 26, 64^3 26 either way) and six lanes in ten are sites (8x256x256 173
+// against 141, 33x154x225 132 against 122, 40x160x160 98 against 113).
+bool sc_one(const Geom& g) {
+    const bool fits = (uint64_t)kResArrays * sizeof(float) * (uint64_t)raw_stride((size_t)g.N) < ((uint64_t)1 << 32);
+    return fits && sc_shape(g).TZ >= 3 && 10 * g.nx >= 6 * kTX * ((g.nx + kTX - 1) / kTX);
 }
 
 // Shan-Chen step (raw storage): density pass, then the collide tiles with the
@@ -221,8 +222,7 @@ int sc_one_pass(const LatticeView& v, const Src& src, const Dst& dst, const Coef
     return launch_status("sc_step_kernel");
 }
 
-// One pass for FP32 without moving walls within the 32-bit offsets of the row
-// loads; two passes otherwise.  (In FP64 the values of two sites and a third's in
+// One pass for FP32 without moving walls where it pays; two passes otherwise.  (In FP64 the values of two sites and a third's in
 // flight exceed the registers, 440 B spill and 128^3 takes 636 us against 387; the
 // terms of moving walls spill too.)
 template <typename R, typename Src, typename Dst>
@@ -234,7 +234,7 @@ int sc_step(const LatticeView& v, const Src& src, const Dst& dst, const Coeffs<R
         int rc = LB_OK;
         bool one = false;
         if constexpr (sizeof(R) == 4 && !Src::moving) {
-            one = sc_fits(v.g);
+            one = sc_one(v.g);
             if (one) {
                 if (t) (void)hipEventRecord(t->ev[1], v.stream);  // (no pass before the collide pass)
                 rc = v.g.wx || v.g.wy || v.g.wz ? sc_one_pass<R, Src, Dst, true>(v, src, dst, c)
@@ -247,6 +247,9 @@ int sc_step(const LatticeView& v, const Src& src, const Dst& dst, const Coeffs<R
     }
 }
 
+// Two passes: the phase pass writes phi; the collide pass z-marches tiles
+// with phi in an LDS ring (or, when the ring does not fit, reads phi from
+// global memory site by site).
 template <typename R, typename Src, typename Dst>
 int two_pass(const LatticeView& v, const Src& src, const Dst& dst, const Coeffs<R>& c, const StepEvents* t) {
     if (!v.phi) return set_error(LB_EINVAL, "two-pass step without a phase-field buffer");
@@ -421,10 +424,14 @@ FusedShape tile_shape(const lb_params& p, int kind) {
     // for the 16-bit phase pass and the raw-storage two-pass collide, the latter
     // shorter where that leaves less than 2048 tile rows (two-pass steps: 32^3
     // FP32 91 -> 25 us, FP64 173 -> 31; 64^3 101 -> 37, 191 -> 57; 128^3 and
-    // larger take 16 planes, FP64 387 us against 404 with 8)
+    // larger take 16 planes, FP64 387 us against 404 with 8).  The Shan-Chen collide,
+    // whose ring holds densities alone, takes 4 planes in FP32 and 2 in FP64: with 16,
+    // 200x96x72 FP64 takes 341 us a step against 254, between moving walls FP32 266
+    // against 197, 8x256x256 there 381 against 284; 128^3 FP64 388 either way
+    const int most = p.model == LB_MODEL_SHAN_CHEN ? (p.storage == LB_STORE_F64 ? 2 : 4) : 16;
     if (tz <= 0 && kind == TILE_PHASE) tz = 16;
     if (tz <= 0 && kind == TILE_COLLIDE && !split_storage(p))
-        tz = (int)std::min<int64_t>(16, std::max<int64_t>(1, (int64_t)p.nz * tiles * fs.TY / 2048));
+        tz = (int)std::min<int64_t>(most, std::max<int64_t>(1, (int64_t)p.nz * tiles * fs.TY / 2048));
     if (tz <= 0) {
         // aim for 1024 workgroups, keeping chunks a few halos deep
         const int want_chunks = std::max(1, 1024 / std::max(1, tiles));
