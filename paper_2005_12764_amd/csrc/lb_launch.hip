@@ -190,12 +190,14 @@ FusedShape sc_shape(const Geom& g) {
     return fs;
 }
 // Does one pass beat two?  Within the 32-bit offsets of its row loads, where chunks are
-// three planes or more (48^3 two planes: 22 us against 17 with two passes, 512x512x1
-// 33 against 26, 64^3 26 either way) and six lanes in ten are sites (8x256x256 173
-// against 141, 33x154x225 132 against 122, 40x160x160 98 against 113).
+// three planes or more, two of full rows (48^3 two planes 22 us against 17 with two
+// passes, 64^3 25.5 against 27, 512x512x1 one plane 33 against 26), and more lanes than
+// about half are sites (8x256x256 173 against 141, 33x154x225, 0.52, 132 against 122;
+// 70x90x300, 0.55, 222 against 234, 40x160x160 98 against 113).
 bool sc_one(const Geom& g) {
     const bool fits = (uint64_t)kResArrays * sizeof(float) * (uint64_t)raw_stride((size_t)g.N) < ((uint64_t)1 << 32);
-    return fits && sc_shape(g).TZ >= 3 && 10 * g.nx >= 6 * kTX * ((g.nx + kTX - 1) / kTX);
+    const double lanes = double(g.nx) / (kTX * ((g.nx + kTX - 1) / kTX));
+    return fits && lanes >= 0.53 && sc_shape(g).TZ >= (lanes == 1.0 ? 2 : 3);
 }
 
 // Shan-Chen step (raw storage): density pass, then the collide tiles with the

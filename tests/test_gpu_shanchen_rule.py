@@ -1,5 +1,5 @@
 """Shan-Chen steps on both sides of the rule between one pass and two (FP32: chunks of
-three planes or more and six lanes in ten sites take one), and the short chunks of two
+three planes or more, two of full rows, and 0.53 of the lanes take one), and the short chunks of two
 passes, against the oracle.
 
 Tolerances: the parity tests' (FP64 1e-12, FP32 1e-5 relative L2).
@@ -14,8 +14,8 @@ from tests.helpers import oracle_params, state_errors
 pytestmark = pytest.mark.gpu
 
 TOL = {W.F64: 1e-12, W.F32: 1e-5}
-ONE = [(100, 63, 50), (64, 60, 97), (130, 33, 90), (39, 65, 130)]       # chunks of 4, 4, 6 and 5 planes
-TWO = [(64, 60, 63), (38, 65, 130), (65, 33, 90), (24, 40, 30)]         # 2 planes, or few lanes
+ONE = [(100, 63, 50), (64, 60, 97), (130, 33, 90), (34, 65, 130), (64, 60, 63)]  # chunks of 4, 4, 6, 5 and 2 planes
+TWO = [(64, 60, 31), (33, 65, 130), (100, 63, 32), (24, 40, 30)]        # 1 or 2 planes, or few lanes
 
 
 @pytest.mark.parametrize("bc", [(0, 0, 0), (0, 1, 1), (1, 0, 1)], ids=["periodic", "yz", "xz"])
