@@ -82,7 +82,7 @@ extern "C" {
 /* Tile kinds of lb_set_tiles. */
 #define LB_TILES_PHASE 0    /* phase-field pass of two-pass steps (16-bit storage) */
 #define LB_TILES_COLLIDE 1  /* collide-and-stream pass of two-pass steps */
-#define LB_TILES_ONE_READ 2 /* one-read step (rows 4, 8 or 16) */
+#define LB_TILES_ONE_READ 2 /* one-read step (rows 4, 8 or 16; 12 in 16-bit storage) */
 #define LB_TILES_BATCH 3    /* tiles of the batched step (rows 4 or 8; other values: 8 at
                                or above 8, else 4) */
 
@@ -256,7 +256,8 @@ const char* lb_last_error(void);
  * LB_*_TY / LB_*_TZ environment variables).  Lattices take the setting at
  * each step (a one-read lattice whose tile shape changed re-sums its phase
  * field before its next step); a batch takes it at lb_batch_create.  Rows
- * that do not fit the LDS budget are halved until they do.  For tools that
+ * that do not fit the LDS budget are halved until they do (one-read step: the
+ * library's choice is taken instead).  For tools that
  * time tile shapes (the package's autotuner) and for callers applying their
  * results.  Results of two-pass steps do not depend on the tile shape; the
  * one-read and batched steps' phase sums follow their tile boxes, so their

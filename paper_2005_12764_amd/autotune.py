@@ -5,8 +5,9 @@ candidate tile shape (rows of a 64-wide tile, planes of the z chunk a
 workgroup marches) of each tile kind on a seeded synthetic emulsion of that
 size, keeps the fastest, and records it in a JSON cache keyed by
 (architecture, storage, kind, box class).  ``apply`` hands the cached shapes
-to the library (``lb_set_tiles``).  The library's built-in defaults are the
-shapes this tuner picked for the 256^3 emulsion on MI355X.
+to the library (``lb_set_tiles``).  Without them the library takes an estimate
+over the lattice's sizes for the one-read step and, for two passes and batches,
+the shapes this tuner picked for the 256^3 emulsion on MI355X.
 
 Kinds: the one-read step (timed as a whole step), the two passes of the
 two-pass step (each pass timed on its own), and the batched step (timed per
@@ -37,6 +38,17 @@ CANDIDATES: Dict[int, List[Tuple[int, int]]] = {
     lb.TILES_PHASE: [(ty, tz) for ty in (4, 8, 16) for tz in (0, 16, 32, 64)],
     lb.TILES_BATCH: [(ty, tz) for ty in (4, 8) for tz in (16, 32, 64)],
 }
+
+# rows of the one-read step in 16-bit storage alone
+SPLIT_ROWS = 12
+
+
+def candidates(kind: int, storage: int) -> List[Tuple[int, int]]:
+    """The shapes to time for a kind and storage."""
+    c = CANDIDATES[kind]
+    if kind == lb.TILES_ONE_READ and storage in (W.F16, W.BF16):
+        c = c + [(SPLIT_ROWS, tz) for tz in (0, 16, 32, 64)]
+    return c
 
 
 def box_class(sites: int) -> str:
@@ -149,11 +161,11 @@ def _batch_timer(storage: int, jobs: list, steps: int):
 def tune_lattice(n: int, storage: int, arch: str, cache: dict, steps: int = 20, log=print) -> dict:
     """Tune the tile kinds a lattice of side n with this storage steps with."""
     w = W.periodic_emulsion(seed=0, n=n, storage=storage)
-    kinds = [lb.TILES_ONE_READ] if storage in (W.F64, W.F32) else []
+    kinds = [lb.TILES_ONE_READ]
     kinds += [lb.TILES_PHASE, lb.TILES_COLLIDE] if storage in (W.F16, W.BF16) else [lb.TILES_COLLIDE]
     out = {}
     for kind in kinds:
-        best, res = pick(_lattice_timer(w, storage, kind, steps), CANDIDATES[kind])
+        best, res = pick(_lattice_timer(w, storage, kind, steps), candidates(kind, storage))
         k = cache_key(arch, storage, kind, box_class(w.sites))
         cache[k] = {"ty": best[0], "tz": best[1], "ms": round(best[2], 4), "sites": w.sites,
                     "timings": res}
