@@ -32,11 +32,6 @@ template <typename R>
 __host__ __device__ constexpr R weight(int i) {
     return Lattice::len2(i) == 0 ? R(1) / R(3) : (Lattice::len2(i) == 1 ? R(1) / R(18) : R(1) / R(36));
 }
-// B_i of the perturbation operator: -1/3, 1/18, 1/36 by shell.
-template <typename R>
-__host__ __device__ constexpr R bpert(int i) {
-    return Lattice::len2(i) == 0 ? -R(1) / R(3) : (Lattice::len2(i) == 1 ? R(1) / R(18) : R(1) / R(36));
-}
 // 1/|c_i| (0 for the rest vector, whose recolouring term vanishes).
 template <typename R>
 __host__ __device__ constexpr R inv_clen(int i) {
@@ -330,26 +325,12 @@ __device__ __forceinline__ void collide_sc(R (&t)[Q], R (&d)[Q], R bx, R by, R b
     }
 }
 
-// Shifted variables from the two components and back.
-template <typename R>
-__device__ __forceinline__ void to_shifted(int i, R fr, R fb, R& t, R& d) {
-    t = (fr + fb) - weight<R>(i);
-    d = fr - fb;
-}
+// The two components from the shifted variables.
 template <typename R>
 __device__ __forceinline__ void from_shifted(int i, R t, R d, R& fr, R& fb) {
     const R f = weight<R>(i) + t;
     fr = R(0.5) * (f + d);
     fb = R(0.5) * (f - d);
-}
-
-// Equilibrium divided by the density, for the 16-bit codec and init.
-template <typename R>
-__device__ __forceinline__ R feq_unit(int i, R ux, R uy, R uz) {
-    using L = Lattice;
-    const R cu = cdot3<R>(i, ux, uy, uz);
-    const R uu = ux * ux + uy * uy + uz * uz;
-    return weight<R>(i) * (R(1) + R(3) * cu + R(4.5) * cu * cu - R(1.5) * uu);
 }
 
 // G = 3 sum_i w_i phi_i c_i from the 18 neighbour values, phi(i) the value at

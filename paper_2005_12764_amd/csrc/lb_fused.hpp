@@ -59,10 +59,6 @@ template <typename R, int TX, int H>
 __host__ __device__ constexpr size_t phi_ring_bytes(int TY) {
     return (size_t)(2 * H + 1) * (TY + 2 * H) * (TX + 2 * H) * sizeof(R);
 }
-template <int TX>
-__host__ __device__ constexpr size_t rec_ring_bytes(int TY) {
-    return (size_t)3 * (TY + 2) * (TX + 2) * 2 * sizeof(f4);
-}
 
 // Copy the records of plane q (tile plus one site) into a ring slot.
 template <typename Src, int TX>

@@ -44,7 +44,6 @@ __device__ __forceinline__ int wave_uniform(int v) { return __builtin_amdgcn_rea
 constexpr int kResArrays = 10;
 constexpr int kResPairs = 4;
 constexpr unsigned kRsrcWord3 = 0x00020000;  // raw 32-bit buffer on gfx9-family targets
-typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 // (t, d) pair loads
 __device__ __forceinline__ void res_load_pair(float& t, float& d, __amdgpu_buffer_rsrc_t r, unsigned voff,

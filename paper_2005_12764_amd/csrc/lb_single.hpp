@@ -129,9 +129,6 @@ constexpr size_t kLdsBytes = 163840;   // LDS of a workgroup on gfx950
 // Own box of a site: its tile column [x0, x1) x [y0, y1) and z chunk [z0, z1).
 struct OwnBox {
     int x0, x1, y0, y1, z0, z1;
-    __device__ __forceinline__ bool has(int x, int y, int z) const {
-        return x >= x0 && x < x1 && y >= y0 && y < y1 && z >= z0 && z < z1;
-    }
 };
 
 template <int TX, int TY>
@@ -250,22 +247,6 @@ __global__ __launch_bounds__(256) void part_kernel(Geom g, Src src, int TZ, Part
     const bool hi = (x % TX == TX - 1 || x == g.nx - 1) && !(g.wx && x == g.nx - 1);
     if (lo) xf[xface_at(g, x / TX, 0, y, z)] = xface_sum<R, 1>(g, src, b, s, x, y, z);
     if (hi) xf[xface_at(g, x / TX, 1, y, z)] = xface_sum<R, -1>(g, src, b, s, x, y, z);
-}
-
-// Walls next to a site: direction i arriving there is a bounce-back exactly
-// when its upstream site lies beyond one of them (the test pull_source makes,
-// without computing the upstream index).
-struct WallFlags {
-    bool xlo, xhi, ylo, yhi, zlo, zhi;
-};
-__device__ __forceinline__ WallFlags wall_flags(const Geom& g, int x, int y, int z) {
-    return WallFlags{g.wx && x == 0, g.wx && x == g.nx - 1, g.wy && y == 0,
-                     g.wy && y == g.ny - 1, g.wz && z == 0, g.wz && z == g.nz - 1};
-}
-__device__ __forceinline__ bool reflected(int i, const WallFlags& w) {
-    using L = Lattice;
-    return (L::cx[i] > 0 && w.xlo) || (L::cx[i] < 0 && w.xhi) || (L::cy[i] > 0 && w.ylo) ||
-           (L::cy[i] < 0 && w.yhi) || (L::cz[i] > 0 && w.zlo) || (L::cz[i] < 0 && w.zhi);
 }
 
 // Faces of a site's own box along one axis: lo = first coordinate of its
