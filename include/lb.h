@@ -69,15 +69,17 @@ extern "C" {
 #define LB_STORE_BF16 3 /* as LB_STORE_F16 with bf16 deviations (no scale) */
 
 /* Kernel selection for lb_step. */
-#define LB_KERNEL_AUTO 0    /* the one-read step, except (two-pass) for the Shan-Chen model,
-                               lattices too large for its 32-bit buffer offsets and some
+#define LB_KERNEL_AUTO 0    /* the one-read step, except (LB_KERNEL_TWOPASS) for the
+                               Shan-Chen model, lattices too large for its 32-bit buffer offsets and some
                                FP64 ones between moving walls with the widest probe */
-#define LB_KERNEL_TWOPASS 1 /* phase-field pass, then collide-and-stream pass */
+#define LB_KERNEL_TWOPASS 1 /* phase-field pass, then collide-and-stream pass (Shan-Chen: a
+                               density pass, or both in one pass in FP32 where that pays) */
 #define LB_KERNEL_FUSED 2   /* one-read step: the collide-and-stream tiles also gather the
                                next phase field's sums, a light pass adds the terms
                                that cross tiles; every population is read once per
-                               step.  The first step of a 16-bit lattice with moving
-                               walls takes two passes. */
+                               step.  Two passes all the same: a 16-bit lattice's first
+                               step beyond the 32-bit buffer offsets, and those of moving
+                               walls beyond them */
 
 /* Tile kinds of lb_set_tiles. */
 #define LB_TILES_PHASE 0    /* phase-field pass of two-pass steps (16-bit storage) */
@@ -131,7 +133,8 @@ typedef struct {
                                on each component k (k' the other one; a neighbour beyond a
                                wall is its mirror image), entering each component's
                                exact-difference source with its share (rho_k/rho) of the
-                               body force.  Raw storage (F64, F32) and two-pass steps only. */
+                               body force.  Raw storage (F64, F32) only, stepped as
+                               LB_KERNEL_TWOPASS says. */
     double g_sc;            /* Shan-Chen coupling G_C (> 0 repels the components) */
 } lb_params;
 

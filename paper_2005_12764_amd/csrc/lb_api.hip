@@ -66,7 +66,7 @@ int validate_params(const lb_params* p, std::string& why) {
         if (p->storage != LB_STORE_F64 && p->storage != LB_STORE_F32)
             return why = "the Shan-Chen model needs raw storage (LB_STORE_F64 or LB_STORE_F32)", LB_EINVAL;
         if (p->kernel == LB_KERNEL_FUSED)
-            return why = "the Shan-Chen model steps with two passes (LB_KERNEL_AUTO or LB_KERNEL_TWOPASS)", LB_EINVAL;
+            return why = "the Shan-Chen model has no one-read step (LB_KERNEL_AUTO or LB_KERNEL_TWOPASS)", LB_EINVAL;
     }
     return LB_OK;
 }
