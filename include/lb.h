@@ -70,8 +70,9 @@ extern "C" {
 
 /* Kernel selection for lb_step. */
 #define LB_KERNEL_AUTO 0    /* the one-read step, except (LB_KERNEL_TWOPASS) for the
-                               Shan-Chen model, lattices too large for its 32-bit buffer offsets and some
-                               FP64 ones between moving walls with the widest probe */
+                               Shan-Chen model, lattices too large for its 32-bit buffer
+                               offsets and some FP64 ones between moving walls with the
+                               widest probe */
 #define LB_KERNEL_TWOPASS 1 /* phase-field pass, then collide-and-stream pass (Shan-Chen: a
                                density pass, or both in one pass in FP32 where that pays) */
 #define LB_KERNEL_FUSED 2   /* one-read step: the collide-and-stream tiles also gather the

@@ -23,9 +23,11 @@
 // per SIMD: 16 rows, four wavefronts per SIMD, take 0.70 ms, 4.8 TB/s (0.77 with
 // 8 rows of 64 x 128 planes).  Left out in turn, probe, decode, phase sums and
 // collision give 4 % each: memory bounds it.  16-bit storage moves 2.78 GB, 0.53
-// ms, and issues 0.43: 12 rows, three wavefronts, take 0.71 ms, 8 rows 0.79; a
-// probe less is 10 % less there.  Everything a plane needs from memory is loaded
-// while the plane before it is collided.
+// ms, and issues 0.43: with droplets over a twentieth of the volume 12 rows, three
+// wavefronts, take 0.71 ms, 8 rows 0.79, and a probe less is 10 % less; with 30 %,
+// the emulsion of bench.py, whose probes are the more, 12 rows take 0.80 ms.
+// Everything a plane needs from memory is loaded while the plane before it is
+// collided.
 #pragma once
 #include "lb_pack.hpp"
 #include "lb_single.hpp"
