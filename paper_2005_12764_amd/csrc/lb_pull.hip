@@ -21,8 +21,8 @@ int status(const char* what) {
 // keep up with memory, and tiles save the records' traffic.  Moments and totals of
 // large lattices: from 0.7 (256^3 FP32 393 us against 442 and 375 against 555;
 // 80x458x458, 0.62, 591 against 447); smaller ones: moments from 0.8 without walls
-// (128x91x91 26 against 29, between walls 34 against 30), FP64 totals (64^3 45 against
-// 53).  Export is bound by its stores: from 0.9 (64x256x256 208 against 229;
+// (128x91x91 26 against 29, between walls 34 against 30; full rows of 2^18 sites, 64^3
+// 7.9 against 8.6), FP64 totals (64^3 45 against 53).  Export is bound by its stores: from 0.9 (64x256x256 208 against 229;
 // 80x229x229 354 against 254).
 enum Reading { MOMENTS, EXPORT, TOTALS };
 bool tiles_pay(const LatticeView& v, Reading what) {
@@ -34,7 +34,7 @@ bool tiles_pay(const LatticeView& v, Reading what) {
     if (what == EXPORT) return v.g.N >= 1 << 20 && used >= 0.9;
     if (v.g.N >= 1 << 21) return used >= 0.7;
     if (what == TOTALS) return f64 && v.g.N >= 1 << 18 && used >= 0.8;
-    return v.g.N >= (f64 ? 1 << 18 : 1 << 19) && used >= 0.8 && !(v.g.wx || v.g.wy || v.g.wz);
+    return v.g.N >= 1 << 18 && used >= (f64 || v.g.N >= 1 << 19 ? 0.8 : 1.0) && !(v.g.wx || v.g.wy || v.g.wz);
 }
 
 // fn(policy) of the current state; taken = false where the state is in pair arrays,
