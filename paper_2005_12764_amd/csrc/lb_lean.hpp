@@ -19,11 +19,11 @@
 //
 // What bounds it: at 256^3 FP32 moves 3.34 GB (92 B per site each way, the phase
 // field, halos of records), 0.59 ms at the rate its access pattern reaches
-// without arithmetic (lb_pattern_ms), and issues 0.33 ms of vector instructions
+// without arithmetic (lb_pattern_ms), and issues 0.40 ms of vector instructions
 // per SIMD: 16 rows, four wavefronts per SIMD, take 0.70 ms, 4.8 TB/s (0.77 with
 // 8 rows of 64 x 128 planes).  Left out in turn, probe, decode, phase sums and
 // collision give 4 % each: memory bounds it.  16-bit storage moves 2.78 GB, 0.53
-// ms, and issues 0.43: with droplets over a twentieth of the volume 12 rows, three
+// ms, and issues 0.46: with droplets over a twentieth of the volume 12 rows, three
 // wavefronts, take 0.71 ms, 8 rows 0.79, and a probe less is 10 % less; with 30 %,
 // the emulsion of bench.py, whose probes are the more, 12 rows take 0.80 ms.
 // Everything a plane needs from memory is loaded while the plane before it is
